@@ -264,7 +264,7 @@ struct F32Src {
 // block against the product's edge, in the loop the products ran at a quarter of the fp32 MFMA rate.
 template <int TS>
 struct F32Tiles {
-    static constexpr int BK = 16, LDT = TS + 4;
+    static constexpr int BK = kSymStep, LDT = TS + 4;
     float a[2][BK][LDT], b[2][BK][LDT];   // two tile buffers: one barrier per k-step
 };
 
@@ -286,11 +286,12 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
     // on two XCDs, 106 us).
     const int nxm = (v.N + TS - 1) / TS, nym = (v.M + TS - 1) / TS;   // this matrix's own tiles
     // symmetric results: nym (nym + 1) / 2 tiles, one work item each per plane
-    SymPlanes sp{nullptr, 0, 1};
+    SymPlanes sp{nullptr, 0, 1, 0};
     if (SYM) sp = sym_planes(op, md, chunk);
     // the projection of a small layer set is cut along the contraction as well
     const bool split = !SYM && op == OP_PROJECT_F32 && md.proj_chunks > 0;
-    if (split) sp = SymPlanes{step_scratch<float>(dyn, md.proj_parts_off), 0, md.proj_chunks};
+    if (split)
+        sp = SymPlanes{step_scratch<float>(dyn, md.proj_parts_off), 0, md.proj_chunks, (long long)md.proj_rows * md.ldn};
     const int items = (SYM ? nym * (nym + 1) / 2 : nxm * nym) * sp.count;
     const int per = (items + 7) / 8;
     const int slot = (int)(blockIdx.x / 8);
@@ -308,7 +309,7 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
         v.A = (const unsigned char*)v.A + (long long)k0 * v.sAk * (ABF ? 2 : 4);
         v.B = (const unsigned char*)v.B + (long long)k0 * v.sBk * (BBF ? 2 : 4);
         v.K = v.K - k0 < kc ? v.K - k0 : kc;
-        v.C = sp.p + plane * (SYM ? (long long)sp.order * sp.order : (long long)md.proj_rows * md.ldn);
+        v.C = sp.p + plane * sp.pitch;
     }
     if (SYM) {
         int ti = 0;
@@ -517,8 +518,7 @@ hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int
     const bool by_side = (left.sAi == 1) != (right.sAi == 1) || (left.sBj == 1) != (right.sBj == 1);
     auto count = [&](int ts) {
         const long long nx = (max_n + ts - 1) / ts, ny = (max_m + ts - 1) / ts;
-        const long long planes = (max_k + chunk - 1) / chunk;
-        return left.sym ? ny * (ny + 1) / 2 * (planes < kSymPlanesMax ? planes : kSymPlanesMax)
+        return left.sym ? ny * (ny + 1) / 2 * sym_plane_count(max_k, chunk)
                         : nx * ny * (op == OP_PROJECT_F32 && max_split > 1 ? max_split : 1);
     };
     // (a split projection is a small one: its chunks were counted in 64 x 64 tiles)

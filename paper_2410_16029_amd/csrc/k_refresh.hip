@@ -211,9 +211,9 @@ __global__ __launch_bounds__(256) void k_chol_update(const MatDev* __restrict__ 
 __global__ __launch_bounds__(256) void k_sum_planes(const MatDev* __restrict__ mats, int op, int chunk) {
     const MatDev& md = mats[blockIdx.y];
     const SymPlanes sp = sym_planes(op, md, chunk);
-    const long long nn = sp.order, pitch = nn * nn;
+    const long long nn = sp.order, pitch = sp.pitch;
     double* __restrict__ T = md.T;
-    for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < pitch; q += (long long)gridDim.x * 256) {
+    for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < nn * nn; q += (long long)gridDim.x * 256) {
         const long long i = q / nn, j = q - i * nn;
         if (j > i) continue;
         double v = 0.0;
@@ -513,7 +513,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void k_inverse_factor(const MatDe
     const MatDev& md = mats[blockIdx.x];
     const SymPlanes sp = sym_planes(op, md, chunk);
     const int nn = sp.order, nb = (nn + 31) / 32;
-    const long long pitch = (long long)nn * nn;
+    const long long pitch = sp.pitch;
     double* Am = fac_smem;                              // the diagonal block
     double* Dm = Am + kFacBlock;                        // its inverse factor
     double* Lp = Dm + kFacBlock;                        // block rows 1 .. of the panel (block i at i - 1)
@@ -741,8 +741,8 @@ __global__ __launch_bounds__(64) void k_inverse_factor_small(const MatDev* __res
 #pragma unroll
     for (int x = 0; x < 16; ++x) v[x] = c == 2 * x + h && c >= nn ? 1.0 : 0.0;      // identity past the order
     for (int y = 0; y < sp.count; y += 2) {
-        const float* __restrict__ p0 = sp.p + (long long)y * nn * nn;
-        const float* __restrict__ p1 = y + 1 < sp.count ? p0 + nn * nn : p0;
+        const float* __restrict__ p0 = sp.p + y * sp.pitch;
+        const float* __restrict__ p1 = y + 1 < sp.count ? p0 + sp.pitch : p0;
         float f[2][16];
 #pragma unroll
         for (int x = 0; x < 16; ++x) {

@@ -774,7 +774,8 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
         st->n_dots = (int)dots.size();
         // The contraction of a symmetric product is cut so that the set gives about 2048 workgroups of one
         // 128 x 128 tile each (eight per CU: their lengths differ by the matrices' row counts), but not
-        // below 128 (64 for orders up to 64): a plane is also read back.
+        // below 128 (64 for orders up to 64): a plane is also read back.  (sym_planes bounds a run by half of
+        // the contraction: a large set would otherwise get longer ones.)
         for (int op = 0; op < OP_COUNT; ++op) {
             double work = 0.0;
             for (const MatDev& md : st->mats) {

@@ -214,15 +214,28 @@ enum GemmOp {
 };
 void gemm_f32_dims(int op, const MatDev& md, int* M, int* N, int* K);
 
-// A symmetric product C = X^T X is left as `count` float planes [order][order], one per run of about
-// `chunk` of the contraction, lower tiles only: C(i, j) is their sum, which the kernel that reads it forms
-// in fp64.  The planes lie in the sketch buffer that is free at that point of the refresh ([max(m,n)][l]
-// floats): Ya while Yb is orthonormalised and for the new projector's Gram matrix, Yb otherwise.
+// A symmetric product C = X^T X is left as `count` float planes [order][order], `pitch` apart, one per run of the
+// contraction, lower tiles only: C(i, j) is their sum, which the kernel that reads it forms in fp64.  A run is
+// about `chunk` long and never longer than half of the contraction, whatever else is in the layer set: one run of
+// 2048 rows instead of two of 1024 left the column norms of the 1.1B set's projectors 6.4e-7 from 1 (rms) instead of
+// 4.0e-7, one of 600 instead of 304 (600 x 600, rank 512) 3.3e-7 instead of 1.8e-7.
+// The planes lie in the sketch buffer that is free at that point of the refresh ([max(m,n)][l] floats): Ya
+// while Yb is orthonormalised and for the new projector's Gram matrix, Yb otherwise.  An order above half of its
+// rows leaves room for one plane there; the second then goes to the head of another buffer that is free: the sketch
+// buffer that the next product fills (while an orthonormalisation runs), Yc for B B^T, and Bm once the
+// rotation staged in it has been applied.  Each holds at least order^2 floats, because order <= l <= m, n.
 constexpr int kSymPlanesMax = 8;
+constexpr int kSymStep = 16;       // k-step of the products: what a contraction up to this long is not cut into
 struct SymPlanes {
     float* p;
     int order, count;
+    long long pitch;               // floats from one plane to the next
 };
+// planes that a contraction of length k is cut into where there is room
+__host__ __device__ inline int sym_plane_count(int k, int chunk) {
+    const int least = k > kSymStep ? 2 : 1, want = (k + chunk - 1) / chunk;
+    return want < least ? least : want < kSymPlanesMax ? want : kSymPlanesMax;
+}
 __host__ __device__ inline SymPlanes sym_planes(int op, const MatDev& md, int chunk) {
     SymPlanes s;
     s.p = (op == OP_GRAM_B || op == OP_GRAM_CB || op == OP_GRAM_P) ? md.Ya : md.Yb;
@@ -230,9 +243,14 @@ __host__ __device__ inline SymPlanes sym_planes(int op, const MatDev& md, int ch
     const int k = (op == OP_GRAM_A || op == OP_GRAM_CA || op == OP_GRAM_P) ? md.m : md.n;
     const int rows = md.m > md.n ? md.m : md.n;
     const int room = rows / s.order;       // (order <= l: at least this many)
-    s.count = (k + chunk - 1) / chunk;
-    if (s.count > kSymPlanesMax) s.count = kSymPlanesMax;
-    if (s.count > room) s.count = room;
+    s.count = sym_plane_count(k, chunk);
+    s.pitch = (long long)s.order * s.order;
+    if (s.count > room && room > 1) s.count = room;
+    if (s.count > room) {
+        const float* second = op == OP_GRAM_P ? md.Bm : op == OP_GRAM_CA ? md.Ya : op == OP_GRAM_CB ? md.Yb : md.Yc;
+        s.count = 2;
+        s.pitch = second - s.p;
+    }
     return s;
 }
 // max_m, max_n, max_k: largest dimensions of the product over the layer set (grid and tile choice)

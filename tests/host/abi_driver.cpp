@@ -10,7 +10,7 @@
 #include <vector>
 
 #include "ng.h"
-#include "ng_internal.h"   // ng::xcd_order, ng::TileRef (internal, host side)
+#include "ng_internal.h"   // ng::xcd_order, ng::TileRef, ng::sym_planes (internal, host side)
 
 static int g_failed = 0;
 #define CHECK(cond)                                                         \
@@ -106,8 +106,61 @@ static void check_tile_order() {
     for (size_t x = 0; x < 8; ++x) CHECK(run_cost[x] * 8 >= total - 8LL * 5461 && run_cost[x] * 8 <= total + 8LL * 5461);
 }
 
+// The partial planes of the refresh's symmetric products: no run of fp32 sums longer than half of the contraction
+// (rounded up to a k-step), whatever the set's run length; planes disjoint and inside buffers that hold nothing
+// at that point of the refresh.
+static void check_sym_planes() {
+    const int shapes[][3] = {{2048, 2048, 512}, {5461, 2048, 512}, {2048, 5461, 512}, {600, 600, 512}, {512, 512, 512}, {200, 200, 128},
+                             {1000, 1000, 900}, {256, 512, 32}, {33, 40, 33}, {17, 17, 1}, {16, 16, 16}, {1, 12, 1}, {12, 1, 1}};
+    const int ops[] = {ng::OP_GRAM_A, ng::OP_GRAM_B, ng::OP_GRAM_CA, ng::OP_GRAM_CB, ng::OP_B_BT, ng::OP_GRAM_P};
+    for (const auto& sh : shapes)
+        for (int chunk : {64, 128, 640, 2112, 2496, 1 << 20})
+            for (int low_memory = 0; low_memory < 2; ++low_memory)
+                for (int op : ops) {
+                    ng::MatDev md{};
+                    md.m = sh[0];
+                    md.n = sh[1];
+                    md.r = md.l = sh[2];
+                    md.ldn = (md.n + 7) / 8 * 8;
+                    const long long y = (long long)(md.m > md.n ? md.m : md.n) * md.l;
+                    float* at = (float*)(uintptr_t)(1ull << 40);     // (addresses only, nothing is read)
+                    struct Range { float* p; long long n; } ya{at, y}, yb{at + 2 * y, y}, yc{at + 4 * y, y}, bm{at + 6 * y, (long long)md.l * md.ldn};
+                    md.Ya = ya.p;
+                    md.Yb = yb.p;
+                    md.Yc = yc.p;
+                    md.Bm = bm.p;
+                    md.P = low_memory ? md.Yb : at + 8 * y + bm.n;
+                    std::vector<Range> unused;
+                    if (op == ng::OP_GRAM_A) unused = {yb, yc};             // input Ya, Yc is filled next
+                    if (op == ng::OP_GRAM_B) unused = {ya, yc};             // input Yb, Yc is filled next
+                    if (op == ng::OP_GRAM_CA) unused = {ya, yb};            // input Yc, Ya is filled next
+                    if (op == ng::OP_GRAM_CB) unused = {ya, yb};            // input Yc, Yb is filled next
+                    if (op == ng::OP_B_BT) unused = {yb, yc};               // input Bm, Ya is the basis
+                    if (op == ng::OP_GRAM_P) unused = low_memory ? std::vector<Range>{ya, bm} : std::vector<Range>{ya, yb, bm};   // Yc: the old projector
+                    const ng::SymPlanes sp = ng::sym_planes(op, md, chunk);
+                    int M, N, K;
+                    ng::gemm_f32_dims(op, md, &M, &N, &K);
+                    CHECK(sp.order == M && M == N && sp.count >= 1 && sp.count <= ng::kSymPlanesMax);
+                    auto run = [&](int count) { return ((K + count - 1) / count + ng::kSymStep - 1) / ng::kSymStep * ng::kSymStep; };
+                    CHECK(run(sp.count) <= run(2));
+                    CHECK(sp.count <= ng::sym_plane_count(K, chunk));        // (what the grid is sized for)
+                    for (int a = 0; a < sp.count; ++a) {
+                        const float* pa = sp.p + a * sp.pitch;
+                        const long long len = (long long)sp.order * sp.order;
+                        int inside = 0;
+                        for (const Range& u : unused) inside += pa >= u.p && pa + len <= u.p + u.n;
+                        CHECK(inside == 1);
+                        for (int b = 0; b < a; ++b) {
+                            const float* pb = sp.p + b * sp.pitch;
+                            CHECK(pa + len <= pb || pb + len <= pa);
+                        }
+                    }
+                }
+}
+
 int main() {
     check_tile_order();
+    check_sym_planes();
     ng_hparams hp;
     CHECK(ng_default_hparams(&hp) == NG_OK);
     CHECK(ng_default_hparams(nullptr) == NG_ERR_INVALID_ARG);

@@ -1488,14 +1488,9 @@ __global__ __launch_bounds__(kSortThreads) void k_ritz_sort(const MatDev* __rest
     __threadfence_block();
     bool bad = false;
     for (int i = threadIdx.x; i < lp; i += kSortThreads) {
-        const double vi = md.ritz[i];
-        int rank = 0;
-        for (int j = 0; j < lp; ++j) {
-            const double vj = md.ritz[j];
-            rank += (vj > vi) || (vj == vi && j < i);
-        }
-        md.order[rank] = i;
-        if (rank < md.r && !(vi > 0.0)) bad = true;
+        const int place = ritz_place(md.ritz, lp, i);
+        md.order[place] = i;
+        if (place < md.r && !(md.ritz[i] > 0.0)) bad = true;
     }
     if (bad) atomicOr(status, 8);
     // no sweep without a rotation was seen before the sweep limit

@@ -307,6 +307,19 @@ hipError_t launch_transform_adam(const MatDev* mats, const MatDyn* dyn, const Ti
                                  StepScalars sc, int grad_dtype, int* status, hipStream_t stream);
 hipError_t launch_make_bf16_copies(const MatDev* mats, int n_mats, int max_m, int max_r, hipStream_t stream);
 
+// Place of value i among n, largest first and equal ones by index.  A NaN (non-finite gradient) comes after every number:
+// the places are a permutation whatever the values, so every entry of the order that is written from them is
+// an index (with NaN comparing false, all NaN values had place 0 and the other entries kept what the workspace held).
+__host__ __device__ inline int ritz_place(const double* v, int n, int i) {
+    const double vi = v[i] == v[i] ? v[i] : -1.0;
+    int place = 0;
+    for (int j = 0; j < n; ++j) {
+        const double vj = v[j] == v[j] ? v[j] : -1.0;
+        place += (vj > vi) || (vj == vi && j < i);
+    }
+    return place;
+}
+
 // refresh helpers (k_refresh.hip)
 hipError_t launch_fill_gaussian(const MatDev* mats, int n_mats, int max_rows, unsigned long long seed,
                                 unsigned long long call_id, hipStream_t stream);   // fills Yb (n x l)

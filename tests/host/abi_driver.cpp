@@ -10,7 +10,7 @@
 #include <vector>
 
 #include "ng.h"
-#include "ng_internal.h"   // ng::xcd_order, ng::TileRef, ng::sym_planes (internal, host side)
+#include "ng_internal.h"   // ng::xcd_order, ng::TileRef, ng::sym_planes, ng::ritz_place (internal, host side)
 
 static int g_failed = 0;
 #define CHECK(cond)                                                         \
@@ -158,8 +158,29 @@ static void check_sym_planes() {
                 }
 }
 
+// The order of the Ritz values is a permutation whatever they are, numbers descending before NaN.
+static void check_ritz_order() {
+    const double nan = __builtin_nan(""), inf = __builtin_inf();
+    const std::vector<std::vector<double>> cases = {{3, 1, 2, 2, 0, 0}, {nan, nan, nan, nan}, {0, nan, 5, nan, 0, 7}, {inf, nan, inf, 1}, {0, 0, 0}};
+    for (const auto& v : cases) {
+        const int n = (int)v.size();
+        std::vector<int> order(n, -1);
+        for (int i = 0; i < n; ++i) {
+            const int p = ng::ritz_place(v.data(), n, i);
+            CHECK(p >= 0 && p < n && order[p] < 0);
+            if (p >= 0 && p < n) order[p] = i;
+        }
+        for (int p = 0; p < n; ++p) CHECK(order[p] >= 0);
+        for (int p = 1; p < n; ++p) {
+            const double a = v[order[p - 1] < 0 ? 0 : order[p - 1]], b = v[order[p] < 0 ? 0 : order[p]];
+            CHECK(b != b || a > b || (a == b && order[p - 1] < order[p]));
+        }
+    }
+}
+
 int main() {
     check_tile_order();
+    check_ritz_order();
     check_sym_planes();
     ng_hparams hp;
     CHECK(ng_default_hparams(&hp) == NG_OK);

@@ -270,7 +270,8 @@ struct F32Tiles {
 
 template <int TS, bool AI, bool BJ, bool ABF, bool BBF, bool SYM>
 __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__ mats, const MatDyn* __restrict__ dyn,
-                                              int grad_dtype, const StepScalars& sc, int chunk, F32Tiles<TS>& lds) {
+                                              int grad_dtype, const StepScalars& sc, const SymPlanes* __restrict__ sym,
+                                              F32Tiles<TS>& lds) {
     constexpr int BK = F32Tiles<TS>::BK, LDT = F32Tiles<TS>::LDT;
     constexpr int NB = TS / 64;          // 32 x 32 blocks per wavefront and dimension
     typedef F32Src<TS, BK, AI, ABF> SA;
@@ -287,7 +288,7 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
     const int nxm = (v.N + TS - 1) / TS, nym = (v.M + TS - 1) / TS;   // this matrix's own tiles
     // symmetric results: nym (nym + 1) / 2 tiles, one work item each per plane
     SymPlanes sp{nullptr, 0, 1, 0};
-    if (SYM) sp = sym_planes(op, md, chunk);
+    if (SYM) sp = sym[blockIdx.z];
     // the projection of a small layer set is cut along the contraction as well
     const bool split = !SYM && op == OP_PROJECT_F32 && md.proj_chunks > 0;
     if (split)
@@ -439,10 +440,10 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
 template <int TS, bool AI, bool BJ, bool ABF, bool BBF, bool SYM>
 __global__ __launch_bounds__(256, TS == 128 ? 3 : 6) void k_gemm_f32(int op, const MatDev* __restrict__ mats,
                                                   const MatDyn* __restrict__ dyn, int grad_dtype,
-                                                  StepScalars sc, int chunk, int side) {
+                                                  StepScalars sc, const SymPlanes* __restrict__ sym, int side) {
     __shared__ __attribute__((aligned(16))) F32Tiles<TS> lds;
     if (side >= 0 && mats[blockIdx.z].side != side) return;
-    gemm_f32_tile<TS, AI, BJ, ABF, BBF, SYM>(op, mats, dyn, grad_dtype, sc, chunk, lds);
+    gemm_f32_tile<TS, AI, BJ, ABF, BBF, SYM>(op, mats, dyn, grad_dtype, sc, sym, lds);
 }
 
 // fp32 layer sets with both sides: AL / BL are a left-side matrix's layouts, AR / BR a right-side one's.  A launch
@@ -453,21 +454,23 @@ __global__ __launch_bounds__(256, TS == 128 ? 3 : 6) void k_gemm_f32_sides(int o
                                                   const MatDyn* __restrict__ dyn, StepScalars sc) {
     __shared__ __attribute__((aligned(16))) F32Tiles<TS> lds;
     if (mats[blockIdx.z].side == NG_SIDE_RIGHT)
-        gemm_f32_tile<TS, AR, BR, false, false, false>(op, mats, dyn, NG_F32, sc, 0, lds);
+        gemm_f32_tile<TS, AR, BR, false, false, false>(op, mats, dyn, NG_F32, sc, nullptr, lds);
     else
-        gemm_f32_tile<TS, AL, BL, false, false, false>(op, mats, dyn, NG_F32, sc, 0, lds);
+        gemm_f32_tile<TS, AL, BL, false, false, false>(op, mats, dyn, NG_F32, sc, nullptr, lds);
 }
 
 // max_m, max_n, max_k: the largest dimensions of this product over the layer set.  The 128 tile is used
 // when neither side nor the contraction is short (a short side wastes most of a big tile, a short
 // contraction leaves only the read-modify-write of the output, which wants many small workgroups) and
-// its tiles are enough to fill the chip twice.
+// its tiles, counted as if every matrix were as large as the largest, are 512 or more.  (Sets of unequal matrices have
+// fewer: the 60M set's products Y L^-T are counted as 616 and are 280 or 336, one to two per CU.)
 template <int TS>
 static void run_gemm_f32(dim3 g, int op, const MatDev* mats, const MatDyn* dyn, int grad_dtype, StepScalars sc,
-                         bool ai, bool bj, bool abf, bool bbf, bool sym, int chunk, int side, hipStream_t stream) {
+                         bool ai, bool bj, bool abf, bool bbf, bool sym,
+                         const SymPlanes* planes, int side, hipStream_t stream) {
 #define NG_GEMM_CASE(AI, BJ, ABF, BBF, SYM)                                                                      \
     if (ai == AI && bj == BJ && abf == ABF && bbf == BBF && sym == SYM) {                                        \
-        k_gemm_f32<TS, AI, BJ, ABF, BBF, SYM><<<g, dim3(256), 0, stream>>>(op, mats, dyn, grad_dtype, sc, chunk, side); \
+        k_gemm_f32<TS, AI, BJ, ABF, BBF, SYM><<<g, dim3(256), 0, stream>>>(op, mats, dyn, grad_dtype, sc, planes, side); \
         return;                                                                                                  \
     }
     NG_GEMM_CASE(true, true, false, false, true)      // the Gram matrices of the sketch and of P
@@ -505,8 +508,8 @@ static bool run_gemm_f32_sides(dim3 g, int op, const MatDev* mats, const MatDyn*
 // weight read their operands along other dimensions on the right side: one kernel with both forms for fp32 sets that
 // have both sides, else one launch per side that is present.
 hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int n_mats, int max_m, int max_n,
-                           int max_k, int grad_dtype, StepScalars sc, int chunk, int max_split, int sides,
-                           hipStream_t stream) {
+                           int max_k, int grad_dtype, StepScalars sc, int max_split, const SymPlanes* sym,
+                           int sides, hipStream_t stream) {
     // layouts and types of the operands are properties of the product and the side
     auto view = [&](int side) {
         MatDev probe{};
@@ -518,8 +521,7 @@ hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int
     const bool by_side = (left.sAi == 1) != (right.sAi == 1) || (left.sBj == 1) != (right.sBj == 1);
     auto count = [&](int ts) {
         const long long nx = (max_n + ts - 1) / ts, ny = (max_m + ts - 1) / ts;
-        return left.sym ? ny * (ny + 1) / 2 * sym_plane_count(max_k, chunk)
-                        : nx * ny * (op == OP_PROJECT_F32 && max_split > 1 ? max_split : 1);
+        return (left.sym ? ny * (ny + 1) / 2 : nx * ny) * (max_split > 1 ? max_split : 1);
     };
     // (a split projection is a small one: its chunks were counted in 64 x 64 tiles)
     const bool big = max_m >= 128 && max_n >= 128 && max_k >= 64 && count(128) * n_mats >= 512 &&
@@ -533,8 +535,8 @@ hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int
         if (by_side ? !(sides & (1 << side)) : side == 1) continue;
         const GemmView& v = side == NG_SIDE_RIGHT && by_side ? right : left;
         const int filter = by_side && sides == 3 ? side : -1;
-        if (big) run_gemm_f32<128>(g, (int)op, mats, dyn, grad_dtype, sc, v.sAi == 1, v.sBj == 1, v.a_bf16, v.b_bf16, v.sym != 0, chunk, filter, stream);
-        else run_gemm_f32<64>(g, (int)op, mats, dyn, grad_dtype, sc, v.sAi == 1, v.sBj == 1, v.a_bf16, v.b_bf16, v.sym != 0, chunk, filter, stream);
+        if (big) run_gemm_f32<128>(g, (int)op, mats, dyn, grad_dtype, sc, v.sAi == 1, v.sBj == 1, v.a_bf16, v.b_bf16, v.sym != 0, sym, filter, stream);
+        else run_gemm_f32<64>(g, (int)op, mats, dyn, grad_dtype, sc, v.sAi == 1, v.sBj == 1, v.a_bf16, v.b_bf16, v.sym != 0, sym, filter, stream);
     }
     return hipGetLastError();
 }

@@ -208,9 +208,9 @@ __global__ __launch_bounds__(256) void k_chol_update(const MatDev* __restrict__ 
 }
 
 // T (lower triangle) = the sum of a symmetric product's planes
-__global__ __launch_bounds__(256) void k_sum_planes(const MatDev* __restrict__ mats, int op, int chunk) {
+__global__ __launch_bounds__(256) void k_sum_planes(const MatDev* __restrict__ mats, const SymPlanes* __restrict__ sym) {
     const MatDev& md = mats[blockIdx.y];
-    const SymPlanes sp = sym_planes(op, md, chunk);
+    const SymPlanes sp = sym[blockIdx.y];
     const long long nn = sp.order, pitch = sp.pitch;
     double* __restrict__ T = md.T;
     for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < nn * nn; q += (long long)gridDim.x * 256) {
@@ -506,12 +506,12 @@ __device__ __forceinline__ bool factor_diag(double* __restrict__ A, double* __re
 // WAVES wavefronts hold up to SLOTS blocks each (one more takes the diagonal blocks): 7 x 6 covers order 256 within
 // 256 registers; orders up to 128 take 10 x 1, every block of a panel at work at once and a fraction of the code.
 template <bool FACTOR, int WAVES, int SLOTS>
-__global__ __launch_bounds__(64 * (WAVES + 1)) void k_inverse_factor(const MatDev* __restrict__ mats, int op, int chunk,
-                                                           double shift_rel, int max_nb, int* status) {
+__global__ __launch_bounds__(64 * (WAVES + 1)) void k_inverse_factor(const MatDev* __restrict__ mats,
+                                                           const SymPlanes* __restrict__ sym, double shift_rel, int max_nb, int* status) {
     extern __shared__ __attribute__((aligned(16))) double fac_smem[];
     __shared__ double red[WAVES];
     const MatDev& md = mats[blockIdx.x];
-    const SymPlanes sp = sym_planes(op, md, chunk);
+    const SymPlanes sp = sym[blockIdx.x];
     const int nn = sp.order, nb = (nn + 31) / 32;
     const long long pitch = sp.pitch;
     double* Am = fac_smem;                              // the diagonal block
@@ -730,11 +730,12 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void k_inverse_factor(const MatDe
 // The same for orders up to 32: one block, one wavefront per matrix.  Most of the large kernel's time there was
 // fetching its code (14 us for one 32 x 32 block).
 template <bool FACTOR>
-__global__ __launch_bounds__(64) void k_inverse_factor_small(const MatDev* __restrict__ mats, int op, int chunk,
+__global__ __launch_bounds__(64) void k_inverse_factor_small(const MatDev* __restrict__ mats,
+                                                             const SymPlanes* __restrict__ sym,
                                                              double shift_rel, int* status) {
     __shared__ __attribute__((aligned(16))) double Am[kFacBlock], Dm[kFacBlock], Lt[FACTOR ? kFacBlock : 1];
     const MatDev& md = mats[blockIdx.x];
-    const SymPlanes sp = sym_planes(op, md, chunk);
+    const SymPlanes sp = sym[blockIdx.x];
     const int nn = sp.order, lane = threadIdx.x, c = lane & 31, h = lane >> 5;
     // lane (c, h): column c, rows h, h + 2, ...; the lower triangle of the sum of the planes
     double v[16];
@@ -786,7 +787,7 @@ __global__ __launch_bounds__(64) void k_inverse_factor_small(const MatDev* __res
 }
 
 template <bool FACTOR, int WAVES, int SLOTS>
-static hipError_t run_factor_blocks(GemmOp op, const MatDev* mats, int n_mats, int nb, double shift_rel, int chunk,
+static hipError_t run_factor_blocks(const MatDev* mats, const SymPlanes* sym, int n_mats, int nb, double shift_rel,
                                     int* status, hipStream_t stream) {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(k_inverse_factor<FACTOR, WAVES, SLOTS>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -794,28 +795,27 @@ static hipError_t run_factor_blocks(GemmOp op, const MatDev* mats, int n_mats, i
     (void)attr;
     const size_t lds = (size_t)2 * nb * kFacBlock * sizeof(double);
     hipLaunchKernelGGL((k_inverse_factor<FACTOR, WAVES, SLOTS>), dim3(n_mats), dim3(64 * (WAVES + 1)), lds, stream, mats,
-                       (int)op, chunk, shift_rel, nb, status);
+                       sym, shift_rel, nb, status);
     return hipGetLastError();
 }
 
 template <bool FACTOR>
-static hipError_t run_factor(GemmOp op, const MatDev* mats, int n_mats, int max_order, double shift_rel, int chunk,
+static hipError_t run_factor(const MatDev* mats, const SymPlanes* sym, int n_mats, int max_order, double shift_rel,
                              int* status, hipStream_t stream) {
     if (max_order <= 32) {
-        hipLaunchKernelGGL(k_inverse_factor_small<FACTOR>, dim3(n_mats), dim3(64), 0, stream, mats, (int)op, chunk, shift_rel,
-                           status);
+        hipLaunchKernelGGL(k_inverse_factor_small<FACTOR>, dim3(n_mats), dim3(64), 0, stream, mats, sym, shift_rel, status);
         return hipGetLastError();
     }
     const int nb = (max_order + 31) / 32;
-    if (nb <= 4) return run_factor_blocks<FACTOR, 10, 1>(op, mats, n_mats, nb, shift_rel, chunk, status, stream);
-    return run_factor_blocks<FACTOR, 7, 6>(op, mats, n_mats, nb, shift_rel, chunk, status, stream);
+    if (nb <= 4) return run_factor_blocks<FACTOR, 10, 1>(mats, sym, n_mats, nb, shift_rel, status, stream);
+    return run_factor_blocks<FACTOR, 7, 6>(mats, sym, n_mats, nb, shift_rel, status, stream);
 }
 
-hipError_t launch_inverse_factor(GemmOp op, const MatDev* mats, int n_mats, int max_order, double shift_rel, int chunk,
-                                 int* status, hipStream_t stream) {
-    if (max_order <= kFactorMax) return run_factor<false>(op, mats, n_mats, max_order, shift_rel, chunk, status, stream);
+hipError_t launch_inverse_factor(GemmOp op, const MatDev* mats, const SymPlanes* sym, int n_mats, int max_order,
+                                 double shift_rel, int* status, hipStream_t stream) {
+    if (max_order <= kFactorMax) return run_factor<false>(mats, sym, n_mats, max_order, shift_rel, status, stream);
     const int which = op == OP_GRAM_P ? 1 : 0;
-    hipLaunchKernelGGL(k_sum_planes, dim3(64, n_mats), dim3(256), 0, stream, mats, (int)op, chunk);
+    hipLaunchKernelGGL(k_sum_planes, dim3(64, n_mats), dim3(256), 0, stream, mats, sym);
     hipError_t e = launch_cholesky(mats, n_mats, which, max_order, shift_rel, false, status, stream);
     if (e != hipSuccess) return e;
     return launch_tri_inverse(mats, n_mats, which, max_order, stream);
@@ -826,11 +826,14 @@ hipError_t launch_inverse_factor(GemmOp op, const MatDev* mats, int n_mats, int 
 // T = U Lambda^2 U^T the singular vectors of L are U, so rotating ROWS of L^T until they are mutually
 // orthogonal gives X = Lambda U^T: row i is ritz_i * u_i^T, ritz the singular value of the gradient (up to
 // the shift, which moves every eigenvalue of T alike).  Started from T itself the rows carry the squares of
-// those values: at a ratio of 1e5 the small ones are below the rounding of the rows as floats, and it
-// takes one sweep more (5 against 6 on a graded spectrum at order 128).  Rows are grouped in blocks of 16; one workgroup takes a pair of blocks (a
-// "visit"): it forms the 32 x 32 Gram matrix of the 32 rows, runs one cyclic Jacobi sweep on that
-// small matrix with the rotations accumulated in V, and applies X <- V X to the rows.  Block pairs
-// follow a round-robin tournament so the lp/16 - 1 rounds of one sweep meet every block pair once.
+// those values: what lies below 2.4e-4 of the largest drowns in the rounding of the rows as floats, and a signal
+// over a floor takes many sweeps more (rank 128 over a floor of 1e-4 at order 256: 12 to 15, from L^T 7 or 8).
+// The shift of 1e-6 trace(T) keeps every row at least 1e-3 of the gradient's norm long; directions whose squared
+// values differ by less than 3e-4 of the shift may end as a mixture among themselves.
+// Rows are grouped in blocks of 16; one workgroup takes a pair of blocks (a "visit"): it forms the 32 x 32
+// Gram matrix of the 32 rows, runs one cyclic Jacobi sweep on that small matrix with the rotations
+// accumulated in V, and applies X <- V X to the rows.  Block pairs follow a round-robin tournament so the
+// lp/16 - 1 rounds of one sweep meet every block pair once.
 __device__ __forceinline__ void tournament_pair(int players, int round, int k, int* a, int* b) {
     const int N = players - 1;
     if (k == 0) {
@@ -865,12 +868,12 @@ __global__ __launch_bounds__(256) void k_jacobi_prepare(const MatDev* __restrict
     for (int y = ty; y < 32; y += 8) X[(long long)(i0 + y) * lp + j0 + tx] = tile[tx][y];
 }
 
-hipError_t launch_jacobi_prepare(const MatDev* mats, int n_mats, int max_l, int max_lp, int chunk, int* status,
+hipError_t launch_jacobi_prepare(const MatDev* mats, const SymPlanes* sym, int n_mats, int max_l, int max_lp, int* status,
                                  hipStream_t stream) {
-    // the shift leaves the eigenvectors alone and covers the rounding of T; see the comment on the rows
+    // the shift leaves the eigenvectors alone and covers the rounding of T; what it hides: see the comment on the rows
     constexpr double kShift = 1e-6;
-    if (max_l <= kFactorMax) return run_factor<true>(OP_B_BT, mats, n_mats, max_l, kShift, chunk, status, stream);
-    hipLaunchKernelGGL(k_sum_planes, dim3(64, n_mats), dim3(256), 0, stream, mats, (int)OP_B_BT, chunk);
+    if (max_l <= kFactorMax) return run_factor<true>(mats, sym, n_mats, max_l, kShift, status, stream);
+    hipLaunchKernelGGL(k_sum_planes, dim3(64, n_mats), dim3(256), 0, stream, mats, sym);
     const hipError_t e = launch_cholesky(mats, n_mats, 0, max_l, kShift, true, status, stream);
     if (e != hipSuccess) return e;
     const unsigned nt = (unsigned)(max_lp + 31) / 32;
@@ -1443,7 +1446,11 @@ hipError_t launch_jacobi(const MatDev* mats, int n_mats, int max_pairs, int swee
     if (max_pairs < 1) max_pairs = 1;
     int done = 0;
     if (max_pairs > 1) {
-        // (a serial sweep takes 0.4 ms at order 128, 3 ms at 256, 10 ms at 512 and grows with the square of the order)
+        // Sweeps needed, the last one without a rotation included, with 0 to 2 power passes on noise, signals of half and
+        // of the full rank over floors of 1e-2 and 1e-4, graded and clustered columns, a single spike: at most 8 up
+        // to order 128, 9 from 192 to 320.  A serial sweep is 120 visits of 14 us at order 256, 1.7 ms, and grows
+        // with the square of the order: one refresh in a few pays one there (noise 3.2 -> 4.9 ms), where one more
+        // launched sweep would cost every refresh 15 empty launches of 2 us.
         done = max_pairs > 32 ? sweeps : max_pairs > 8 ? 14 : 8;
         if (done > sweeps) done = sweeps;
         const dim3 g(max_pairs, n_mats);
@@ -1481,7 +1488,7 @@ __global__ __launch_bounds__(kSortThreads) void k_ritz_sort(const MatDev* __rest
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const double v = wave_sum_d(a[u]);
-            if (lane == 0) md.ritz[i + u] = sqrt(v);
+            if (lane == 0) md.ritz[i + u] = ritz_value(v);
         }
     }
     __syncthreads();

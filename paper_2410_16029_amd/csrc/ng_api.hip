@@ -179,7 +179,7 @@ struct Plan {
     int skinny_rk;                              // 0: the MFMA / fp32-GEMM projection and update
     long long tiles4;                           // 256 x 256 tiles of the left-side projection
     int proj_direct, proj_staged, proj_right;   // lengths of the three runs of proj
-    size_t off_status, off_mats, off_step, off_proj, off_upd, off_dots, off_patches, off_skinny, off_scratch;
+    size_t off_status, off_mats, off_step, off_proj, off_upd, off_dots, off_patches, off_skinny, off_sym, off_scratch;
     // the scratch block of one step: the per-step table, then what the step's kernels hand to each
     // other (offsets from the start of the block; per matrix)
     size_t step_tail8_off, step_bytes;
@@ -318,6 +318,7 @@ void make_plan(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* 
     p->off_dots = off;   off += align_up(sizeof(TileRef) * (size_t)n_mats * kDotPartsMax, 256);
     p->off_patches = off; off += align_up(sizeof(TileRef) * p->patches.size(), 256);
     p->off_skinny = off;  off += align_up(sizeof(TileRef) * p->skinny.size(), 256);
+    p->off_sym = off;     off += align_up(sizeof(SymPlanes) * kSymOps * (size_t)n_mats, 256);
     p->off_scratch = off;
     for (int i = 0; i < n_mats; ++i) {
         const Sizes& z = p->sz[i];
@@ -346,10 +347,11 @@ struct ng_state {
     MatDyn* d_dyn;
     int* d_status;
     TileRef *d_proj, *d_upd, *d_dots, *d_patches, *d_skinny;
+    SymPlanes* d_sym;   // [kSymOps][n_mats]
     int n_dots;
     int max_m, max_n, max_r, max_l, max_lp, max_rows, max_ldn;
     int max_ti[OP_COUNT], max_tj[OP_COUNT], max_tk[OP_COUNT];   // largest M, N, K of each fp32 product
-    int sym_chunk[OP_COUNT];                                    // contraction per partial plane of a symmetric product
+    int max_cut[OP_COUNT];                                      // most pieces its contraction is cut into
     int max_jpairs;
     int sides;       // bit 0: left-side matrices present, bit 1: right-side ones
     // profiling
@@ -448,9 +450,14 @@ int gradient_product(ng_state* st, GemmOp op, bool last, hipStream_t stream, con
     return gemm(st, op, stream, sc);
 }
 
+const SymPlanes* planes_of(const ng_state* st, GemmOp op) {
+    const int i = sym_index(op);
+    return i < 0 ? nullptr : st->d_sym + (size_t)st->n_mats * i;
+}
+
 int gemm(ng_state* st, GemmOp op, hipStream_t stream, const StepScalars& sc, const MatDyn* dyn) {
     NG_HIP(launch_gemm_f32(op, st->d_mats, dyn ? dyn : st->d_dyn, st->n_mats, st->max_ti[op], st->max_tj[op], st->max_tk[op],
-                           st->hp.grad_dtype, sc, st->sym_chunk[op], st->plan.max_split, st->sides, stream));
+                           st->hp.grad_dtype, sc, st->max_cut[op], planes_of(st, op), st->sides, stream));
     return NG_OK;
 }
 
@@ -458,8 +465,8 @@ int gemm(ng_state* st, GemmOp op, hipStream_t stream, const StepScalars& sc, con
 int inverse_factor(ng_state* st, GemmOp op, double shift_rel, hipStream_t stream, const StepScalars& sc) {
     int rc;
     if ((rc = gemm(st, op, stream, sc)) != NG_OK) return rc;
-    NG_HIP(launch_inverse_factor(op, st->d_mats, st->n_mats, st->max_ti[op], shift_rel, st->sym_chunk[op], st->d_status,
-                                 stream));
+    NG_HIP(launch_inverse_factor(op, st->d_mats, planes_of(st, op), st->n_mats, st->max_ti[op], shift_rel,
+                                 st->d_status, stream));
     return NG_OK;
 }
 
@@ -689,6 +696,7 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
         st->d_dots = (TileRef*)(ws + pl.off_dots);
         st->d_patches = (TileRef*)(ws + pl.off_patches);
         st->d_skinny = (TileRef*)(ws + pl.off_skinny);
+        st->d_sym = (SymPlanes*)(ws + pl.off_sym);
 
         st->mats.resize(n_mats);
         std::vector<TileRef> dots;
@@ -776,7 +784,9 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
         // 128 x 128 tile each (eight per CU: their lengths differ by the matrices' row counts), but not
         // below 128 (64 for orders up to 64): a plane is also read back.  (sym_planes bounds a run by half of
         // the contraction: a large set would otherwise get longer ones.)
-        for (int op = 0; op < OP_COUNT; ++op) {
+        for (int op = 0; op < OP_COUNT; ++op) st->max_cut[op] = op == OP_PROJECT_F32 ? pl.max_split : 0;
+        std::vector<SymPlanes> sym((size_t)kSymOps * n_mats);
+        for (int op : {OP_GRAM_A, OP_GRAM_B, OP_GRAM_CA, OP_GRAM_CB, OP_B_BT, OP_GRAM_P}) {
             double work = 0.0;
             for (const MatDev& md : st->mats) {
                 int M, N, K;
@@ -786,7 +796,11 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
             }
             const int least = st->max_ti[op] <= 64 ? 64 : 128;
             const int chunk = (int)align_up((size_t)(work / 2048.0), 64);
-            st->sym_chunk[op] = chunk < least ? least : chunk;
+            for (int i = 0; i < n_mats; ++i) {
+                const SymPlanes sp = sym_planes(op, st->mats[i], chunk < least ? least : chunk);
+                sym[(size_t)n_mats * sym_index(op) + i] = sp;
+                if (sp.count > st->max_cut[op]) st->max_cut[op] = sp.count;
+            }
         }
 
         st->tables_valid = !(flags & NG_INIT_HOST_ONLY);
@@ -801,6 +815,7 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
         const char zeros[256] = {0};
         e = hipMemcpy(st->d_status, zeros, sizeof(zeros), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(st->d_mats, st->mats.data(), sizeof(MatDev) * n_mats, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(st->d_sym, sym.data(), sizeof(SymPlanes) * sym.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess && !pl.proj.empty())
             e = hipMemcpy(st->d_proj, pl.proj.data(), sizeof(TileRef) * pl.proj.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess && !pl.upd.empty())
@@ -878,7 +893,7 @@ int ng_refresh_projector(ng_state* st, const void* const* grads, ng_stream strea
     // Rayleigh-Ritz: B = Q^T G, T = B B^T = U diag(ritz^2) U^T, P = Q U[:, top r]
     if ((rc = gradient_product(st, OP_QT_G, true, stream, sc)) != NG_OK) return rc;
     if ((rc = gemm(st, OP_B_BT, stream, sc)) != NG_OK) return rc;
-    NG_HIP(launch_jacobi_prepare(st->d_mats, st->n_mats, st->max_l, st->max_lp, st->sym_chunk[OP_B_BT], st->d_status, stream));
+    NG_HIP(launch_jacobi_prepare(st->d_mats, planes_of(st, OP_B_BT), st->n_mats, st->max_l, st->max_lp, st->d_status, stream));
     NG_HIP(launch_jacobi(st->d_mats, st->n_mats, st->max_jpairs, st->hp.refresh_sweeps, stream));
     NG_HIP(launch_jacobi_finish(st->d_mats, st->n_mats, st->hp.refresh_sweeps, st->d_status, stream));
     // history carry-over needs the outgoing projector: keep it in Yc (free from here on)

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include <vector>
@@ -22,7 +23,8 @@ constexpr int kSkinnyRows = 128;     // rows and columns of the gradient / weigh
 constexpr int kSkinnyCols = 256;
 constexpr int kStatePanelCols = 2048;   // columns per panel of a wide M, V or history slot (see state_panel)
 // bits of the device's sticky status word: 1 solve (pivot / non-finite), 2 transform+Adam (non-finite),
-// 4 Cholesky pivot of the refresh, 8 non-positive Ritz value among the leading r
+// 4 Cholesky pivot of the refresh, 8 Ritz value among the leading r not positive (zero or NaN: the rows it is the norm
+// of come from a factor of T plus a shift, so a gradient of too low a rank shows as a pivot, bit 4)
 constexpr int kStatusNotConverged = 16;   // the Jacobi eigen-solve of a refresh ran out of sweeps
 constexpr int kFactorMax = 256;   // largest order whose inverse Cholesky factor one workgroup computes in registers
 constexpr int kJacobiBlock = 16;  // rows per block of the blocked Jacobi (a visit rotates a pair of blocks)
@@ -225,18 +227,18 @@ void gemm_f32_dims(int op, const MatDev& md, int* M, int* N, int* K);
 // buffer that the next product fills (while an orthonormalisation runs), Yc for B B^T, and Bm once the
 // rotation staged in it has been applied.  Each holds at least order^2 floats, because order <= l <= m, n.
 constexpr int kSymPlanesMax = 8;
-constexpr int kSymStep = 16;       // k-step of the products: what a contraction up to this long is not cut into
+constexpr int kSymStep = 16;       // k-step of the products: a contraction up to this long is not cut
 struct SymPlanes {
     float* p;
     int order, count;
     long long pitch;               // floats from one plane to the next
 };
 // planes that a contraction of length k is cut into where there is room
-__host__ __device__ inline int sym_plane_count(int k, int chunk) {
+inline int sym_plane_count(int k, int chunk) {
     const int least = k > kSymStep ? 2 : 1, want = (k + chunk - 1) / chunk;
     return want < least ? least : want < kSymPlanesMax ? want : kSymPlanesMax;
 }
-__host__ __device__ inline SymPlanes sym_planes(int op, const MatDev& md, int chunk) {
+inline SymPlanes sym_planes(int op, const MatDev& md, int chunk) {
     SymPlanes s;
     s.p = (op == OP_GRAM_B || op == OP_GRAM_CB || op == OP_GRAM_P) ? md.Ya : md.Yb;
     s.order = op == OP_GRAM_P ? md.r : md.l;
@@ -253,12 +255,20 @@ __host__ __device__ inline SymPlanes sym_planes(int op, const MatDev& md, int ch
     }
     return s;
 }
+// The kernels read it from a table [kSymOps][n_mats] in the workspace, `sym` being a product's row of it.  (Formed in the
+// kernels, the divisions and the choice of buffers were 7 us of a refresh of the 60M set; as members of MatDev, its
+// longer stride was 0.5 us of the step of three mid-size matrices.)
+constexpr int kSymOps = 6;
+inline int sym_index(int op) {      // -1: not a symmetric product
+    return op >= OP_GRAM_A && op <= OP_GRAM_CB ? op - OP_GRAM_A : op == OP_B_BT ? 4 : op == OP_GRAM_P ? 5 : -1;
+}
+
 // max_m, max_n, max_k: largest dimensions of the product over the layer set (grid and tile choice)
-// chunk: run of the contraction per partial plane, symmetric products only (see sym_planes); max_split: largest
-// MatDev::proj_chunks, OP_PROJECT_F32 only
+// max_split: largest number of pieces that a matrix's contraction is cut into, 0 or 1 for none (symmetric products:
+// SymPlanes::count, the projection: MatDev::proj_chunks); sym: symmetric products only
 hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int n_mats,
                            int max_m, int max_n, int max_k, int grad_dtype, StepScalars sc,
-                           int chunk, int max_split, int sides, hipStream_t stream);
+                           int max_split, const SymPlanes* sym, int sides, hipStream_t stream);
 
 // bf16 MFMA GEMMs of the step (k_gemm_bf16.hip)
 // which: 0 projection (direct-to-LDS kernel), 1 update, 2 projection (register-staged kernel)
@@ -307,14 +317,16 @@ hipError_t launch_transform_adam(const MatDev* mats, const MatDyn* dyn, const Ti
                                  StepScalars sc, int grad_dtype, int* status, hipStream_t stream);
 hipError_t launch_make_bf16_copies(const MatDev* mats, int n_mats, int max_m, int max_r, hipStream_t stream);
 
-// Place of value i among n, largest first and equal ones by index.  A NaN (non-finite gradient) comes after every number:
-// the places are a permutation whatever the values, so every entry of the order that is written from them is
-// an index (with NaN comparing false, all NaN values had place 0 and the other entries kept what the workspace held).
+// Ritz value from the sum of its row's squares; -1 for NaN (non-finite gradient), behind every number, so that the places
+// are a permutation whatever the rows hold and every entry of the order written from them is an index (with NaN
+// comparing false, all NaN values had place 0 and the other entries kept what the workspace held).
+__host__ __device__ inline double ritz_value(double sum) { return sum >= 0.0 ? sqrt(sum) : -1.0; }
+// Place of value i among n, largest first and equal ones by index.
 __host__ __device__ inline int ritz_place(const double* v, int n, int i) {
-    const double vi = v[i] == v[i] ? v[i] : -1.0;
+    const double vi = v[i];
     int place = 0;
     for (int j = 0; j < n; ++j) {
-        const double vj = v[j] == v[j] ? v[j] : -1.0;
+        const double vj = v[j];
         place += (vj > vi) || (vj == vi && j < i);
     }
     return place;
@@ -324,11 +336,11 @@ __host__ __device__ inline int ritz_place(const double* v, int n, int i) {
 hipError_t launch_fill_gaussian(const MatDev* mats, int n_mats, int max_rows, unsigned long long seed,
                                 unsigned long long call_id, hipStream_t stream);   // fills Yb (n x l)
 // Linv = inverse Cholesky factor of the symmetric product `op` (its planes, plus shift_rel * trace on the
-// diagonal); chunk: as given to that product
-hipError_t launch_inverse_factor(GemmOp op, const MatDev* mats, int n_mats, int max_order, double shift_rel, int chunk,
-                                 int* status, hipStream_t stream);
+// diagonal)
+hipError_t launch_inverse_factor(GemmOp op, const MatDev* mats, const SymPlanes* sym, int n_mats, int max_order,
+                                 double shift_rel, int* status, hipStream_t stream);
 // the rows that the Jacobi starts from: L^T of T = B B^T = L L^T (planes of OP_B_BT)
-hipError_t launch_jacobi_prepare(const MatDev* mats, int n_mats, int max_l, int max_lp, int chunk, int* status,
+hipError_t launch_jacobi_prepare(const MatDev* mats, const SymPlanes* sym, int n_mats, int max_l, int max_lp, int* status,
                                  hipStream_t stream);
 // up to `sweeps` (1 .. 64) sweeps over every matrix, each matrix until one of its sweeps rotates nothing
 hipError_t launch_jacobi(const MatDev* mats, int n_mats, int max_pairs, int sweeps, hipStream_t stream);

@@ -100,7 +100,12 @@ def refresh_invariants(P, G, r, k_signal=None, energy_tol=2e-3, orth_tol=5e-6, a
     tie = max(1e-6, 4.0 * orth_tol)
     assert np.all(P.max(axis=0) >= np.abs(P).max(axis=0) * (1.0 - tie)), (label, "sign rule")
     ritz = np.sum(B_ ** 2, axis=1)
-    assert np.all(ritz[:-1] >= ritz[1:] * (1.0 - 1e-3)), (label, "Ritz order")
+    # (T = B B^T is summed in fp32: its eigenvalues, which the columns are ordered by, are off by about 2^-24 sqrt(n)
+    # of the largest, so the order of two values within twice that is a matter of rounding.  130 x 136 at rank 129, 16
+    # signals over 1 % noise, 61 sets: the last values lie at 3e-7 of the largest, and one or two sets have a pair in
+    # the other order, by up to 1.1e-6, with the sums cut in any of three ways; the slack is 1.4e-6 there.)
+    slack = 2.0 * 2.0 ** -24 * np.sqrt(G.shape[1]) * ritz[0]
+    assert np.all(ritz[:-1] >= ritz[1:] * (1.0 - 1e-3) - slack), (label, "Ritz order")
     return out
 
 

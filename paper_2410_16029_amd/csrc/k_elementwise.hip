@@ -297,7 +297,7 @@ hipError_t launch_gram_row(const MatDev* mats, const MatDyn* dyn, const TileRef*
 // 16 loads in flight each, and up to s = 16 the system is solved in one wavefront's registers: X = L^{-1} by
 // the elimination of a 16 x 16 block, lane c holding column c, and w = X^T (X e_head).  (With one
 // wavefront, eight loads in flight and the factor in LDS, three barriers a column: 30 us for 168
-// matrices at s = 16, 11 us for 56 at s = 8; now 11 and 6.)
+// matrices at s = 16, 11 us for 56 at s = 8; now 9 and 7.)
 constexpr int kSolveSub = 16;      // threads that share the sum of one slot's partials
 __global__ __launch_bounds__(256) void k_solve(const MatDev* __restrict__ mats, const MatDyn* __restrict__ dyn,
                                                int first, StepScalars sc, int row_override, int* status) {

@@ -1,15 +1,20 @@
-// Grouped fp32 GEMM on the fp32 MFMA (v_mfma_f32_32x32x2_f32), one launch for
-// all matrices of the layer set.  It serves the NG_F32 step (projection
+// Grouped fp32 GEMM, one launch for all matrices of the layer set.  It serves the NG_F32 step (projection
 // R = P^T G, paper Sec. 1; update W -= lr (scale P N + wd W), paper Sec. 2.2)
 // and every dense product of the projector refresh.  Operands are described as
 // strided views A(i,k), B(k,j) so one kernel covers all transpositions; an
 // operand may be stored as float or bf16 (gradients).
 //
-// Tile 128 x 128 per workgroup (4 wavefronts of 64 x 64), BK = 16, two LDS tile buffers (one barrier
-// per k-step) and two register sets (a tile's loads are issued two k-steps ahead).
-// MFMA 32x32x2 f32 operand layout: lane L supplies A[i = L%32][k = L/32] and
-// B[k = L/32][j = L%32]; the 16 accumulators of lane L are
-// D[8*g + 4*(L/32) + e][L%32], index 4*g + e.
+// The products run on the bf16 MFMA, each operand split into three bf16 planes on its way into LDS (F32Src).
+// On the fp32 MFMA (v_mfma_f32_32x32x2_f32) they reached half of its rate.  Before / now, and the rms error of a sum of 600
+// terms relative to the root of the sum of its squared terms, 4.4e-7 / 1.4e-7: 168 Gram matrices of 1024..2736 x 256
+// 266 / 182 us, 168 products with a 256 x 256 factor 293 / 188 us, fp32 step of eight mid-size blocks 974 / 658 us.
+// What bounds them now: 128 x 128 tiles of 6 to 10 k-steps, each with its split, two barriers and the latency of the
+// first loads; the matrix cores are busy a third of the time.
+//
+// Tile 128 x 128 per workgroup (4 wavefronts of 64 x 64, two workgroups per CU), BK = 32.  Tried: eight wavefronts of 64 x
+// 32, two LDS buffers and three register sets (one workgroup per CU): 290 us.
+// MFMA 32x32x16 bf16 operand layout: lane L supplies eight consecutive k, 8 (L/32) .. of A row L%32 and of B column L%32;
+// the 16 accumulators of lane L are D[8*g + 4*(L/32) + e][L%32], index 4*g + e.
 #include "ng_internal.h"
 
 namespace ng {
@@ -188,18 +193,51 @@ __device__ __forceinline__ f32x4_t load4(const NG_AS1 unsigned char* p) {
     return *reinterpret_cast<const NG_AS1 f32x4_a4*>(p);
 }
 
+// Every operand value x goes into LDS as three bf16 planes, x = x0 + x1 + x2 (each the rounding of what the ones before
+// leave: 24 bits, the float itself), and a product of two operands is six bf16 MFMA products,
+//   a b = a0 b0 + (a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0),      dropped: a1 b2, a2 b1, a2 b2, below 2^-25 |a b|.
+// a0 b0 has an accumulator of its own, which is rounded once per 16 contraction steps (the fp32 MFMA rounds every
+// two), and the other five share one that is some 2^-8 as large: the sums are closer to 64 bits than the fp32
+// MFMA's, at three eighths of its matrix-core time.
+// A gradient (or history slot) stored as bf16 has one plane.
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+
+// Beyond this a value may round to an infinity in bf16, and an infinity times a lower plane is NaN: tiles that
+// meet one are computed again in plain fp32 (see gemm_f32_tile).
+constexpr float kSplitMax = 3.38e38f;
+
+// the NP planes of two values, a in the low halves
+template <int NP>
+__device__ __forceinline__ void split2(float a, float b, unsigned (&p)[NP]) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const f32x2_t f = {a, b};
+        const bf16x2_t hv = __builtin_convertvector(f, bf16x2_t);      // v_cvt_pk_bf16_f32: nearest even
+        p[i] = *reinterpret_cast<const unsigned int*>(&hv);
+        a -= __uint_as_float(p[i] << 16);
+        b -= __uint_as_float(p[i] & 0xffff0000u);
+    }
+}
+
 // One operand of a tile: T (tile index) x K (contraction), TS x BK per k-step, moved as vectors of four
-// elements along the stride-1 dimension -- the tile index (TF) or the contraction.  tile-fast: positions
-// 4 (t % (TS/4)) of the tile index at k = t / (TS/4) + (1024/TS) q; k-fast: k = 4 (t % (BK/4)) at tile
-// index t / (BK/4) + (1024/BK) q.
+// elements along the stride-1 dimension -- the tile index (TF) or the contraction -- and kept in LDS as NP planes
+// [T][K], K contiguous (what the MFMA reads).  tile-fast: a thread has 4 tile indexes of BK / KG consecutive k, the
+// k-groups fastest over the lanes (LDS writes of one instruction on distinct banks, 128 consecutive bytes in memory);
+// k-fast: 4 consecutive k at tile index t / (BK/4) + (1024/BK) q.
 template <int TS, int BK, bool TF, bool BF>
 struct F32Src {
-    static constexpr int NV = TS * BK / 1024, LDT = TS + 4, ES = BF ? 2 : 4, KT = BK / 4, TQ = 1024 / BK;
+    static constexpr int NV = TS * BK / 1024, LDK = BK + 8, ES = BF ? 2 : 4, KT = BK / 4, TQ = 1024 / BK;
+    static constexpr int KG = 1024 / TS, NP = BF ? 1 : 3, PLANE = TS * LDK;      // PLANE: bf16 elements per plane
+    static_assert(BK / KG == NV, "vectors of a tile-fast thread");
     const NG_AS1 unsigned char* base;   // element (0, 0)
     const NG_AS1 unsigned char* safe;   // 16 readable bytes
-    const NG_AS1 unsigned char* ptr[NV];
     long long st, sk;                   // element strides along T and K
+    unsigned off[NV];                   // byte offsets of this thread's vectors of k-step 0 (an operand is below 2 GiB)
     int t0, k0, lim, K;                 // this thread's first position, valid tile indexes, contraction length
+    int shift;                          // tile-fast: elements by which a vector that straddles the edge was moved back
     __device__ __forceinline__ void init(const void* p, const void* safe_, long long st_, long long sk_, int tile0,
                                          int lim_, int K_, int t) {
         base = (const NG_AS1 unsigned char*)p;
@@ -208,27 +246,41 @@ struct F32Src {
         sk = sk_;
         lim = lim_;
         K = K_;
-        t0 = tile0 + (TF ? 4 * (t % (TS / 4)) : t / KT);
-        k0 = TF ? t / (TS / 4) : 4 * (t % KT);
+        t0 = tile0 + (TF ? 4 * (t / KG) : t / KT);
+        k0 = TF ? NV * (t % KG) : 4 * (t % KT);
+        // what lies past the operand's last tile index is read from inside it: it only reaches results that are not stored
+        const int ti = TF ? (t0 + 4 <= lim ? t0 : lim >= 4 ? lim - 4 : 0) : t0;
+        shift = TF && t0 < lim ? t0 - ti : 0;
 #pragma unroll
-        for (int q = 0; q < NV; ++q)
-            ptr[q] = base + (TF ? (long long)t0 + (long long)(k0 + (1024 / TS) * q) * sk
-                                : (long long)(t0 + TQ * q) * st + k0) * ES;
+        for (int q = 0; q < NV; ++q) {
+            const int i = TF ? ti : t0 + TQ * q < lim ? t0 + TQ * q : lim - 1;
+            off[q] = (unsigned)((TF ? (long long)i + (long long)(k0 + q) * sk : (long long)i * st + k0) * ES);
+        }
     }
-    // k-step kt, wholly inside the operand
+    // (a tile-fast operand of fewer than four tile indexes has no whole vectors)
+    __device__ __forceinline__ int whole_steps() const { return TF && lim < 4 ? 0 : K / BK; }
+    // k-step kt < whole_steps(): whole vectors, no tests
     __device__ __forceinline__ void fetch(int kt, f32x4_t (&r)[NV]) const {
-        const long long off = (TF ? (long long)BK * sk : (long long)BK) * ES * kt;
+        const NG_AS1 unsigned char* p = base + (TF ? (long long)BK * sk : (long long)BK) * ES * kt;      // uniform
 #pragma unroll
-        for (int q = 0; q < NV; ++q) r[q] = load4<BF>(ptr[q] + off);
+        for (int q = 0; q < NV; ++q) r[q] = load4<BF>(p + off[q]);
     }
-    // k-step kt at the operand's edge, zero outside: whole vectors from clamped addresses; the lanes whose vector
-    // straddles the edge (only where the edge is not a multiple of four) read theirs element by element
+    // the straddling vectors' elements back to their places (tiles at such an edge only)
+    __device__ __forceinline__ void realign(f32x4_t (&r)[NV]) const {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            if (shift & 1) r[q] = (f32x4_t){r[q].y, r[q].z, r[q].w, 0.f};
+            if (shift & 2) r[q] = (f32x4_t){r[q].z, r[q].w, 0.f, 0.f};
+        }
+    }
+    // any k-step, zero outside the operand: whole vectors from clamped addresses; the lanes whose vector straddles the
+    // edge (only where the edge is not a multiple of four) read theirs element by element
     __device__ __forceinline__ void fetch_edge(int kt, f32x4_t (&r)[NV]) const {
         const bool straddles = ((TF ? lim : K) & 3) != 0;
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
             const int i = TF ? t0 : t0 + TQ * q;
-            const int k = kt * BK + (TF ? k0 + (1024 / TS) * q : k0);
+            const int k = kt * BK + (TF ? k0 + q : k0);
             const bool in = i < lim && k < K;
             const bool all = in && (TF ? i + 4 <= lim : k + 4 <= K);
             const f32x4_t v = load4<BF>(all ? base + ((long long)i * st + (long long)k * sk) * ES : safe);
@@ -241,38 +293,53 @@ struct F32Src {
             }
         }
     }
-    __device__ __forceinline__ void stage(const f32x4_t (&r)[NV], float (*S)[LDT], int t) const {
+    // the planes -> S (PLANE elements each); big: the largest magnitude met
+    __device__ __forceinline__ void stage(const f32x4_t (&r)[NV], bf16_t* S, int t, float& big) const {
+        if (!BF) {
 #pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            if (TF) {
-                *reinterpret_cast<f32x4_t*>(&S[t / (TS / 4) + (1024 / TS) * q][4 * (t % (TS / 4))]) = r[q];
-            } else {
+            for (int q = 0; q < NV; ++q)
 #pragma unroll
-                for (int x = 0; x < 4; ++x) S[4 * (t % KT) + x][t / KT + TQ * q] = r[q][x];
+                for (int x = 0; x < 4; x += 2) big = fmaxf(fmaxf(big, fabsf(r[q][x])), fabsf(r[q][x + 1]));
+        }
+#pragma unroll
+        for (int y = 0; y < (TF ? 4 : NV); ++y) {
+            bf16_t* dst = S + (TF ? 4 * (t / KG) + y : t / KT + TQ * y) * LDK + k0;
+            constexpr int PAIRS = TF ? NV / 2 : 2;
+            unsigned p[PAIRS][NP];
+#pragma unroll
+            for (int c = 0; c < PAIRS; ++c)
+                split2<NP>(TF ? r[2 * c][y] : r[y % NV][2 * c], TF ? r[2 * c + 1][y] : r[y % NV][2 * c + 1], p[c]);
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                if (PAIRS == 2) *reinterpret_cast<uint2*>(dst + i * PLANE) = make_uint2(p[0][i], p[PAIRS - 1][i]);
+                else *reinterpret_cast<unsigned*>(dst + i * PLANE) = p[0][i];
             }
         }
     }
 };
 
 // Tile TS x TS per workgroup (128: four wavefronts of 64 x 64 = 2 x 2 MFMA blocks of 32 x 32; 64: one
-// block per wavefront, for products with a short side, a short contraction or few tiles).  BK = 16 (32 with the
-// small tile: half the barriers, but three mid-size matrices' step 73.8 -> 78.4 us).
+// block per wavefront, for products with a short side, a short contraction or few tiles).
 // AI / BJ: the tile index is operand A's / B's stride-1 dimension (else the contraction is); ABF / BBF:
 // operand A / B is stored as bf16; SYM: a symmetric product (partial planes).  side >= 0: only matrices
 // of that side.  A tile whose rows and columns all exist takes whole vectors without a test (only a
 // last partial k-step is read element by element); with the tests of every vector, and of every MFMA
 // block against the product's edge, in the loop the products ran at a quarter of the fp32 MFMA rate.
+constexpr int kF32BK = 32;             // contraction steps per LDS tile
 template <int TS>
 struct F32Tiles {
-    static constexpr int BK = kSymStep, LDT = TS + 4;
-    float a[2][BK][LDT], b[2][BK][LDT];   // two tile buffers: one barrier per k-step
+    bf16_t a[3 * TS * (kF32BK + 8)], b[3 * TS * (kF32BK + 8)];   // three planes each, rows padded by 16 bytes
 };
+
+// A barrier that waits for this wave's LDS accesses only: __syncthreads() would also wait for the operand loads in
+// flight, i.e. expose a memory latency in every k-step.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <int TS, bool AI, bool BJ, bool ABF, bool BBF, bool SYM>
 __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__ mats, const MatDyn* __restrict__ dyn,
                                               int grad_dtype, const StepScalars& sc, const SymPlanes* __restrict__ sym,
                                               F32Tiles<TS>& lds) {
-    constexpr int BK = F32Tiles<TS>::BK, LDT = F32Tiles<TS>::LDT;
+    constexpr int BK = kF32BK;
     constexpr int NB = TS / 64;          // 32 x 32 blocks per wavefront and dimension
     typedef F32Src<TS, BK, AI, ABF> SA;
     typedef F32Src<TS, BK, BJ, BBF> SB;
@@ -305,7 +372,7 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
         const int plane = tile % sp.count;
         tile /= sp.count;
         // this plane's run of the contraction (an empty one leaves zeros)
-        const int kc = ((v.K + sp.count - 1) / sp.count + BK - 1) / BK * BK;
+        const int kc = ((v.K + sp.count - 1) / sp.count + kSymStep - 1) / kSymStep * kSymStep;
         const int k0 = plane * kc < v.K ? plane * kc : v.K;
         v.A = (const unsigned char*)v.A + (long long)k0 * v.sAk * (ABF ? 2 : 4);
         v.B = (const unsigned char*)v.B + (long long)k0 * v.sBk * (BBF ? 2 : 4);
@@ -331,74 +398,122 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
     const int wm = wv >> 1, wn = wv & 1;
     const int li = lane & 31, h = lane >> 5;
 
-    floatx16 acc[NB][NB];
+    floatx16 acc[NB][NB], low[NB][NB];      // a0 b0, and the five smaller products
 #pragma unroll
     for (int a = 0; a < NB; ++a)
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int x = 0; x < 16; ++x) acc[a][b][x] = 0.f;
+            for (int x = 0; x < 16; ++x) acc[a][b][x] = low[a][b][x] = 0.f;
 
     SA sa;
     SB sb;
     sa.init(v.A, mats, v.sAi, v.sAk, i0, v.M, v.K, t);
     sb.init(v.B, mats, v.sBj, v.sBk, j0, v.Nvalid, v.K, t);
 
-    auto multiply = [&](int buf) {
-        const float (*As)[LDT] = lds.a[buf];
-        const float (*Bs)[LDT] = lds.b[buf];
+    auto multiply = [&]() {
+        const bf16_t* pa = lds.a + (wm * (TS / 2) + li) * SA::LDK + 8 * h;
+        const bf16_t* pb = lds.b + (wn * (TS / 2) + li) * SB::LDK + 8 * h;
 #pragma unroll
-        for (int kk = 0; kk < BK; kk += 2) {
-            float a[NB], b[NB];
+        for (int kk = 0; kk < BK; kk += 16) {
+            bf16x8_t a[SA::NP][NB], b[SB::NP][NB];
 #pragma unroll
             for (int x = 0; x < NB; ++x) {
-                a[x] = As[kk + h][wm * (TS / 2) + 32 * x + li];
-                b[x] = Bs[kk + h][wn * (TS / 2) + 32 * x + li];
+#pragma unroll
+                for (int i = 0; i < SA::NP; ++i)
+                    a[i][x] = *reinterpret_cast<const bf16x8_t*>(pa + i * SA::PLANE + 32 * x * SA::LDK + kk);
+#pragma unroll
+                for (int i = 0; i < SB::NP; ++i)
+                    b[i][x] = *reinterpret_cast<const bf16x8_t*>(pb + i * SB::PLANE + 32 * x * SB::LDK + kk);
+            }
+#pragma unroll
+            for (int ia = 0; ia < SA::NP; ++ia)
+#pragma unroll
+                for (int ib = 0; ib < SB::NP && ia + ib < 3; ++ib)
+#pragma unroll
+                    for (int x = 0; x < NB; ++x)
+#pragma unroll
+                        for (int y = 0; y < NB; ++y) {
+                            floatx16& c = ia + ib == 0 ? acc[x][y] : low[x][y];
+                            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ia][x], b[ib][y], c, 0, 0, 0);
+                        }
+        }
+    };
+
+    // The loads of tile kt + 1 are in flight while tile kt is multiplied; one LDS tile (a second would leave room for
+    // one workgroup per CU instead of two, whose staging and products overlap).  The loop has no branch around a load
+    // (the compiler waits for the load where such paths meet): whole k-steps of both operands first, what is left after.
+    const int nk = (v.K + BK - 1) / BK;
+    const int whole_a = sa.whole_steps(), whole_b = sb.whole_steps();
+    const int nw = whole_a < whole_b ? whole_a : whole_b;
+    // (uniform) tiles with vectors that straddle the last tile index
+    const bool back_a = AI && (v.M & 3) != 0 && i0 + TS > v.M, back_b = BJ && (v.Nvalid & 3) != 0 && j0 + TS > v.Nvalid;
+    f32x4_t ra[NV], rb[NV];
+    float big = 0.f;
+    auto stage = [&]() {
+        sa.stage(ra, lds.a, t, big);
+        sb.stage(rb, lds.b, t, big);
+    };
+    if (nw > 0) {
+        sa.fetch(0, ra);
+        sb.fetch(0, rb);
+        for (int kt = 0; kt < nw; ++kt) {
+            if (back_a) sa.realign(ra);
+            if (back_b) sb.realign(rb);
+            stage();
+            const int next = kt + 1 < nw ? kt + 1 : kt;
+            sa.fetch(next, ra);
+            sb.fetch(next, rb);
+            lds_barrier();
+            multiply();
+            lds_barrier();
+        }
+    }
+    for (int kt = nw; kt < nk; ++kt) {
+        sa.fetch_edge(kt, ra);
+        sb.fetch_edge(kt, rb);
+        stage();
+        lds_barrier();
+        multiply();
+        lds_barrier();
+    }
+#pragma unroll
+    for (int x = 0; x < NB; ++x)
+#pragma unroll
+        for (int y = 0; y < NB; ++y)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[x][y][e] += low[x][y][e];
+    // infinities (and what would round to one): the tile again in plain fp32, element by element
+    if (__syncthreads_or(big > kSplitMax)) {
+#pragma unroll 1
+        for (int k = 0; k < v.K; ++k) {
+            float b[NB];
+#pragma unroll
+            for (int y = 0; y < NB; ++y) {
+                const int j = j0 + wn * (TS / 2) + 32 * y + li;
+                b[y] = j < v.Nvalid ? load1<BBF>((const NG_AS1 unsigned char*)v.B, k * v.sBk + j * v.sBj) : 0.f;
             }
 #pragma unroll
             for (int x = 0; x < NB; ++x)
 #pragma unroll
-                for (int y = 0; y < NB; ++y)
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x], b[y], acc[x][y], 0, 0, 0);
+                for (int e = 0; e < 16; ++e) {
+                    const int i = i0 + wm * (TS / 2) + 32 * x + 8 * (e >> 2) + 4 * h + (e & 3);
+                    const float a = i < v.M ? load1<ABF>((const NG_AS1 unsigned char*)v.A, i * v.sAi + k * v.sAk) : 0.f;
+#pragma unroll
+                    for (int y = 0; y < NB; ++y) acc[x][y][e] = k == 0 ? a * b[y] : fmaf(a, b[y], acc[x][y][e]);
+                }
         }
-    };
+    }
 
-    // Two register sets: a tile's loads are issued two k-steps before it is written to LDS (one step
-    // ahead is not enough for operands that stream from HBM).  Iteration kt: tile kt + 1 goes from its
-    // register set into the LDS buffer that tile kt - 1 was read from (everyone has passed the barrier that
-    // ended that step), the set is refilled with the loads of tile kt + 3, tile kt is multiplied, one barrier.
-    // (an odd number of k-steps gets one of zeros: leaving the loop in its middle would cost a second set of accumulators)
-    const int nk = (v.K + 2 * BK - 1) / (2 * BK) * 2;
-    // k-steps that each operand reads as whole vectors: an edge of one does not put the other on the clamped path
-    // (fp32 steps, two 1168-wide blocks at rank 292: 1055 -> 963 us; four 1000-wide ones at rank 500: 1731 -> 1604)
-    const int wholea = i0 + TS <= v.M ? v.K / BK : 0, wholeb = j0 + TS <= v.Nvalid ? v.K / BK : 0;
-    f32x4_t ra0[NV], rb0[NV], ra1[NV], rb1[NV];
-    auto fetch = [&](int kt, f32x4_t (&ra)[NV], f32x4_t (&rb)[NV]) {
-        if (kt >= nk) return;
-        if (kt < wholea) sa.fetch(kt, ra);
-        else sa.fetch_edge(kt, ra);
-        if (kt < wholeb) sb.fetch(kt, rb);
-        else sb.fetch_edge(kt, rb);
-    };
-    auto stage = [&](const f32x4_t (&ra)[NV], const f32x4_t (&rb)[NV], int buf) {
-        sa.stage(ra, lds.a[buf], t);
-        sb.stage(rb, lds.b[buf], t);
-    };
-    if (nk > 0) {
-        fetch(0, ra0, rb0);
-        fetch(1, ra1, rb1);
-        stage(ra0, rb0, 0);
-        fetch(2, ra0, rb0);
-        __syncthreads();
-        for (int kt = 0; kt < nk; kt += 2) {
-            stage(ra1, rb1, 1);
-            fetch(kt + 3, ra1, rb1);
-            multiply(0);
-            __syncthreads();
-            if (kt + 2 < nk) stage(ra0, rb0, 0);
-            fetch(kt + 4, ra0, rb0);
-            multiply(1);
-            __syncthreads();
+    // columns from Nvalid on (the padding of a state's rows) are zero
+    if (j0 + TS > v.Nvalid) {
+#pragma unroll
+        for (int y = 0; y < NB; ++y) {
+            const bool in = j0 + wn * (TS / 2) + 32 * y + li < v.Nvalid;
+#pragma unroll
+            for (int x = 0; x < NB; ++x)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[x][y][e] = in ? acc[x][y][e] : 0.f;
         }
     }
 
@@ -438,7 +553,7 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
 }
 
 template <int TS, bool AI, bool BJ, bool ABF, bool BBF, bool SYM>
-__global__ __launch_bounds__(256, TS == 128 ? 3 : 6) void k_gemm_f32(int op, const MatDev* __restrict__ mats,
+__global__ __launch_bounds__(256, TS == 128 ? 2 : 4) void k_gemm_f32(int op, const MatDev* __restrict__ mats,
                                                   const MatDyn* __restrict__ dyn, int grad_dtype,
                                                   StepScalars sc, const SymPlanes* __restrict__ sym, int side) {
     __shared__ __attribute__((aligned(16))) F32Tiles<TS> lds;
@@ -450,7 +565,7 @@ __global__ __launch_bounds__(256, TS == 128 ? 3 : 6) void k_gemm_f32(int op, con
 // per side has two ends at which the chip runs empty, the second for the few matrices of one side (four blocks
 // of width 450 at rank 56, 24 left and 4 right: step 138.8 -> 114.9 us).
 template <int TS, bool AL, bool BL, bool AR, bool BR>
-__global__ __launch_bounds__(256, TS == 128 ? 3 : 6) void k_gemm_f32_sides(int op, const MatDev* __restrict__ mats,
+__global__ __launch_bounds__(256, TS == 128 ? 2 : 4) void k_gemm_f32_sides(int op, const MatDev* __restrict__ mats,
                                                   const MatDyn* __restrict__ dyn, StepScalars sc) {
     __shared__ __attribute__((aligned(16))) F32Tiles<TS> lds;
     if (mats[blockIdx.z].side == NG_SIDE_RIGHT)

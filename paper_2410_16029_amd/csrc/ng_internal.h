@@ -227,7 +227,7 @@ void gemm_f32_dims(int op, const MatDev& md, int* M, int* N, int* K);
 // buffer that the next product fills (while an orthonormalisation runs), Yc for B B^T, and Bm once the
 // rotation staged in it has been applied.  Each holds at least order^2 floats, because order <= l <= m, n.
 constexpr int kSymPlanesMax = 8;
-constexpr int kSymStep = 16;       // k-step of the products: a contraction up to this long is not cut
+constexpr int kSymStep = 16;       // runs are whole multiples of this; a contraction up to this long is not cut
 struct SymPlanes {
     float* p;
     int order, count;

@@ -703,11 +703,13 @@ struct OctetSrc {
             ptr[p] = (const NG_AS1 unsigned char*)base + ((long long)oct[p] * ldn + (rowok[p] ? row : 0)) * 16;
         }
     }
-    __device__ __forceinline__ void issue(int kt, unsigned char* stage, const NG_AS1 unsigned char* zp, int wv) const {
+    // plane: bytes added to the address (one of several matrices of this shape that lie at a constant distance)
+    __device__ __forceinline__ void issue(int kt, unsigned char* stage, const NG_AS1 unsigned char* zp, int wv,
+                                          long long plane = 0) const {
 #pragma unroll
         for (int p = 0; p < INSTR; ++p) {
             const bool in = rowok[p] && (kt * KC + oct[p] < roct);
-            const NG_AS1 unsigned char* g = in ? ptr[p] + kt * step : zp;
+            const NG_AS1 unsigned char* g = in ? ptr[p] + (kt * step + plane) : zp;
             __builtin_amdgcn_global_load_lds((const NG_AS1 void*)g, (NG_AS3 void*)(stage + (p * C::NW + wv) * 1024), 16,
                                              0, 0);
         }
@@ -864,16 +866,11 @@ __device__ __forceinline__ void lds_read_tr16_done(u32x2_t& x, u32x2_t& y) {
 }
 __device__ __forceinline__ void lds_read_done(u32x4_t& x) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(x)::"memory"); }
 
-template <class C, int DBK>
+// R: columns per tile; NW: wavefronts; STREAM: cache policy of the loads (0 cached, 2 nontemporal).
+template <int R, int NW, int DBK, int STREAM>
 struct GradSrc {
-    // Cache policy of the gradient's loads (2: nontemporal).  Ranks up to 128 read it once, and streamed past
-    // the caches it does not push out the weights that the update has just written (72 encoder gradients
-    // at rank 8: step 147 -> 141 us; 60M set 154.4 -> 152.7 us).  At larger ranks, with several row tiles, or
-    // where cache lines are shared by two chunks' worth of columns, the second reader wants it cached
-    // (350M set, rank 256, rows of 2736: 2.02 -> 2.05 ms).
-    static constexpr int kStream = C::BM <= 128 ? 2 : 0;
-    static constexpr int JC = C::BN / 8, RPI = 64 / JC, INSTR = DBK / (RPI * C::NW);
-    static_assert((JC == 16 || JC == 32) && DBK % (RPI * C::NW) == 0 && (RPI * C::NW) % 4 == 0, "chunk mapping");
+    static constexpr int JC = R / 8, RPI = 64 / JC, INSTR = DBK / (RPI * NW);
+    static_assert((JC == 16 || JC == 32) && DBK % (RPI * NW) == 0 && (RPI * NW) % 4 == 0, "chunk mapping");
     const NG_AS1 unsigned char* ptr;   // this lane's chunk in contraction row 0 of the matrix
     long long pitch;                   // bytes per contraction row
     int krow, m;                       // krow: this lane's row within the rows of instruction 0; m: rows to fetch
@@ -896,10 +893,10 @@ struct GradSrc {
     __device__ __forceinline__ void issue(int kt, unsigned char* stage, const NG_AS1 unsigned char* zp, int wv) const {
 #pragma unroll
         for (int p = 0; p < INSTR; ++p) {
-            const int k = kt * DBK + p * C::NW * RPI + krow;   // (p NW RPI) % 4 == 0: the XOR of init holds for every p
+            const int k = kt * DBK + p * NW * RPI + krow;   // (p NW RPI) % 4 == 0: the XOR of init holds for every p
             const NG_AS1 unsigned char* g = (colok && k < m) ? ptr + k * pitch : (k == m ? lastp : zp);
-            __builtin_amdgcn_global_load_lds((const NG_AS1 void*)g, (NG_AS3 void*)(stage + (p * C::NW + wv) * 1024), 16,
-                                             0, kStream);
+            __builtin_amdgcn_global_load_lds((const NG_AS1 void*)g, (NG_AS3 void*)(stage + (p * NW + wv) * 1024), 16,
+                                             0, STREAM);
         }
     }
     // byte offset inside the stage that lane (li = lane % 32, h = lane / 32) passes to the first
@@ -921,7 +918,11 @@ __global__ __launch_bounds__(C::NT) void k_project_bf16_dl(const MatDev* __restr
     typedef DlCfg<C, DBK, NST> D;
     constexpr int KK = DBK / 16;
     typedef RowMajorSrc<C, DBK, C::BM> ARows;
-    typedef GradSrc<C, DBK> BGrad;
+    // Ranks up to 128 read the gradient once, and streamed past the caches it does not push out the weights that the
+    // update has just written (72 encoder gradients at rank 8: step 147 -> 141 us; 60M set 154.4 -> 152.7 us).  At
+    // larger ranks, with several row tiles, or where cache lines are shared by two chunks' worth of columns, the second
+    // reader wants it cached (350M set, rank 256, rows of 2736: 2.02 -> 2.05 ms).
+    typedef GradSrc<C::BN, C::NW, DBK, (C::BM <= 128 ? 2 : 0)> BGrad;
     static_assert(BGrad::INSTR == D::B_INSTR, "stage accounting");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
@@ -1065,204 +1066,242 @@ __global__ __launch_bounds__(C::NT) void k_project_bf16_dl(const MatDev* __restr
 }
 
 // =================================================================== refresh products with a bf16 gradient
-// The big products of the projector refresh multiply the bf16 gradient by an fp32 sketch matrix Y.
-// On the fp32 MFMA they run at a sixteenth of the bf16 rate, so Y is split on its way into LDS into
+// The big products of the projector refresh multiply the bf16 gradient by an fp32 sketch matrix Y (K x l).
+// On the fp32 MFMA they would run at a sixteenth of the bf16 rate, so Y is split into
 // three bf16 planes, Y = Y0 + Y1 + Y2 with Y0 = bf16(Y), Y1 = bf16(Y - Y0), Y2 = bf16(Y - Y0 - Y1)
 // (24 mantissa bits: the float itself unless it spans more than three bf16 exponent windows), and the
 // product is three bf16 MFMA products accumulated in fp32 -- the arithmetic of an fp32 GEMM whose
 // gradient operand is exactly representable, at three sixteenths of its MFMA cost.
 //
-// YTLoader: Y stored [k][x] with x contiguous (the sketch matrices are [rows][l]).  One 4 (k) x 8 (x)
-// block per thread and 64-deep tile, transposed in registers like the gradient tile of the
-// register-staged projection, each value split, written as 8-byte LDS words (4 consecutive k).
-template <class C>
-struct YTLoader {
-    static_assert(C::KG * (C::BM / 8) == C::NT && C::BM == C::BN, "one block per thread");
-    const NG_AS1 float* base;
-    long long ld;
-    int k_lim, x_lim, kg4, xcol;
-    f32x4_t r[4][2];
-    unsigned rowok;
+// The kernel that makes Y (fill_gaussian, the product with the inverse factor) stores the planes as octets of rows,
+// [K / 8][l][8], rows past K zero: a 16-byte chunk in memory is one MFMA fragment, as N is for the update.  Both operands go
+// from memory straight into LDS, three k-steps deep or two.  (Split on its way into LDS, once per row tile of the result, Y
+// cost more vector-ALU time than the products took of the matrix cores, and a k-step waited for its own loads: 168
+// products of 1024 x 1024 .. 2736 with 256 columns took 523 / 600 / 740 us with 1 / 2 / 3 planes; now 305 / 355 / 500,
+// i.e. up to 930 TFLOP/s; the 60M set's 61 / 66 / 80 us are 33 / 33 / 43.)  One plane is bound by its operands' way into
+// LDS, three by the matrix cores at the clock they hold.  256-row tiles with one workgroup of eight wavefronts per CU:
+// 299 / 343 / 490 us, but 38 / 41 / 57 on the 60M set, whose 278 tiles are one wave.
+//
+// FORM 1: C = Ya [m][l] = G Y        (Y [n][l]; G's rows are contraction-contiguous)
+// FORM 2: C = Yb [n][l] = G^T Y      (Y [m][l]; G through transposing reads, as in the projection)
+// FORM 3: C = Bm [l][ldn] = Y^T G    (Y [m][l]; the same, planes on the A side; columns >= n of C are zero)
+// NP: planes of Y that enter the product.  1 for the first product of a refresh, whose Y is the random test matrix
+// (rounding its entries to bf16 leaves it as good a test matrix as before); 2 (16 significant bits) for the products
+// inside the subspace iteration, whose results are re-orthonormalised and multiplied again; 3 for the last
+// basis and for B = Q^T G, which the Rayleigh-Ritz step takes at face value.
 
-    __device__ __forceinline__ void init(const float* Y, long long ld_, int k_lim_, int x_lim_, int x0, int t) {
-        base = (const NG_AS1 float*)Y;
-        ld = ld_;
-        k_lim = k_lim_;
-        x_lim = x_lim_;
-        kg4 = (t % C::KG) * 4;
-        xcol = x0 + 8 * (t / C::KG);
-    }
-    __device__ __forceinline__ void load(int k0) {
-        rowok = 0;
-        const bool whole = xcol + 8 <= x_lim;
+// The gradient's rows as tile rows: 16-byte chunks of 8 consecutive columns (at any 2-byte alignment) of R rows; the chunk
+// that would end past column n is left to the caller (n8: the columns in whole chunks).  Rows past the matrix re-read
+// its last one (their results are not stored).  LDS layout as RowMajorSrc's.
+template <int R, int NW, int DBK>
+struct GradRowSrc {
+    static constexpr int KC = DBK / 8, INSTR = R * KC / (64 * NW), RPI = 64 / KC;
+    static_assert(DBK == 32, "four chunks per row");
+    const NG_AS1 unsigned char* ptr[INSTR];
+    int kc, n8;
+    __device__ __forceinline__ void init(const void* G, long long ld_g, int rows, int n, int row0, int lane, int wv) {
+        const int lrow = lane / KC;
+        kc = (lane & 3) ^ ((lrow >> 2) & 3);
+        n8 = n & ~7;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int k = k0 + kg4 + q;
-            const bool ok = k < k_lim;
-            rowok |= ok ? (1u << q) : 0u;
-            const NG_AS1 float* row = base + (long long)(ok ? k : k_lim - 1) * ld;
-            if (whole) {
-                r[q][0] = *(const NG_AS1 f32x4_a4*)(row + xcol);
-                r[q][1] = *(const NG_AS1 f32x4_a4*)(row + xcol + 4);
-            } else {
-#pragma unroll
-                for (int c = 0; c < 8; ++c) r[q][c >> 2][c & 3] = (xcol + c < x_lim) ? row[xcol + c] : 0.f;
-            }
+        for (int p = 0; p < INSTR; ++p) {
+            const int row = row0 + (p * NW + wv) * RPI + lrow;
+            ptr[p] = (const NG_AS1 unsigned char*)G + ((long long)(row < rows ? row : rows - 1) * ld_g + kc * 8) * 2;
         }
     }
-    // P0, P1, P2: the plane tiles, [x][LDS_K] bf16 each; only the leading NP planes are written
-    template <int NP>
-    __device__ __forceinline__ void store(bf16_t* P0, bf16_t* P1, bf16_t* P2, int t) const {
-        const int xg = t / C::KG;
+    __device__ __forceinline__ void issue(int kt, unsigned char* stage, const NG_AS1 unsigned char* zp, int wv) const {
+        const bool in = kt * DBK + kc * 8 < n8;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            unsigned short h0[4], h1[4], h2[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float v = ((rowok >> q) & 1u) ? r[q][c >> 2][c & 3] : 0.f;
-                const unsigned a = f2bf(v);
-                const float r1 = v - __uint_as_float(a << 16);
-                const unsigned b = f2bf(r1);
-                const float r2 = r1 - __uint_as_float(b << 16);
-                h0[q] = (unsigned short)a;
-                h1[q] = (unsigned short)b;
-                h2[q] = (unsigned short)f2bf(r2);
-            }
-            const int off = (xg * 8 + c) * C::LDS_K + kg4;
-            *reinterpret_cast<u32x2_t*>(P0 + off) = (u32x2_t){h0[0] | ((unsigned)h0[1] << 16), h0[2] | ((unsigned)h0[3] << 16)};
-            if (NP == 1) continue;
-            *reinterpret_cast<u32x2_t*>(P1 + off) = (u32x2_t){h1[0] | ((unsigned)h1[1] << 16), h1[2] | ((unsigned)h1[3] << 16)};
-            if (NP == 2) continue;
-            *reinterpret_cast<u32x2_t*>(P2 + off) = (u32x2_t){h2[0] | ((unsigned)h2[1] << 16), h2[2] | ((unsigned)h2[3] << 16)};
+        for (int p = 0; p < INSTR; ++p) {
+            const NG_AS1 unsigned char* g = in ? ptr[p] + (long long)kt * (DBK * 2) : zp;
+            __builtin_amdgcn_global_load_lds((const NG_AS1 void*)g, (NG_AS3 void*)(stage + (p * NW + wv) * 1024), 16, 0, 0);
         }
     }
+    static __device__ __forceinline__ int frag(int row, int sw, int ks) { return (row * KC + (ks ^ sw)) * 16; }
+    static __device__ __forceinline__ int swz(int li) { return (li >> 2) & 3; }
 };
 
-// One BK-deep sweep: the plain operand's fragments against the three planes'.  PA: the planes are the A
-// operand (rows of the result), else the B operand.
-template <class C, bool PA, int NP>
-__device__ __forceinline__ void mma_tile_x3(floatx16 (&acc)[C::MI][C::NJ], const bf16_t* Gs, const bf16_t* P0, int wm,
-                                            int wn, int li, int h) {
-    constexpr int KK = C::BK / 16, PL = C::BM * C::LDS_K;   // elements per plane tile
-    const int prow = (PA ? wm * C::WM : wn * C::WN) + li, grow = (PA ? wn * C::WN : wm * C::WM) + li;
-    constexpr int PN = PA ? C::MI : C::NJ, GN = PA ? C::NJ : C::MI;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-        u32x4_t g[GN];
-#pragma unroll
-        for (int x = 0; x < GN; ++x)
-            g[x] = *reinterpret_cast<const u32x4_t*>(Gs + (grow + 32 * x) * C::LDS_K + kk * 16 + h * 8);
-#pragma unroll
-        for (int pl = 0; pl < NP; ++pl) {
-            u32x4_t y[PN];
-#pragma unroll
-            for (int x = 0; x < PN; ++x)
-                y[x] = *reinterpret_cast<const u32x4_t*>(P0 + pl * PL + (prow + 32 * x) * C::LDS_K + kk * 16 + h * 8);
-#pragma unroll
-            for (int mi = 0; mi < C::MI; ++mi)
-#pragma unroll
-                for (int nj = 0; nj < C::NJ; ++nj) {
-                    const u32x4_t& a = PA ? y[mi] : g[mi];
-                    const u32x4_t& b = PA ? g[nj] : y[nj];
-                    acc[mi][nj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(&a),
-                                                                          *reinterpret_cast<const bf16x8_t*>(&b),
-                                                                          acc[mi][nj], 0, 0, 0);
-                }
-        }
-    }
-}
+// Tile: TG rows or columns of the gradient x TL sketch columns, wavefronts of 64 x TL / 2, NST stages of 32.
+template <int TG_, int TL_, int NP_, int NST_>
+struct SketchCfg {
+    static constexpr int TG = TG_, TL = TL_, NP = NP_, NST = NST_, DBK = 32;
+    static constexpr int BM = TG, BN = TL, NWG = TG / 64, NW = 2 * NWG, NT = 64 * NW, WL = TL / 2, NL = WL / 32;
+    static constexpr int G_BYTES = TG * DBK * 2, P_BYTES = TL * DBK * 2, STAGE = G_BYTES + NP * P_BYTES, LDS = NST * STAGE;
+};
 
-// FORM 1: C = Ya [m][l] = G Y        (Y [n][l]; G rows are contraction-contiguous: chunk loader)
-// FORM 2: C = Yb [n][l] = G^T Y      (Y [m][l]; G through the transposing loader, as the A operand)
-// FORM 3: C = Bm [l][ldn] = Y^T G    (Y [m][l]: planes on the A side; G through the transposing
-//                                     loader; columns >= n of C are written as zero)
-// ysrc: which sketch buffer Y is (0 Ya, 1 Yb, 2 Yc).  One 128 x 128 tile per workgroup, 64-deep
-// k-steps, register-staged loads one step ahead.  NP: planes of Y that enter the product.  1 for the
-// first product of a refresh, whose Y is the random test matrix (rounding its entries to bf16
-// leaves it as good a test matrix as before); 2 (16 significant bits) for the products inside the
-// subspace iteration, whose results are re-orthonormalised and multiplied again; 3 for the last
-// basis and for B = Q^T G, which the Rayleigh-Ritz step takes at face value.
-template <class C, int FORM, int NP>
-__global__ __launch_bounds__(C::NT) void k_refresh_x3(const MatDev* __restrict__ mats, const MatDyn* __restrict__ dyn,
-                                                      int ysrc) {
+template <class C, int FORM>
+__global__ __launch_bounds__(C::NT, 2) void k_sketch_product(const MatDev* __restrict__ mats, const MatDyn* __restrict__ dyn,
+                                                             const TileRef* __restrict__ tiles, const void* zero16) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    static_assert(FORM >= 1 && FORM <= 3 && NP >= 1 && NP <= 3, "product form");
-    const MatDev& md = mats[blockIdx.z];
-    if (md.side == NG_SIDE_RIGHT) return;
-    const MatDyn dy = dyn[blockIdx.z];
-    const int M = FORM == 1 ? md.m : FORM == 2 ? md.n : md.l;
-    const int N = FORM == 3 ? md.ldn : md.l;
-    const int K = FORM == 1 ? md.n : md.m;
-    const int i0 = blockIdx.y * C::BM, j0 = blockIdx.x * C::BN;
-    if (i0 >= M || j0 >= N) return;
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int wm = wv / C::NWN, wn = wv % C::NWN, li = lane & 31, h = lane >> 5;
-    bf16_t* Gs = reinterpret_cast<bf16_t*>(smem);
-    bf16_t* P0 = Gs + C::BN * C::LDS_K;
-    bf16_t* P1 = P0 + C::BM * C::LDS_K;
-    bf16_t* P2 = P1 + C::BM * C::LDS_K;
-    const float* Y = ysrc == 0 ? md.Ya : ysrc == 1 ? md.Yb : md.Yc;
+    static_assert(FORM >= 1 && FORM <= 3 && C::NP >= 1 && C::NP <= 3, "product form");
+    constexpr int DBK = C::DBK, NP = C::NP, NL = C::NL, NST = C::NST;
+    typedef GradRowSrc<C::TG, C::NW, DBK> GRow;
+    typedef GradSrc<C::TG, C::NW, DBK, 0> GCol;
+    typedef OctetSrc<C, DBK, C::TL> Planes;
+    const TileRef tr = tiles[blockIdx.x];
+    if (tr.mat < 0) return;   // padding entry of the XCD-ordered table
+    const MatDev& md = mats[tr.mat];
+    const MatDyn dy = dyn[tr.mat];
+    const int g0 = tr.ti * C::TG, l0 = tr.tj * C::TL;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wg = wv >> 1, wl = wv & 1, li = lane & 31, h = lane >> 5;
+    const int m = md.m, n = md.n, l = md.l;
+    const int K = FORM == 1 ? n & ~7 : m;                          // (form 1: the rest of n after the loop)
+    const int nk = (K + DBK - 1) / DBK;
+    const NG_AS1 unsigned char* zp = (const NG_AS1 unsigned char*)zero16;
 
-    floatx16 acc[C::MI][C::NJ];
-    zero_acc<C>(acc);
+    floatx16 acc[2][NL];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < NL; ++y)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
 
-    // the planes' tile index runs over Y's columns (the l sketch columns): result rows in form 3,
-    // result columns otherwise
-    YTLoader<C> ly;
-    ly.init(Y, md.l, K, md.l, FORM == 3 ? i0 : j0, t);
-    BTLoader<C> lgt;   // forms 2, 3: tile index = gradient column
-    BKLoader<C> lgk;   // form 1: tile index = gradient row
-    const int g0 = FORM == 3 ? j0 : i0;
-    bool full = true, k8 = true;
-    if (FORM == 1) {
-        lgk.init(dy.g, md.ld_g, g0, md.m, md.n, t);
-        k8 = (md.n & 7) == 0;
-    } else {
-        lgt.init(dy.g, md.ld_g, md.m, md.n, g0, t);
-        full = (md.n >= 8) && ((md.n & 7) == 0 || g0 + C::BN <= md.n);
-    }
-    const int nk = (K + C::BK - 1) / C::BK;
-    auto loads = [&](int k0) {
-        ly.load(k0);
-        if (FORM == 1) {
-            if (k8) lgk.template load<true>(k0);
-            else lgk.template load<false>(k0);
-        } else {
-            if (full) lgt.template load<true>(k0);
-            else lgt.template load<false>(k0);
+    GRow gr;
+    GCol gc;
+    if (FORM == 1) gr.init(dy.g, md.ld_g, m, n, g0, lane, wv);
+    else gc.init(dy.g, md.ld_g, m, n, g0, lane, wv,
+                 md.tail8_off >= 0 ? (const void*)step_scratch<char>(dyn, md.tail8_off) : zero16, zp);
+    Planes pl;
+    pl.init(md.Yp, l, FORM == 1 ? n >> 3 : (m + 7) >> 3, l0, lane, wv);
+    const long long plane = md.yp_plane * 2;                       // bytes from one plane to the next
+    auto issue = [&](int kt) {
+        unsigned char* stage = smem + (kt % NST) * C::STAGE;
+        if (FORM == 1) gr.issue(kt, stage, zp, wv);
+        else gc.issue(kt, stage, zp, wv);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) pl.issue(kt, stage + C::G_BYTES + p * C::P_BYTES, zp, wv, p * plane);
+    };
+
+    // fragment addresses inside a stage
+    const unsigned smem_lds = (unsigned)(unsigned long long)(NG_AS3 unsigned char*)smem;
+    unsigned g_off[2][2];      // [16-deep step][32-row block]
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+            g_off[kk][x] = FORM == 1 ? GRow::frag(wg * 64 + 32 * x + li, GRow::swz(li), 2 * kk + h)
+                                     : GCol::frag(wg * 64 + 32 * x, li, h) + kk * 16 * GCol::ROW_BYTES;
+    const unsigned p_off = C::G_BYTES + Planes::frag(wl * C::WL + li, 0, h);
+    struct Frag {
+        u32x4_t g[2], y[NP][NL];
+        u32x2_t lo[2], hi[2];
+    };
+    Frag f[2];
+    constexpr int STEP_READS = (FORM == 1 ? 2 : 4) + NP * NL;
+    static_assert(STEP_READS <= 15, "the wait count of one step must fit the counter");
+    auto read_step = [&](unsigned cur, int kk) {   // kk is a literal at every call
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            if (FORM == 1) {
+                lds_read_b128(f[kk].g[x], cur + g_off[kk][x], 0);
+            } else {
+                lds_read_tr16(f[kk].lo[x], cur + g_off[kk][x], 0);
+                lds_read_tr16(f[kk].hi[x], cur + g_off[kk][x], 4 * GCol::ROW_BYTES);
+            }
         }
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int y = 0; y < NL; ++y)
+                lds_read_b128(f[kk].y[p][y], cur + p_off, p * C::P_BYTES + 2 * kk * C::TL * 16 + 32 * y * 16);
     };
-    auto stores = [&]() {
-        ly.template store<NP>(P0, P1, P2, t);
-        if (FORM == 1) lgk.store(Gs, t);
-        else if (full) lgt.template store<true>(Gs, t);
-        else lgt.template store<false>(Gs, t);
+    auto done_step = [&](int kk, bool later) {     // the reads of step kk; later: those of the other one were issued behind them
+        if (later) asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(STEP_READS) : "memory");
+        else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            if (FORM == 1) asm volatile("" : "+v"(f[kk].g[x])::"memory");
+            else asm volatile("" : "+v"(f[kk].lo[x]), "+v"(f[kk].hi[x])::"memory");
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int y = 0; y < NL; ++y) asm volatile("" : "+v"(f[kk].y[p][y])::"memory");
     };
-    loads(0);
-    stores();
-    __syncthreads();
+    auto multiply = [&](const Frag& v) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < NL; ++y) {
+                    const u32x4_t gv = FORM == 1 ? v.g[x] : (u32x4_t){v.lo[x].x, v.lo[x].y, v.hi[x].x, v.hi[x].y};
+                    const bf16x8_t g = *reinterpret_cast<const bf16x8_t*>(&gv), q = *reinterpret_cast<const bf16x8_t*>(&v.y[p][y]);
+                    acc[x][y] = FORM == 3 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(q, g, acc[x][y], 0, 0, 0)
+                                          : __builtin_amdgcn_mfma_f32_32x32x16_bf16(g, q, acc[x][y], 0, 0, 0);
+                }
+    };
+
+    // Ring as in the update: the loads of the stages up to kt + NST - 2 have been issued before stage kt is multiplied,
+    // and the barrier tells everyone that stage kt has landed and that buffer (kt - 1) % NST has been read.
+    constexpr int PER_STAGE = (FORM == 1 ? GRow::INSTR : GCol::INSTR) + NP * Planes::INSTR;
+    static_assert(NST >= 2 && NST <= 4 && (NST - 2) * PER_STAGE <= 63, "ring depth / wait counter");
+    for (int q = 0; q < NST - 1; ++q)
+        if (q < nk) issue(q);
     for (int kt = 0; kt < nk; ++kt) {
-        if (kt + 1 < nk) loads((kt + 1) * C::BK);
-        mma_tile_x3<C, FORM == 3, NP>(acc, Gs, P0, wm, wn, li, h);
-        __syncthreads();
-        if (kt + 1 < nk) stores();
-        __syncthreads();
+        const int ahead = nk - kt - 1;             // stages issued beyond this one: at most NST - 2
+        if (NST >= 4 && ahead >= 2) wait_vmcnt<(NST >= 4 ? 2 : 0) * PER_STAGE>();
+        else if (NST >= 3 && ahead >= 1) wait_vmcnt<(NST >= 3 ? 1 : 0) * PER_STAGE>();
+        else wait_vmcnt<0>();
+        asm volatile("s_barrier" ::: "memory");    // (bare: __syncthreads() would also wait for the loads in flight)
+        if (kt + NST - 1 < nk) issue(kt + NST - 1);
+        const unsigned cur = smem_lds + (unsigned)(kt % NST) * C::STAGE;
+        read_step(cur, 0);
+        read_step(cur, 1);
+        done_step(0, true);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(f[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        done_step(1, false);
+        multiply(f[1]);
     }
+    if (FORM == 1 && (n & 7) != 0) {
+        // the last n % 8 columns: one more 16-deep step, its upper half zero, element by element
+        Frag v;
+        const int k0 = n & ~7;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const int row = g0 + wg * 64 + 32 * x + li;
+            const NG_AS1 bf16_t* src = (const NG_AS1 bf16_t*)dy.g + (long long)(row < m ? row : m - 1) * md.ld_g + k0;
+            unsigned e[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) e[c] = h == 0 && k0 + c < n ? (unsigned)src[c] : 0u;
+            v.g[x] = (u32x4_t){e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int y = 0; y < NL; ++y) {
+                const int col = l0 + wl * C::WL + 32 * y + li;
+                const bool in = h == 0 && col < l;
+                const u32x4_t q = *(const NG_AS1 u32x4_t*)((const NG_AS1 bf16_t*)md.Yp + p * md.yp_plane + ((long long)(k0 >> 3) * l + (col < l ? col : 0)) * 8);
+                v.y[p][y] = zero_unless(in, q);
+            }
+        multiply(v);
+    }
+
     float* Cout = FORM == 1 ? md.Ya : FORM == 2 ? md.Yb : md.Bm;
-    const int ldc = FORM == 3 ? md.ldn : md.l;
+    const int ldc = FORM == 3 ? md.ldn : l;
 #pragma unroll
-    for (int mi = 0; mi < C::MI; ++mi)
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int nj = 0; nj < C::NJ; ++nj) {
-            const int col = j0 + wn * C::WN + nj * 32 + li;
+        for (int y = 0; y < NL; ++y)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int row = i0 + wm * C::WM + mi * 32 + 8 * g + 4 * h + e;
-                    if (row < M && col < N) Cout[(long long)row * ldc + col] = acc[mi][nj][4 * g + e];
+                    const float v = acc[x][y][4 * g + e];
+                    const int gi = g0 + wg * 64 + 32 * x + (FORM == 3 ? li : 8 * g + 4 * h + e);
+                    const int lc = l0 + wl * C::WL + 32 * y + (FORM == 3 ? 8 * g + 4 * h + e : li);
+                    NG_AS1 float* dst = (NG_AS1 float*)Cout + (FORM == 3 ? (long long)lc * ldc + gi : (long long)gi * ldc + lc);
+                    if (lc < l) {
+                        if (gi < (FORM == 1 ? m : n)) *dst = v;
+                        else if (FORM == 3 && gi < ldc) *dst = 0.f;
+                    }
                 }
-        }
 }
 
 // =================================================================== launchers
@@ -1372,32 +1411,29 @@ void bf16_tile_shape(int which, int max_r, long long tiles4, int* bm, int* bn) {
     else set(Cfg4::BM, Cfg4::BN);
 }
 
-template <int FORM, int NP>
-static hipError_t run_refresh_x3(dim3 g, const MatDev* mats, const MatDyn* dyn, int ysrc, hipStream_t stream) {
-    typedef Cfg0 C;
-    constexpr int lds = (C::BN + NP * C::BM) * C::LDS_K * 2;
-    static bool attr = false;
-    if (!attr) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_refresh_x3<C, FORM, NP>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        attr = true;
-    }
-    hipLaunchKernelGGL((k_refresh_x3<C, FORM, NP>), g, dim3(C::NT), lds, stream, mats, dyn, ysrc);
+template <class C, int FORM>
+static hipError_t run_sketch(const MatDev* mats, const MatDyn* dyn, const TileRef* tiles, int n_tiles, const void* zero16,
+                             hipStream_t stream) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(k_sketch_product<C, FORM>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+    (void)attr;
+    hipLaunchKernelGGL((k_sketch_product<C, FORM>), dim3(n_tiles), dim3(C::NT), C::LDS, stream, mats, dyn, tiles, zero16);
     return hipGetLastError();
 }
 
-hipError_t launch_refresh_x3(int form, int ysrc, int planes, const MatDev* mats, const MatDyn* dyn, int n_mats,
-                             int max_m, int max_n, hipStream_t stream) {
-    typedef Cfg0 C;
-    const dim3 g((max_n + C::BN - 1) / C::BN, (max_m + C::BM - 1) / C::BM, n_mats);
-    if (form == 1 && planes == 1) return run_refresh_x3<1, 1>(g, mats, dyn, ysrc, stream);
-    if (form == 1 && planes == 2) return run_refresh_x3<1, 2>(g, mats, dyn, ysrc, stream);
-    if (form == 1 && planes == 3) return run_refresh_x3<1, 3>(g, mats, dyn, ysrc, stream);
-    if (form == 2 && planes == 2) return run_refresh_x3<2, 2>(g, mats, dyn, ysrc, stream);
-    if (form == 2 && planes == 3) return run_refresh_x3<2, 3>(g, mats, dyn, ysrc, stream);
-    if (form == 3 && planes == 3) return run_refresh_x3<3, 3>(g, mats, dyn, ysrc, stream);
+hipError_t launch_sketch_product(int form, int planes, const MatDev* mats, const MatDyn* dyn, const TileRef* tiles,
+                                 int n_tiles, const void* zero16, hipStream_t stream) {
+    if (n_tiles == 0) return hipSuccess;
+#define NG_SKETCH_CASE(FORM, NP, NST) \
+    if (form == FORM && planes == NP) return run_sketch<SketchCfg<kSketchTileG, kSketchTileL, NP, NST>, FORM>(mats, dyn, tiles, n_tiles, zero16, stream)
+    NG_SKETCH_CASE(1, 1, 4);
+    NG_SKETCH_CASE(1, 2, 3);
+    NG_SKETCH_CASE(1, 3, 2);
+    NG_SKETCH_CASE(2, 2, 3);
+    NG_SKETCH_CASE(2, 3, 2);
+    NG_SKETCH_CASE(3, 3, 2);
+#undef NG_SKETCH_CASE
     return hipErrorInvalidValue;
 }
 
 }  // namespace ng
-

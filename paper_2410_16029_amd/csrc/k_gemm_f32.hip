@@ -203,7 +203,7 @@ __device__ __forceinline__ f32x4_t load4(const NG_AS1 unsigned char* p) {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
 // Beyond this a value may round to an infinity in bf16, and an infinity times a lower plane is NaN: tiles that
 // meet one are computed again in plain fp32 (see gemm_f32_tile).
@@ -517,6 +517,34 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
         }
     }
 
+    // the sketch planes that a gradient product reads next: octets of rows (a lane's four rows are half an octet), rows past
+    // the last zero
+    if (v.b_tri && sc.planes > 0) {
+        const long long plane = md.yp_plane;
+#pragma unroll
+        for (int bi = 0; bi < NB; ++bi)
+#pragma unroll
+            for (int bj = 0; bj < NB; ++bj) {
+                const int col = j0 + wn * (TS / 2) + bj * 32 + li;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int oct = i0 + wm * (TS / 2) + bi * 32 + 8 * g;       // its first row
+                    float x[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] = oct + 4 * h + e < v.M ? acc[bi][bj][4 * g + e] : 0.f;
+                    unsigned lo[3], hi[3];
+                    split2<3>(x[0], x[1], lo);
+                    split2<3>(x[2], x[3], hi);
+                    if (oct < v.M && col < v.N) {
+                        NG_AS1 bf16_t* dst = (NG_AS1 bf16_t*)md.Yp + ((long long)(oct >> 3) * md.l + col) * 8 + 4 * h;
+#pragma unroll
+                        for (int p = 0; p < 3; ++p)
+                            if (p < sc.planes) *(NG_AS1 u32x2_t*)(dst + p * plane) = (u32x2_t){lo[p], hi[p]};
+                    }
+                }
+            }
+        if (sc.planes_only) return;
+    }
     const bool whole = i0 + TS <= v.M && j0 + TS <= v.N;
 #pragma unroll
     for (int bi = 0; bi < NB; ++bi)

@@ -27,26 +27,44 @@ __device__ __forceinline__ unsigned long long mix64(unsigned long long z) {
     return z ^ (z >> 31);
 }
 
+__device__ __forceinline__ float gaussian(unsigned long long key, long long i) {
+    const unsigned long long z = mix64(key + (unsigned long long)(i + 1) * 0x9E3779B97F4A7C15ULL);
+    const float u1 = ((float)(unsigned int)(z >> 40) + 1.0f) * (1.0f / 16777216.0f);      // (0, 1]
+    const float u2 = (float)(unsigned int)((z >> 8) & 0xFFFFFFu) * (1.0f / 16777216.0f);   // [0, 1)
+    return sqrtf(-2.0f * logf(u1)) * cosf(6.28318530717958647692f * u2);
+}
+
+// PLANE: eight rows of one column per thread, rounded to bf16, as the octets that a gradient product reads
+template <bool PLANE>
 __global__ __launch_bounds__(256) void k_fill_gaussian(const MatDev* __restrict__ mats, unsigned long long seed,
                                                        unsigned long long call_id) {
     const MatDev& md = mats[blockIdx.y];
-    const long long total = (long long)md.n * md.l;
     const unsigned long long key =
         mix64(seed ^ (call_id * 0x9E3779B97F4A7C15ULL) ^ ((unsigned long long)(blockIdx.y + 1) * 0xD1B54A32D192ED03ULL));
+    const int n = md.n, l = md.l;
+    const long long total = PLANE ? (long long)((n + 7) / 8) * l : (long long)n * l;
     for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
-        const unsigned long long z = mix64(key + (unsigned long long)(i + 1) * 0x9E3779B97F4A7C15ULL);
-        const float u1 = ((float)(unsigned int)(z >> 40) + 1.0f) * (1.0f / 16777216.0f);      // (0, 1]
-        const float u2 = (float)(unsigned int)((z >> 8) & 0xFFFFFFu) * (1.0f / 16777216.0f);   // [0, 1)
-        md.Yb[i] = sqrtf(-2.0f * logf(u1)) * cosf(6.28318530717958647692f * u2);
+        if (!PLANE) {
+            md.Yb[i] = gaussian(key, i);
+            continue;
+        }
+        const int oct = (int)(i / l), col = (int)(i - (long long)oct * l);
+        typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+        bf16x8_t v;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            v[e] = (__bf16)(8 * oct + e < n ? gaussian(key, (long long)(8 * oct + e) * l + col) : 0.f);
+        *reinterpret_cast<bf16x8_t*>(md.Yp + 8 * i) = v;
     }
 }
 
-hipError_t launch_fill_gaussian(const MatDev* mats, int n_mats, int max_rows, unsigned long long seed,
+hipError_t launch_fill_gaussian(const MatDev* mats, int n_mats, int max_rows, bool plane, unsigned long long seed,
                                 unsigned long long call_id, hipStream_t stream) {
     int gx = (max_rows + 3) / 4;   // grid-stride loop covers the rest
     if (gx < 1) gx = 1;
     if (gx > 4096) gx = 4096;
-    hipLaunchKernelGGL(k_fill_gaussian, dim3(gx, n_mats), dim3(256), 0, stream, mats, seed, call_id);
+    if (plane) hipLaunchKernelGGL(k_fill_gaussian<true>, dim3((gx + 7) / 8, n_mats), dim3(256), 0, stream, mats, seed, call_id);
+    else hipLaunchKernelGGL(k_fill_gaussian<false>, dim3(gx, n_mats), dim3(256), 0, stream, mats, seed, call_id);
     return hipGetLastError();
 }
 

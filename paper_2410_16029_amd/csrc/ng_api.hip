@@ -63,7 +63,7 @@ struct Sizes {   // per-matrix derived sizes
     size_t k_gram_off, k_w64_off, k_w32_off;
     size_t aux_pb_off, aux_pbt_off;
     // refresh scratch
-    size_t ws_y, ws_bm, ws_t, ws_linv, ws_ritz, ws_order, ws_flag, ws_parts, ws_carry, ws_proj;
+    size_t ws_y, ws_yp, ws_bm, ws_t, ws_linv, ws_ritz, ws_order, ws_flag, ws_parts, ws_carry, ws_proj;
     int proj_chunks, proj_rows;   // row chunks of the fp32 projection (0: none)
 };
 
@@ -159,6 +159,7 @@ void derive(const ng_matrix_desc& user, const ng_hparams& hp, int skinny_rk, Siz
     }
     const size_t rows = (size_t)(d.m > d.n ? d.m : d.n);
     z->ws_y = align_up(rows * l * 4, 256);
+    z->ws_yp = align_up((rows + 7) / 8 * 8 * l * 2, 256) * 3;      // (sketch planes; dropped where the set does not use them)
     z->ws_bm = align_up((size_t)l * z->ldn * 4, 256);
     z->ws_t = align_up((size_t)z->lp * z->lp * 8, 256);
     z->ws_linv = align_up((size_t)z->lp * z->lp * 4, 256);
@@ -176,10 +177,12 @@ void derive(const ng_matrix_desc& user, const ng_hparams& hp, int skinny_rk, Siz
 struct Plan {
     std::vector<Sizes> sz;
     std::vector<TileRef> proj, upd, dots, patches, skinny;
+    bool sketch_planes;                         // the refresh's gradient products read bf16 planes (launch_sketch_product)
+    std::vector<TileRef> sketch[3];             // their tiles, by form - 1
     int skinny_rk;                              // 0: the MFMA / fp32-GEMM projection and update
     long long tiles4;                           // 256 x 256 tiles of the left-side projection
     int proj_direct, proj_staged, proj_right;   // lengths of the three runs of proj
-    size_t off_status, off_mats, off_step, off_proj, off_upd, off_dots, off_patches, off_skinny, off_sym, off_scratch;
+    size_t off_status, off_mats, off_step, off_proj, off_upd, off_dots, off_patches, off_skinny, off_sym, off_sketch[3], off_scratch;
     // the scratch block of one step: the per-step table, then what the step's kernels hand to each
     // other (offsets from the start of the block; per matrix)
     size_t step_tail8_off, step_bytes;
@@ -255,6 +258,25 @@ void make_plan(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* 
         p->proj.insert(p->proj.end(), c.begin(), c.end());
     }
     xcd_order(upd, cost_upd, &p->upd);
+    // The refresh's products with bf16 gradients: sets on the left side (the right side's gradients are read along their
+    // other dimension) of at least 8 columns (see projection_tile_direct).  Forms 1 and 2 list a matrix's column tiles of one
+    // gradient tile next to each other, form 3 its row tiles: they share the gradient tile in one XCD's L2.
+    p->sketch_planes = hp.grad_dtype == NG_BF16 && all_left;
+    for (int i = 0; i < n_mats; ++i) p->sketch_planes = p->sketch_planes && projection_tile_direct(d[i].n);
+    for (int f = 0; f < 3; ++f) p->sketch[f].clear();
+    for (int i = 0; i < n_mats; ++i)
+        if (!p->sketch_planes) p->sz[i].ws_yp = 0;
+    for (int f = 0; f < 3 && p->sketch_planes; ++f) {
+        std::vector<TileRef> logical;
+        std::vector<int> cost;
+        for (int i = 0; i < n_mats; ++i)
+            for (int ti = 0; ti < ceil_div(f == 0 ? d[i].m : f == 1 ? d[i].n : p->sz[i].ldn, kSketchTileG); ++ti)
+                for (int tj = 0; tj < ceil_div(p->sz[i].l, kSketchTileL); ++tj) {
+                    logical.push_back(TileRef{i, ti, tj, 0});
+                    cost.push_back(f == 0 ? d[i].n : d[i].m);
+                }
+        xcd_order(logical, cost, &p->sketch[f]);
+    }
     // Gram-row parts are appended in make_mats (they need dot_nparts)
     size_t off = 0;
     p->off_status = off; off += 256;
@@ -319,10 +341,14 @@ void make_plan(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* 
     p->off_patches = off; off += align_up(sizeof(TileRef) * p->patches.size(), 256);
     p->off_skinny = off;  off += align_up(sizeof(TileRef) * p->skinny.size(), 256);
     p->off_sym = off;     off += align_up(sizeof(SymPlanes) * kSymOps * (size_t)n_mats, 256);
+    for (int f = 0; f < 3; ++f) {
+        p->off_sketch[f] = off;
+        off += align_up(sizeof(TileRef) * p->sketch[f].size(), 256);
+    }
     p->off_scratch = off;
     for (int i = 0; i < n_mats; ++i) {
         const Sizes& z = p->sz[i];
-        off += 3 * z.ws_y + z.ws_bm + z.ws_t + z.ws_linv + z.ws_ritz + z.ws_order + z.ws_flag + z.ws_carry;
+        off += 3 * z.ws_y + z.ws_yp + z.ws_bm + z.ws_t + z.ws_linv + z.ws_ritz + z.ws_order + z.ws_flag + z.ws_carry;
     }
     p->total = off;
 }
@@ -346,7 +372,7 @@ struct ng_state {
     MatDev* d_mats;
     MatDyn* d_dyn;
     int* d_status;
-    TileRef *d_proj, *d_upd, *d_dots, *d_patches, *d_skinny;
+    TileRef *d_proj, *d_upd, *d_dots, *d_patches, *d_skinny, *d_sketch[3];
     SymPlanes* d_sym;   // [kSymOps][n_mats]
     int n_dots;
     int max_m, max_n, max_r, max_l, max_lp, max_rows, max_ldn;
@@ -397,7 +423,7 @@ int upload_dyn(ng_state* st, MatDyn* dyn, const void* const* grads, void* const*
             }
         }
         NG_HIP(launch_upload_dyn(dyn, chunk, first, n,
-                                 (stepping && st->hp.grad_dtype == NG_BF16) ? st->d_mats : nullptr, stream));
+                                 st->hp.grad_dtype == NG_BF16 ? st->d_mats : nullptr, stream));
     }
     return NG_OK;
 }
@@ -426,28 +452,20 @@ int clear_history(ng_state* st, hipStream_t stream) {
     return NG_OK;
 }
 
-// The refresh's products with the gradient: OP_G_B2A / OP_G_C2A (Ya = G Y), OP_GT_C2B (Yb = G^T Y),
-// OP_QT_G (Bm = Ya^T G).  bf16 gradients on the left side take three bf16 MFMA
-// products (launch_refresh_x3), everything else the fp32 GEMM.
 int gemm(ng_state* st, GemmOp op, hipStream_t stream, const StepScalars& sc, const MatDyn* dyn = nullptr);
+
+// Sketch planes that enter a product with the gradient: the random test matrix needs one, the last basis and B = Q^T G
+// all three, the products inside the subspace iteration two.
+int sketch_planes(GemmOp op, bool last) { return op == OP_G_B2A ? 1 : op == OP_QT_G || last ? 3 : 2; }
+
+// The refresh's products with the gradient: OP_G_B2A / OP_G_C2A (Ya = G Y), OP_GT_C2B (Yb = G^T Y),
+// OP_QT_G (Bm = Ya^T G).
 int gradient_product(ng_state* st, GemmOp op, bool last, hipStream_t stream, const StepScalars& sc) {
-    if (st->hp.grad_dtype == NG_BF16 && !(st->sides & 2)) {
-        // planes of the sketch that enter: the random test matrix needs one, the last basis and
-        // B = Q^T G all three, the products inside the subspace iteration two
-        int form = 0, ysrc = 0, planes = last ? 3 : 2;
-        switch (op) {
-            case OP_G_B2A: form = 1; ysrc = 1; planes = 1; break;
-            case OP_G_C2A: form = 1; ysrc = 2; break;
-            case OP_GT_C2B: form = 2; ysrc = 2; break;
-            case OP_QT_G: form = 3; ysrc = 0; planes = 3; break;
-            default: break;
-        }
-        if (form != 0) {
-            NG_HIP(launch_refresh_x3(form, ysrc, planes, st->d_mats, st->d_dyn, st->n_mats, st->max_ti[op], st->max_tj[op], stream));
-            return NG_OK;
-        }
-    }
-    return gemm(st, op, stream, sc);
+    if (!st->plan.sketch_planes) return gemm(st, op, stream, sc);
+    const int form = op == OP_QT_G ? 3 : op == OP_GT_C2B ? 2 : 1;
+    NG_HIP(launch_sketch_product(form, sketch_planes(op, last), st->d_mats, st->d_dyn, st->d_sketch[form - 1],
+                                 (int)st->plan.sketch[form - 1].size(), (const char*)st->d_status + 64, stream));
+    return NG_OK;
 }
 
 const SymPlanes* planes_of(const ng_state* st, GemmOp op) {
@@ -475,13 +493,17 @@ int inverse_factor(ng_state* st, GemmOp op, double shift_rel, hipStream_t stream
 //                  power iteration from collapsing;
 //   twice = true : a second, unshifted pass repairs the first pass's loss of orthogonality and
 //                  puts the result back in X (the basis handed to the Rayleigh-Ritz step).
-int orthonormalise(ng_state* st, bool is_a, bool twice, hipStream_t stream, const StepScalars& sc) {
+// planes: what the product that reads the result next takes; one pass then leaves the planes only.
+int orthonormalise(ng_state* st, bool is_a, bool twice, int planes, hipStream_t stream, StepScalars sc) {
     int rc;
+    StepScalars result = sc;
+    result.planes = st->plan.sketch_planes ? planes : 0;
+    result.planes_only = !twice;
     if ((rc = inverse_factor(st, is_a ? OP_GRAM_A : OP_GRAM_B, 2e-7, stream, sc)) != NG_OK) return rc;
-    if ((rc = gemm(st, is_a ? OP_APPLY_A2C : OP_APPLY_B2C, stream, sc)) != NG_OK) return rc;
+    if ((rc = gemm(st, is_a ? OP_APPLY_A2C : OP_APPLY_B2C, stream, twice ? sc : result)) != NG_OK) return rc;
     if (!twice) return NG_OK;
     if ((rc = inverse_factor(st, is_a ? OP_GRAM_CA : OP_GRAM_CB, 0.0, stream, sc)) != NG_OK) return rc;
-    if ((rc = gemm(st, is_a ? OP_APPLY_C2A : OP_APPLY_C2B, stream, sc)) != NG_OK) return rc;
+    if ((rc = gemm(st, is_a ? OP_APPLY_C2A : OP_APPLY_C2B, stream, result)) != NG_OK) return rc;
     return NG_OK;
 }
 
@@ -697,6 +719,7 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
         st->d_patches = (TileRef*)(ws + pl.off_patches);
         st->d_skinny = (TileRef*)(ws + pl.off_skinny);
         st->d_sym = (SymPlanes*)(ws + pl.off_sym);
+        for (int f = 0; f < 3; ++f) st->d_sketch[f] = (TileRef*)(ws + pl.off_sketch[f]);
 
         st->mats.resize(n_mats);
         std::vector<TileRef> dots;
@@ -742,6 +765,8 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
             // Yb ([max(m,n)][l] floats, l >= r), which is free from the Rayleigh-Ritz step on
             if (hp->proj_dtype == NG_BF16) md.P = md.Yb;
             md.Yc = (float*)(ws + off); off += z.ws_y;
+            md.Yp = z.ws_yp ? (bf16_t*)(ws + off) : nullptr; off += z.ws_yp;
+            md.yp_plane = (long long)(z.ws_yp / 3 / 2);
             md.Bm = (float*)(ws + off); off += z.ws_bm;
             md.T = (double*)(ws + off); off += z.ws_t;
             md.Linv = (float*)(ws + off); off += z.ws_linv;
@@ -826,6 +851,9 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
             e = hipMemcpy(st->d_patches, pl.patches.data(), sizeof(TileRef) * pl.patches.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess && !pl.skinny.empty())
             e = hipMemcpy(st->d_skinny, pl.skinny.data(), sizeof(TileRef) * pl.skinny.size(), hipMemcpyHostToDevice);
+        for (int f = 0; f < 3; ++f)
+            if (e == hipSuccess && !pl.sketch[f].empty())
+                e = hipMemcpy(st->d_sketch[f], pl.sketch[f].data(), sizeof(TileRef) * pl.sketch[f].size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             delete st;
@@ -878,17 +906,17 @@ int ng_refresh_projector(ng_state* st, const void* const* grads, ng_stream strea
     if ((rc = upload_dyn(st, st->d_dyn, grads, nullptr, false, stream)) != NG_OK) return rc;
 
     // randomised subspace iteration: Ya = orth(G Omega); q times { Yb = orth(G^T Ya); Ya = orth(G Yb) }
-    NG_HIP(launch_fill_gaussian(st->d_mats, st->n_mats, st->max_n, st->hp.seed,
+    NG_HIP(launch_fill_gaussian(st->d_mats, st->n_mats, st->max_n, st->plan.sketch_planes, st->hp.seed,
                                 (unsigned long long)st->n_refresh[0], stream));
     const int q = st->hp.refresh_power_iters;
     if ((rc = gradient_product(st, OP_G_B2A, q == 0, stream, sc)) != NG_OK) return rc;
-    if ((rc = orthonormalise(st, true, q == 0, stream, sc)) != NG_OK) return rc;
+    if ((rc = orthonormalise(st, true, q == 0, q == 0 ? 3 : 2, stream, sc)) != NG_OK) return rc;
     for (int it = 0; it < q; ++it) {
         // intermediate bases live in Yc (single-pass orthonormalisation)
         if ((rc = gradient_product(st, OP_GT_C2B, false, stream, sc)) != NG_OK) return rc;
-        if ((rc = orthonormalise(st, false, false, stream, sc)) != NG_OK) return rc;
+        if ((rc = orthonormalise(st, false, false, sketch_planes(OP_G_C2A, it + 1 == q), stream, sc)) != NG_OK) return rc;
         if ((rc = gradient_product(st, OP_G_C2A, it + 1 == q, stream, sc)) != NG_OK) return rc;
-        if ((rc = orthonormalise(st, true, it + 1 == q, stream, sc)) != NG_OK) return rc;
+        if ((rc = orthonormalise(st, true, it + 1 == q, it + 1 == q ? 3 : 2, stream, sc)) != NG_OK) return rc;
     }
     // Rayleigh-Ritz: B = Q^T G, T = B B^T = U diag(ritz^2) U^T, P = Q U[:, top r]
     if ((rc = gradient_product(st, OP_QT_G, true, stream, sc)) != NG_OK) return rc;

@@ -65,6 +65,8 @@ struct MatDev {
     float* Ya;        // [max(m,n)][l]
     float* Yb;        // [max(m,n)][l]
     float* Yc;        // [max(m,n)][l]
+    bf16_t* Yp;       // three planes [max(m,n) / 8][l][8] of the sketch that a gradient product reads, yp_plane
+    long long yp_plane;   // elements apart (null: the set's gradient products run on the fp32 GEMM)
     float* Bm;        // [l][ldn]   B = Q^T G; later the l x r rotation
     double* T;        // [lp][lp]   Gram matrix / Cholesky factor of orders above kFactorMax
     float* Linv;      // [lp][lp]   inverse Cholesky factor (float); during the Rayleigh-Ritz step the rows
@@ -160,6 +162,8 @@ struct StepScalars {
     int hist_bf16;       // history slots are bf16 (else float)
     int norm_count;      // Fisher normaliser 1/count (valid slots) instead of 1/s
     int slot;            // history slot an OP_CARRY_SLOT product works on
+    int planes;          // sketch planes that an OP_APPLY_* product stores (MatDev::Yp); 0: none
+    int planes_only;     // ... and not its float result
 };
 
 // Grouped-launch work item: which matrix and which tile / part of it a workgroup takes.
@@ -285,12 +289,13 @@ hipError_t launch_project_bf16(const MatDev* mats, const MatDyn* dyn, const Tile
 hipError_t launch_update_bf16(const MatDev* mats, const MatDyn* dyn, const TileRef* tiles, int n_tiles,
                               StepScalars sc, const void* zero16, int sides, hipStream_t stream);
 
-// Refresh products of a bf16 gradient with an fp32 sketch matrix Y as three bf16 MFMA products (left side).
-// form 1: Ya = G Y, form 2: Yb = G^T Y, form 3: Bm = Y^T G; ysrc: Y is 0 Ya, 1 Yb, 2 Yc;
-// planes: how many of Y's three bf16 planes enter (1: form 1 only; 2: forms 1 and 2; 3: any form);
-// max_m / max_n: largest row / column count of the result over the layer set
-hipError_t launch_refresh_x3(int form, int ysrc, int planes, const MatDev* mats, const MatDyn* dyn, int n_mats,
-                             int max_m, int max_n, hipStream_t stream);
+// Refresh products of a bf16 gradient with an fp32 sketch matrix Y, held as bf16 planes (MatDev::Yp), on the bf16 MFMA;
+// left side, at least 8 columns.  form 1: Ya = G Y, form 2: Yb = G^T Y, form 3: Bm = Y^T G; planes: how many of Y's three
+// planes enter (form 1: 1 to 3, form 2: 2 or 3, form 3: 3).  tiles: ti counts kSketchTileG rows or columns of the
+// gradient, tj kSketchTileL sketch columns.
+constexpr int kSketchTileG = 128, kSketchTileL = 128;
+hipError_t launch_sketch_product(int form, int planes, const MatDev* mats, const MatDyn* dyn, const TileRef* tiles,
+                                 int n_tiles, const void* zero16, hipStream_t stream);
 
 // Projection and update of fp32 layer sets with ranks <= kSkinnyMaxRank, left side (k_skinny.hip).
 // tiles: one entry per kSkinnyRows x kSkinnyCols block of the m x ldn range of every matrix; rk: 4, 8
@@ -333,8 +338,9 @@ __host__ __device__ inline int ritz_place(const double* v, int n, int i) {
 }
 
 // refresh helpers (k_refresh.hip)
-hipError_t launch_fill_gaussian(const MatDev* mats, int n_mats, int max_rows, unsigned long long seed,
-                                unsigned long long call_id, hipStream_t stream);   // fills Yb (n x l)
+// fills Yb (n x l), or the first sketch plane with the same values rounded to bf16
+hipError_t launch_fill_gaussian(const MatDev* mats, int n_mats, int max_rows, bool plane, unsigned long long seed,
+                                unsigned long long call_id, hipStream_t stream);
 // Linv = inverse Cholesky factor of the symmetric product `op` (its planes, plus shift_rel * trace on the
 // diagonal)
 hipError_t launch_inverse_factor(GemmOp op, const MatDev* mats, const SymPlanes* sym, int n_mats, int max_order,

@@ -1411,21 +1411,28 @@ __device__ __forceinline__ int jacobi_visit(float* __restrict__ X, int lp, int b
 // in each block: the pairs inside a block would otherwise be rotated again in each of its nb - 1 visits
 // of the sweep.
 template <int NW>
-__global__ __launch_bounds__(64 * NW, 3) void k_jacobi_round(const MatDev* __restrict__ mats, int sweep, int round) {
+__global__ __launch_bounds__(64 * NW, 3) void k_jacobi_round(const MatDev* __restrict__ mats, int n_mats, int pairs, bool local,
+                                                             int sweep, int round) {
     __shared__ __attribute__((aligned(16))) double smem[jacobi_visit_lds<NW>()];
-    const MatDev& md = mats[blockIdx.y];
+    const int seq = (int)(local ? blockIdx.x >> 3 : blockIdx.x);
+    const int mat = local ? seq / pairs * 8 + (int)(blockIdx.x & 7) : seq / pairs, pair = seq % pairs;
+    if (mat >= n_mats) return;
+    const MatDev& md = mats[mat];
     const int lp = md.lp;
     const int nb = lp / 16;
-    if ((int)blockIdx.x >= nb / 2 || round >= nb - 1) return;
+    if (pair >= nb / 2 || round >= nb - 1) return;
     if (sweep > 0 && md.jflag[sweep - 1] == 0) return;
     int bp, bq;
-    tournament_pair(nb, round, blockIdx.x, &bp, &bq);
+    tournament_pair(nb, round, pair, &bp, &bq);
     const bool cross = round != 0;
     // a block of padding rows only has nothing to rotate (in round 0 its partner still has its own pairs)
     if (cross ? (bp * 16 >= md.l || bq * 16 >= md.l) : (bp * 16 >= md.l && bq * 16 >= md.l)) return;
-    // the small sweeps of the workgroups that share a CU (ids about 256 apart, wavefronts dealt to the four
-    // SIMDs in turn) go to different SIMDs
-    const int sweeper = (int)((blockIdx.x + blockIdx.y * gridDim.x) / (NW == 4 ? 256 : 512) % NW);
+    // Which wavefront runs the small sweep: those of the workgroups that share a CU (ids 256 apart) are to be on
+    // different SIMDs, because one alone fills its SIMD's issue (two on one take twice as long).  For two wavefronts per
+    // visit and up to six visits per CU the choice was measured: second wavefront in the third turn only: 2.4 % off
+    // the refresh of the 350M set against the third and fourth; first, third and fourth 1.5 %, third to fifth 1.3 %.
+    const int turn = (int)(blockIdx.x / 256);
+    const int sweeper = NW == 2 ? turn % 6 == 2 : turn % NW;
     const int nrot = jacobi_visit<NW>(jacobi_rows(md), lp, bp, bq, cross, sweeper, smem);
     if (nrot) atomicAdd(&md.jflag[sweep], nrot);
 }
@@ -1471,14 +1478,18 @@ hipError_t launch_jacobi(const MatDev* mats, int n_mats, int max_pairs, int swee
         // launched sweep would cost every refresh 15 empty launches of 2 us.
         done = max_pairs > 32 ? sweeps : max_pairs > 8 ? 14 : 8;
         if (done > sweeps) done = sweeps;
-        const dim3 g(max_pairs, n_mats);
+        // Workgroup ids go round-robin over the 8 XCDs.  All visits of a matrix on one XCD find its rows in that L2 (rows
+        // change blocks every round); where that would load the XCDs unevenly beyond one visit per CU, they are spread.
+        const int turns = (n_mats + 7) / 8;
+        const bool local = turns * max_pairs <= 32 || turns * 8 <= n_mats + n_mats / 4;
+        const dim3 g(max_pairs * (local ? 8 * turns : n_mats));
         // Four wavefronts per visit where the visits leave CUs to spare (the products of a visit in half the
         // time), two otherwise (twice the visits per CU).
         const bool few = (long long)max_pairs * n_mats <= 512;
         for (int sw = 0; sw < done; ++sw)
             for (int round = 0; round < 2 * max_pairs - 1; ++round) {
-                if (few) hipLaunchKernelGGL(k_jacobi_round<4>, g, dim3(256), 0, stream, mats, sw, round);
-                else hipLaunchKernelGGL(k_jacobi_round<2>, g, dim3(128), 0, stream, mats, sw, round);
+                if (few) hipLaunchKernelGGL(k_jacobi_round<4>, g, dim3(256), 0, stream, mats, n_mats, max_pairs, local, sw, round);
+                else hipLaunchKernelGGL(k_jacobi_round<2>, g, dim3(128), 0, stream, mats, n_mats, max_pairs, local, sw, round);
             }
     }
     if (done < sweeps) hipLaunchKernelGGL(k_jacobi_sweeps, dim3(n_mats), dim3(256), 0, stream, mats, done, sweeps);

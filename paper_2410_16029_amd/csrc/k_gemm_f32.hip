@@ -602,11 +602,13 @@ __global__ __launch_bounds__(256, TS == 128 ? 2 : 4) void k_gemm_f32_sides(int o
         gemm_f32_tile<TS, AL, BL, false, false, false>(op, mats, dyn, NG_F32, sc, nullptr, lds);
 }
 
-// max_m, max_n, max_k: the largest dimensions of this product over the layer set.  The 128 tile is used
-// when neither side nor the contraction is short (a short side wastes most of a big tile, a short
-// contraction leaves only the read-modify-write of the output, which wants many small workgroups) and
-// its tiles, counted as if every matrix were as large as the largest, are 512 or more.  (Sets of unequal matrices have
-// fewer: the 60M set's products Y L^-T are counted as 616 and are 280 or 336, one to two per CU.)
+// max_m, max_n, max_k: the largest dimensions of this product over the layer set; tiles: its 128 x 128 tiles.  The large
+// tile, half of the operand bytes per product, is used from 1536 tiles (three per workgroup slot) on for runs of the
+// contraction of 256, from 512 on for runs of 768: the small one, a quarter of the work per workgroup, hides more of each
+// one's first loads and of its epilogue.  Small against large tiles: fp32 step of 56 matrices of the 60M set at rank 128 (1568 tiles) 353 -> 297 us, 14
+// of them 122 -> 103; refresh of that set 1790 -> 1700; of 84 768-wide matrices (1248 tiles, runs of 256) 7259 -> 7149; but
+// 14 and 28 matrices of the 350M set in fp32 (1568 and 3136 tiles, runs of 256) 404 -> 406 and 700 -> 714, refresh of
+// that set in bf16 12.49 -> 12.75 ms, projection of the 28 in fp32 (672 tiles, runs of 1024 and more): step 689 -> 712.
 template <int TS>
 static void run_gemm_f32(dim3 g, int op, const MatDev* mats, const MatDyn* dyn, int grad_dtype, StepScalars sc,
                          bool ai, bool bj, bool abf, bool bbf, bool sym,
@@ -651,8 +653,8 @@ static bool run_gemm_f32_sides(dim3 g, int op, const MatDev* mats, const MatDyn*
 // weight read their operands along other dimensions on the right side: one kernel with both forms for fp32 sets that
 // have both sides, else one launch per side that is present.
 hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int n_mats, int max_m, int max_n,
-                           int max_k, int grad_dtype, StepScalars sc, int max_split, const SymPlanes* sym,
-                           int sides, hipStream_t stream) {
+                           int max_k, long long tiles, int grad_dtype, StepScalars sc, int max_split,
+                           const SymPlanes* sym, int sides, hipStream_t stream) {
     // layouts and types of the operands are properties of the product and the side
     auto view = [&](int side) {
         MatDev probe{};
@@ -667,7 +669,8 @@ hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int
         return (left.sym ? ny * (ny + 1) / 2 : nx * ny) * (max_split > 1 ? max_split : 1);
     };
     // (a split projection is a small one: its chunks were counted in 64 x 64 tiles)
-    const bool big = max_m >= 128 && max_n >= 128 && max_k >= 64 && count(128) * n_mats >= 512 &&
+    const int run = max_k / (max_split > 1 ? max_split : 1);
+    const bool big = max_m >= 128 && max_n >= 128 && run >= 256 && tiles >= 512 && tiles * run >= 1536 * 256 &&
                      !(op == OP_PROJECT_F32 && max_split > 0);
     const dim3 g((unsigned)((count(big ? 128 : 64) + 7) / 8 * 8), 1, n_mats);
     if (by_side && sides == 3 && grad_dtype == NG_F32 &&

@@ -378,6 +378,7 @@ struct ng_state {
     int max_m, max_n, max_r, max_l, max_lp, max_rows, max_ldn;
     int max_ti[OP_COUNT], max_tj[OP_COUNT], max_tk[OP_COUNT];   // largest M, N, K of each fp32 product
     int max_cut[OP_COUNT];                                      // most pieces its contraction is cut into
+    long long tiles[OP_COUNT];                                  // its 128 x 128 tiles
     int max_jpairs;
     int sides;       // bit 0: left-side matrices present, bit 1: right-side ones
     // profiling
@@ -474,7 +475,7 @@ const SymPlanes* planes_of(const ng_state* st, GemmOp op) {
 }
 
 int gemm(ng_state* st, GemmOp op, hipStream_t stream, const StepScalars& sc, const MatDyn* dyn) {
-    NG_HIP(launch_gemm_f32(op, st->d_mats, dyn ? dyn : st->d_dyn, st->n_mats, st->max_ti[op], st->max_tj[op], st->max_tk[op],
+    NG_HIP(launch_gemm_f32(op, st->d_mats, dyn ? dyn : st->d_dyn, st->n_mats, st->max_ti[op], st->max_tj[op], st->max_tk[op], st->tiles[op],
                            st->hp.grad_dtype, sc, st->max_cut[op], planes_of(st, op), st->sides, stream));
     return NG_OK;
 }
@@ -727,7 +728,10 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
         st->max_m = st->max_n = st->max_r = st->max_l = st->max_lp = st->max_rows = st->max_ldn = 0;
         st->max_jpairs = 0;
         st->sides = 0;
-        for (int op = 0; op < OP_COUNT; ++op) st->max_ti[op] = st->max_tj[op] = st->max_tk[op] = 1;
+        for (int op = 0; op < OP_COUNT; ++op) {
+            st->max_ti[op] = st->max_tj[op] = st->max_tk[op] = 1;
+            st->tiles[op] = 0;
+        }
         for (int i = 0; i < n_mats; ++i) {
             const Sizes& z = pl.sz[i];
             MatDev& md = st->mats[i];
@@ -802,6 +806,7 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
                 if (M > st->max_ti[op]) st->max_ti[op] = M;
                 if (N > st->max_tj[op]) st->max_tj[op] = N;
                 if (K > st->max_tk[op]) st->max_tk[op] = K;
+                if (sym_index(op) < 0) st->tiles[op] += (long long)ceil_div(M, 128) * ceil_div(N, 128);
             }
         }
         st->n_dots = (int)dots.size();
@@ -824,6 +829,8 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
             for (int i = 0; i < n_mats; ++i) {
                 const SymPlanes sp = sym_planes(op, st->mats[i], chunk < least ? least : chunk);
                 sym[(size_t)n_mats * sym_index(op) + i] = sp;
+                const long long nt = ceil_div(sp.order, 128);
+                st->tiles[op] += nt * (nt + 1) / 2 * sp.count;
                 if (sp.count > st->max_cut[op]) st->max_cut[op] = sp.count;
             }
         }

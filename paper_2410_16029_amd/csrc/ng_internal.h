@@ -267,11 +267,12 @@ inline int sym_index(int op) {      // -1: not a symmetric product
     return op >= OP_GRAM_A && op <= OP_GRAM_CB ? op - OP_GRAM_A : op == OP_B_BT ? 4 : op == OP_GRAM_P ? 5 : -1;
 }
 
-// max_m, max_n, max_k: largest dimensions of the product over the layer set (grid and tile choice)
+// max_m, max_n, max_k: largest dimensions of the product over the layer set, tiles: its 128 x 128 tiles, each piece of a cut
+// contraction counted (grid and tile choice)
 // max_split: largest number of pieces that a matrix's contraction is cut into, 0 or 1 for none (symmetric products:
 // SymPlanes::count, the projection: MatDev::proj_chunks); sym: symmetric products only
 hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int n_mats,
-                           int max_m, int max_n, int max_k, int grad_dtype, StepScalars sc,
+                           int max_m, int max_n, int max_k, long long tiles, int grad_dtype, StepScalars sc,
                            int max_split, const SymPlanes* sym, int sides, hipStream_t stream);
 
 // bf16 MFMA GEMMs of the step (k_gemm_bf16.hip)

@@ -6,10 +6,11 @@
 
 namespace ng {
 
-// lane K of the lane's own row of 16, in every lane of that row
+// lane K of the lane's own row of 16, in every lane of that row.  (Every lane has a source, so the old value does not
+// matter; naming v as it cost a copy and two wait states per broadcast.)
 template <int K>
 __device__ __forceinline__ double row_bcast(double v) {
-    return __builtin_amdgcn_update_dpp(v, v, 0x150 | K, 0xf, 0xf, false);
+    return __builtin_amdgcn_update_dpp(0.0, v, 0x150 | K, 0xf, 0xf, true);
 }
 
 // Step K of the elimination of a 16 x 16 block: a holds column lane % 16 of it (in every row of 16 lanes), v

@@ -33,11 +33,65 @@ __device__ __forceinline__ unsigned int pack_bf16x2(float a, float b) {
 }
 __device__ __forceinline__ unsigned short f32_to_bf16_rne(float x) { return (unsigned short)(pack_bf16x2(x, 0.f) & 0xffffu); }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    return v;
+// The value of the lane's partner at level L: lane ^ 32, lane ^ 16 (by exchanging halves of rows, see wave_sums), lane ^ 8,
+// and inside a group of eight the mirrored lane, inside four the mirrored one, inside two the other one.
+template <int L>
+__device__ __forceinline__ double partner_dpp(double v) {
+    constexpr int kCtrl = L == 2 ? 0x128 : L == 3 ? 0x141 : L == 4 ? 0x1B : 0xB1;   // row_ror:8, half mirror, quad_perm
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), kCtrl, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), kCtrl, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
 }
+// a keeps its own lower half of the wavefront (L 0) or of every pair of rows (L 1) and gets b's lower half in the upper
+// one's place, b the reverse: afterwards a + b is the first value's sum in the lower lanes, the second's in the upper ones
+template <int L>
+__device__ __forceinline__ double swap_add(double a, double b) {
+    u32x2_t lo, hi;
+    if (L == 0) {
+        lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+        hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    } else {
+        lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+        hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    }
+    return __hiloint2double((int)hi.x, (int)lo.x) + __hiloint2double((int)hi.y, (int)lo.y);
+}
+// Sums of N = 2^q values over the 64 lanes.  Each level adds the partner lanes and, while there is more than one value,
+// leaves either lane of a pair half of the values: N - 1 + (6 - q) exchanges instead of 6 N, none of them through LDS.  On
+// return v[0] is the sum of value wave_sums_slot(N, lane).  (Six LDS exchanges per value were the larger part of what
+// the Gram row of a small slot did besides its loads: 60M set 33.4 -> 29.4 us, three mid-size fp32 matrices 10.8 -> 8.7,
+// 350M set 608 -> 602.)
+template <int N, int L>
+__device__ __forceinline__ void wave_sums(double* v, int lane) {
+    if constexpr (L < 6) {
+        if constexpr (N > 1) {
+            constexpr int H = N / 2;
+            const bool upper = (lane >> (5 - L)) & 1;
+#pragma unroll
+            for (int j = 0; j < H; ++j) {
+                if constexpr (L < 2) {
+                    v[j] = swap_add<L>(v[j], v[j + H]);
+                } else {
+                    const double give = upper ? v[j] : v[j + H], keep = upper ? v[j + H] : v[j];
+                    v[j] = keep + partner_dpp<L>(give);
+                }
+            }
+            wave_sums<H, L + 1>(v, lane);
+        } else {
+            if constexpr (L < 2) v[0] = swap_add<L>(v[0], v[0]);
+            else v[0] += partner_dpp<L>(v[0]);
+            wave_sums<1, L + 1>(v, lane);
+        }
+    }
+}
+template <int N>
+__device__ __forceinline__ int wave_sums_slot(int lane) {
+    int slot = 0;
+#pragma unroll
+    for (int h = N / 2, b = 5; h > 0; h >>= 1, --b) slot += ((lane >> b) & 1) ? h : 0;
+    return slot;
+}
+constexpr int pow2_from(int n) { return n <= 1 ? 1 : 2 * pow2_from((n + 1) / 2); }
 
 // ------------------------------------------------------------------ per-step table upload
 __global__ void k_upload_dyn(MatDyn* table, DynChunk chunk, int first, int n, const MatDev* mats) {
@@ -249,13 +303,14 @@ __global__ __launch_bounds__(256) void k_gram_row(const MatDev* __restrict__ mat
         }
     }
 
-    __shared__ double red[4][SMAX];
+    constexpr int NS = pow2_from(SMAX);
+    __shared__ double red[4][NS];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double sums[NS];
 #pragma unroll
-    for (int j = 0; j < SMAX; ++j) {
-        double v = wave_sum(acc[j]);
-        if (lane == 0) red[wv][j] = v;
-    }
+    for (int j = 0; j < NS; ++j) sums[j] = j < SMAX ? acc[j < SMAX ? j : 0] : 0.0;
+    wave_sums<NS, 0>(sums, lane);
+    if ((lane & (64 / NS - 1)) == 0) red[wv][wave_sums_slot<NS>(lane)] = sums[0];
     __syncthreads();
     if ((int)threadIdx.x < s) {
         double v = ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];

@@ -15,10 +15,10 @@ __device__ __forceinline__ double row_bcast(double v) {
 
 // Step K of the elimination of a 16 x 16 block: a holds column lane % 16 of it (in every row of 16 lanes), v
 // the columns of a right-hand side.  Row K becomes the row of the factor, scaled by 1 / sqrt(pivot).  A pivot
-// below `least` counts as that.
-template <int K>
+// below `least` counts as that.  Rows and columns from END on are those of an identity and stay as they are.
+template <int K, int END = 16>
 __device__ __forceinline__ void eliminate16(double (&a)[16], double (&v)[16], double least, bool& bad) {
-    if constexpr (K < 16) {
+    if constexpr (K < END) {
         double d = row_bcast<K>(a[K]);
         d = d < least ? least : d;
         const bool ok = (d > 0.0) && (d < 1.0e300);
@@ -31,12 +31,12 @@ __device__ __forceinline__ void eliminate16(double (&a)[16], double (&v)[16], do
         a[K] *= rs;
         const double wv = -rs * v[K], wa = -rs * a[K];
 #pragma unroll
-        for (int i = K + 1; i < 16; ++i) {
+        for (int i = K + 1; i < END; ++i) {
             const double m = row_bcast<K>(a[i]);
             v[i] = fma(m, wv, v[i]);
             a[i] = fma(m, wa, a[i]);
         }
-        eliminate16<K + 1>(a, v, least, bad);
+        eliminate16<K + 1, END>(a, v, least, bad);
     }
 }
 

@@ -352,7 +352,8 @@ hipError_t launch_gram_row(const MatDev* mats, const MatDyn* dyn, const TileRef*
 // 16 loads in flight each, and up to s = 16 the system is solved in one wavefront's registers: X = L^{-1} by
 // the elimination of a 16 x 16 block, lane c holding column c, and w = X^T (X e_head).  (With one
 // wavefront, eight loads in flight and the factor in LDS, three barriers a column: 30 us for 168
-// matrices at s = 16, 11 us for 56 at s = 8; now 9 and 7.)
+// matrices at s = 16, 11 us for 56 at s = 8; now 9 and 5.8.)  Systems of up to 4 and 8 stop after as many of the elimination's
+// dependent steps (72 matrices at s = 4 5.5 -> 4.8 us, one 5.6 -> 4.3).
 constexpr int kSolveSub = 16;      // threads that share the sum of one slot's partials
 __global__ __launch_bounds__(256) void k_solve(const MatDev* __restrict__ mats, const MatDyn* __restrict__ dyn,
                                                int first, StepScalars sc, int row_override, int* status) {
@@ -416,7 +417,9 @@ __global__ __launch_bounds__(256) void k_solve(const MatDev* __restrict__ mats, 
             a[k] = k < s && c < s ? A[k < s ? k : 0][c < s ? c : 0] * inv_s + (k == c ? lam : 0.0) : (k == c ? 1.0 : 0.0);
             v[k] = k == c ? 1.0 : 0.0;
         }
-        eliminate16<0>(a, v, 0.0, bad);
+        if (s <= 4) eliminate16<0, 4>(a, v, 0.0, bad);
+        else if (s <= 8) eliminate16<0, 8>(a, v, 0.0, bad);
+        else eliminate16<0>(a, v, 0.0, bad);
         // v: column c of X = L^{-1}; column `head` goes to all lanes through LDS (one wavefront: in order)
         if (c == head) {
 #pragma unroll

@@ -1,7 +1,7 @@
 // Small dense linear algebra of the projector refresh (paper Sec. 1: P = leading
 // left singular vectors of the gradient, recomputed every ~200 steps).  The
-// large products run on the grouped fp32 MFMA GEMM (or, for bf16 gradients, on the
-// split-sketch bf16 MFMA kernel); this file holds what sits between them, one launch for all matrices of the layer set:
+// large products run on the grouped fp32 GEMM (those with a bf16 gradient on
+// k_sketch_product); this file holds what sits between them, one launch for all matrices of the layer set:
 //
 //   k_fill_gaussian     random sketch Omega (counter-based generator, Box-Muller)
 //   k_inverse_factor    Linv = L^{-1} as float, where S = L L^T is a symmetric product (the GEMM then

@@ -2,7 +2,7 @@
 // side): the fine-tuning regime of the paper's Sec. 3.2 (ranks 4 and 8).  With so few rows of R the
 // two contractions are pure streams over the gradient and the weight (2r flop per element), so they
 // run on the vector ALU with the gradient / weight read exactly once, coalesced, and nothing padded
-// up to a tile (the fp32 MFMA GEMM spends a 64-row tile on them).  bf16 layer sets keep the bf16 MFMA
+// up to a tile (the tiled fp32 GEMM spends a 64-row tile on them).  bf16 layer sets keep the bf16 MFMA
 // kernels, which are bandwidth-bound at these ranks already.
 //
 //   k_project_skinny   partial R over a chunk of rows:  part[c][rho][j] = sum_{i in chunk c} P[i][rho] G[i][j]

@@ -281,7 +281,7 @@ void make_plan(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* 
     size_t off = 0;
     p->off_status = off; off += 256;
     p->off_mats = off;   off += align_up(sizeof(MatDev) * (size_t)n_mats, 256);
-    // The fp32 MFMA projection of a small layer set is cut along its contraction, the gradient's rows: three
+    // The tiled fp32 projection of a small layer set is cut along its contraction, the gradient's rows: three
     // mid-size matrices are 80 tiles of 64 x 64 with a chain of 100 k-steps each, most of the chip idle.
     // Cut until there are about 1024 tiles (four per CU), in runs of at least 64 rows and at most 16 of
     // them, and not at all where the tiles are 512 or more already.  The partial planes are then at

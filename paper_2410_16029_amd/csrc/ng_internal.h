@@ -194,7 +194,7 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t stream);   // b
 hipError_t launch_clear_history(const MatDev* mats, int n_mats, int s, int h_elem_bytes, size_t k_bytes,
                                 hipStream_t stream);
 
-// fp32 MFMA grouped GEMM with selectable operands (k_gemm_f32.hip)
+// fp32 grouped GEMM with selectable operands (k_gemm_f32.hip)
 enum GemmOp {
     OP_PROJECT_F32 = 0,   // R(slot head) = P^T G                     (step, NG_F32)
     OP_UPDATE_F32,        // W -= lr*(scale * P N + wd W)             (step, NG_F32)

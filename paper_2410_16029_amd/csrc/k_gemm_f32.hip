@@ -195,7 +195,7 @@ __device__ __forceinline__ f32x4_t load4(const NG_AS1 unsigned char* p) {
 
 // Every operand value x goes into LDS as three bf16 planes, x = x0 + x1 + x2 (each the rounding of what the ones before
 // leave: 24 bits, the float itself), and a product of two operands is six bf16 MFMA products,
-//   a b = a0 b0 + (a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0),      dropped: a1 b2, a2 b1, a2 b2, below 2^-25 |a b|.
+//   a b = a0 b0 + (a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0),      dropped: a1 b2, a2 b1, a2 b2, together at most 2^-24 (1 + 2^-10) |a b|.
 // a0 b0 has an accumulator of its own, which is rounded once per 16 contraction steps (the fp32 MFMA rounds every
 // two), and the other five share one that is some 2^-8 as large: the sums are closer to 64 bits than the fp32
 // MFMA's, at three eighths of its matrix-core time.
@@ -204,10 +204,6 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-
-// Beyond this a value may round to an infinity in bf16, and an infinity times a lower plane is NaN: tiles that
-// meet one are computed again in plain fp32 (see gemm_f32_tile).
-constexpr float kSplitMax = 3.38e38f;
 
 // the NP planes of two values, a in the low halves
 template <int NP>
@@ -293,14 +289,8 @@ struct F32Src {
             }
         }
     }
-    // the planes -> S (PLANE elements each); big: the largest magnitude met
-    __device__ __forceinline__ void stage(const f32x4_t (&r)[NV], bf16_t* S, int t, float& big) const {
-        if (!BF) {
-#pragma unroll
-            for (int q = 0; q < NV; ++q)
-#pragma unroll
-                for (int x = 0; x < 4; x += 2) big = fmaxf(fmaxf(big, fabsf(r[q][x])), fabsf(r[q][x + 1]));
-        }
+    // the planes -> S (PLANE elements each)
+    __device__ __forceinline__ void stage(const f32x4_t (&r)[NV], bf16_t* S, int t) const {
 #pragma unroll
         for (int y = 0; y < (TF ? 4 : NV); ++y) {
             bf16_t* dst = S + (TF ? 4 * (t / KG) + y : t / KT + TQ * y) * LDK + k0;
@@ -334,6 +324,41 @@ struct F32Tiles {
 // A barrier that waits for this wave's LDS accesses only: __syncthreads() would also wait for the operand loads in
 // flight, i.e. expose a memory latency in every k-step.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// A wavefront's blocks once more, on the fp32 MFMA and straight from memory: the planes cannot stand for an infinity (nor
+// for a value that rounds to one in bf16), whose lower planes are NaN and whose products with the other operand's lower
+// planes are infinities of either sign, nor for a product that overflows before its smaller parts are taken off.  Each
+// shows as a result that is not finite, so such results are formed again; i, j: this lane's first row and column.
+template <int NB, bool ABF, bool BBF>
+__device__ __forceinline__ void fp32_again(floatx16 (&acc)[NB][NB], const GemmView& v, int i, int j, int h) {
+    const NG_AS1 unsigned char *pa[NB], *pb[NB];
+#pragma unroll
+    for (int x = 0; x < NB; ++x) {
+        // (rows and columns past the product's edge re-read its last ones: their results are not stored, or zeroed)
+        const int row = i + 32 * x < v.M ? i + 32 * x : v.M - 1, col = j + 32 * x < v.Nvalid ? j + 32 * x : v.Nvalid - 1;
+        pa[x] = (const NG_AS1 unsigned char*)v.A + row * v.sAi * (ABF ? 2 : 4);
+        pb[x] = (const NG_AS1 unsigned char*)v.B + col * v.sBj * (BBF ? 2 : 4);
+#pragma unroll
+        for (int y = 0; y < NB; ++y)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
+    }
+#pragma unroll 4
+    for (int k0 = 0; k0 < v.K; k0 += 2) {
+        const bool in = k0 + h < v.K;
+        const int k = in ? k0 + h : v.K - 1;
+        float a[NB], b[NB];
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+            a[x] = in ? load1<ABF>(pa[x], k * v.sAk) : 0.f;
+            b[x] = in ? load1<BBF>(pb[x], k * v.sBk) : 0.f;
+        }
+#pragma unroll
+        for (int x = 0; x < NB; ++x)
+#pragma unroll
+            for (int y = 0; y < NB; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x], b[y], acc[x][y], 0, 0, 0);
+    }
+}
 
 template <int TS, bool AI, bool BJ, bool ABF, bool BBF, bool SYM>
 __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__ mats, const MatDyn* __restrict__ dyn,
@@ -449,10 +474,9 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
     // (uniform) tiles with vectors that straddle the last tile index
     const bool back_a = AI && (v.M & 3) != 0 && i0 + TS > v.M, back_b = BJ && (v.Nvalid & 3) != 0 && j0 + TS > v.Nvalid;
     f32x4_t ra[NV], rb[NV];
-    float big = 0.f;
     auto stage = [&]() {
-        sa.stage(ra, lds.a, t, big);
-        sb.stage(rb, lds.b, t, big);
+        sa.stage(ra, lds.a, t);
+        sb.stage(rb, lds.b, t);
     };
     if (nw > 0) {
         sa.fetch(0, ra);
@@ -477,33 +501,17 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
         multiply();
         lds_barrier();
     }
+    bool finite = true;
 #pragma unroll
     for (int x = 0; x < NB; ++x)
 #pragma unroll
         for (int y = 0; y < NB; ++y)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[x][y][e] += low[x][y][e];
-    // infinities (and what would round to one): the tile again in plain fp32, element by element
-    if (__syncthreads_or(big > kSplitMax)) {
-#pragma unroll 1
-        for (int k = 0; k < v.K; ++k) {
-            float b[NB];
-#pragma unroll
-            for (int y = 0; y < NB; ++y) {
-                const int j = j0 + wn * (TS / 2) + 32 * y + li;
-                b[y] = j < v.Nvalid ? load1<BBF>((const NG_AS1 unsigned char*)v.B, k * v.sBk + j * v.sBj) : 0.f;
+            for (int e = 0; e < 16; ++e) {
+                acc[x][y][e] += low[x][y][e];
+                finite = finite && fabsf(acc[x][y][e]) <= 3.402823466e38f;
             }
-#pragma unroll
-            for (int x = 0; x < NB; ++x)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int i = i0 + wm * (TS / 2) + 32 * x + 8 * (e >> 2) + 4 * h + (e & 3);
-                    const float a = i < v.M ? load1<ABF>((const NG_AS1 unsigned char*)v.A, i * v.sAi + k * v.sAk) : 0.f;
-#pragma unroll
-                    for (int y = 0; y < NB; ++y) acc[x][y][e] = k == 0 ? a * b[y] : fmaf(a, b[y], acc[x][y][e]);
-                }
-        }
-    }
+    if (__any(!finite)) fp32_again<NB, ABF, BBF>(acc, v, i0 + wm * (TS / 2) + li, j0 + wn * (TS / 2) + li, h);
 
     // columns from Nvalid on (the padding of a state's rows) are zero
     if (j0 + TS > v.Nvalid) {

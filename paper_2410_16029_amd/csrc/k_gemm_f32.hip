@@ -193,8 +193,9 @@ __device__ __forceinline__ f32x4_t load4(const NG_AS1 unsigned char* p) {
     return *reinterpret_cast<const NG_AS1 f32x4_a4*>(p);
 }
 
-// Every operand value x goes into LDS as three bf16 planes, x = x0 + x1 + x2 (each the rounding of what the ones before
-// leave: 24 bits, the float itself), and a product of two operands is six bf16 MFMA products,
+// Every operand value x goes into LDS as three bf16 planes, 2^16 x = x0 + x1 + x2 (each the rounding of what the ones before
+// leave: 24 bits, the float itself; every float is a multiple of 2^-149, bf16's subnormals of 2^-133, hence the factor: without
+// it operands below 2^-110 lost bits, 2.7e-6 of a product at 1e-35), and a product of two operands is six bf16 MFMA products,
 //   a b = a0 b0 + (a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0),      dropped: a1 b2, a2 b1, a2 b2, together at most 2^-24 (1 + 2^-10) |a b|.
 // a0 b0 has an accumulator of its own, which is rounded once per 16 contraction steps (the fp32 MFMA rounds every
 // two), and the other five share one that is some 2^-8 as large: the sums are closer to 64 bits than the fp32
@@ -206,6 +207,7 @@ typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
 // the NP planes of two values, a in the low halves
+constexpr float kSplitUp = 65536.f;
 template <int NP>
 __device__ __forceinline__ void split2(float a, float b, unsigned (&p)[NP]) {
 #pragma unroll
@@ -296,9 +298,10 @@ struct F32Src {
             bf16_t* dst = S + (TF ? 4 * (t / KG) + y : t / KT + TQ * y) * LDK + k0;
             constexpr int PAIRS = TF ? NV / 2 : 2;
             unsigned p[PAIRS][NP];
+            constexpr float up = BF ? 1.f : kSplitUp;
 #pragma unroll
             for (int c = 0; c < PAIRS; ++c)
-                split2<NP>(TF ? r[2 * c][y] : r[y % NV][2 * c], TF ? r[2 * c + 1][y] : r[y % NV][2 * c + 1], p[c]);
+                split2<NP>(up * (TF ? r[2 * c][y] : r[y % NV][2 * c]), up * (TF ? r[2 * c + 1][y] : r[y % NV][2 * c + 1]), p[c]);
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
                 if (PAIRS == 2) *reinterpret_cast<uint2*>(dst + i * PLANE) = make_uint2(p[0][i], p[PAIRS - 1][i]);
@@ -325,10 +328,10 @@ struct F32Tiles {
 // flight, i.e. expose a memory latency in every k-step.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// A wavefront's blocks once more, on the fp32 MFMA and straight from memory: the planes cannot stand for an infinity (nor
-// for a value that rounds to one in bf16), whose lower planes are NaN and whose products with the other operand's lower
-// planes are infinities of either sign, nor for a product that overflows before its smaller parts are taken off.  Each
-// shows as a result that is not finite, so such results are formed again; i, j: this lane's first row and column.
+// A wavefront's blocks once more, on the fp32 MFMA and straight from memory: the planes cannot stand for an infinity, whose
+// lower planes are NaN and whose products with the other operand's lower planes are infinities of either sign, nor for
+// values from 2^112 on, nor for sums from 2^96 on (both carry the planes' factor).  Each shows as a result that is not
+// finite, so such results are formed again; i, j: this lane's first row and column.
 template <int NB, bool ABF, bool BBF>
 __device__ __forceinline__ void fp32_again(floatx16 (&acc)[NB][NB], const GemmView& v, int i, int j, int h) {
     const NG_AS1 unsigned char *pa[NB], *pb[NB];
@@ -501,6 +504,7 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
         multiply();
         lds_barrier();
     }
+    constexpr float down = 1.f / ((ABF ? 1.f : kSplitUp) * (BBF ? 1.f : kSplitUp));
     bool finite = true;
 #pragma unroll
     for (int x = 0; x < NB; ++x)
@@ -508,7 +512,7 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
         for (int y = 0; y < NB; ++y)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                acc[x][y][e] += low[x][y][e];
+                acc[x][y][e] = down * (acc[x][y][e] + low[x][y][e]);
                 finite = finite && fabsf(acc[x][y][e]) <= 3.402823466e38f;
             }
     if (__any(!finite)) fp32_again<NB, ABF, BBF>(acc, v, i0 + wm * (TS / 2) + li, j0 + wn * (TS / 2) + li, h);

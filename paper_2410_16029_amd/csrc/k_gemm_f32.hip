@@ -314,11 +314,12 @@ struct F32Src {
 // Tile TS x TS per workgroup (128: four wavefronts of 64 x 64 = 2 x 2 MFMA blocks of 32 x 32; 64: one
 // block per wavefront, for products with a short side, a short contraction or few tiles).
 // AI / BJ: the tile index is operand A's / B's stride-1 dimension (else the contraction is); ABF / BBF:
-// operand A / B is stored as bf16; SYM: a symmetric product (partial planes).  side >= 0: only matrices
-// of that side.  A tile whose rows and columns all exist takes whole vectors without a test (only a
+// operand A / B is stored as bf16; SYM: a symmetric product (partial planes).  only >= 0: matrices of that side,
+// or those without sketch planes.  A tile whose rows and columns all exist takes whole vectors without a test (only a
 // last partial k-step is read element by element); with the tests of every vector, and of every MFMA
 // block against the product's edge, in the loop the products ran at a quarter of the fp32 MFMA rate.
 constexpr int kF32BK = 32;             // contraction steps per LDS tile
+constexpr int kOnlyPlaneless = 2;
 template <int TS>
 struct F32Tiles {
     bf16_t a[3 * TS * (kF32BK + 8)], b[3 * TS * (kF32BK + 8)];   // three planes each, rows padded by 16 bytes
@@ -531,7 +532,7 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
 
     // the sketch planes that a gradient product reads next: octets of rows (a lane's four rows are half an octet), rows past
     // the last zero
-    if (v.b_tri && sc.planes > 0) {
+    if (v.b_tri && sc.planes > 0 && md.Yp != nullptr) {
         const long long plane = md.yp_plane;
 #pragma unroll
         for (int bi = 0; bi < NB; ++bi)
@@ -595,9 +596,9 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
 template <int TS, bool AI, bool BJ, bool ABF, bool BBF, bool SYM>
 __global__ __launch_bounds__(256, TS == 128 ? 2 : 4) void k_gemm_f32(int op, const MatDev* __restrict__ mats,
                                                   const MatDyn* __restrict__ dyn, int grad_dtype,
-                                                  StepScalars sc, const SymPlanes* __restrict__ sym, int side) {
+                                                  StepScalars sc, const SymPlanes* __restrict__ sym, int only) {
     __shared__ __attribute__((aligned(16))) F32Tiles<TS> lds;
-    if (side >= 0 && mats[blockIdx.z].side != side) return;
+    if (only >= 0 && (only == kOnlyPlaneless ? mats[blockIdx.z].Yp != nullptr : mats[blockIdx.z].side != only)) return;
     gemm_f32_tile<TS, AI, BJ, ABF, BBF, SYM>(op, mats, dyn, grad_dtype, sc, sym, lds);
 }
 
@@ -624,10 +625,10 @@ __global__ __launch_bounds__(256, TS == 128 ? 2 : 4) void k_gemm_f32_sides(int o
 template <int TS>
 static void run_gemm_f32(dim3 g, int op, const MatDev* mats, const MatDyn* dyn, int grad_dtype, StepScalars sc,
                          bool ai, bool bj, bool abf, bool bbf, bool sym,
-                         const SymPlanes* planes, int side, hipStream_t stream) {
+                         const SymPlanes* planes, int only, hipStream_t stream) {
 #define NG_GEMM_CASE(AI, BJ, ABF, BBF, SYM)                                                                      \
     if (ai == AI && bj == BJ && abf == ABF && bbf == BBF && sym == SYM) {                                        \
-        k_gemm_f32<TS, AI, BJ, ABF, BBF, SYM><<<g, dim3(256), 0, stream>>>(op, mats, dyn, grad_dtype, sc, planes, side); \
+        k_gemm_f32<TS, AI, BJ, ABF, BBF, SYM><<<g, dim3(256), 0, stream>>>(op, mats, dyn, grad_dtype, sc, planes, only); \
         return;                                                                                                  \
     }
     NG_GEMM_CASE(true, true, false, false, true)      // the Gram matrices of the sketch and of P
@@ -663,10 +664,10 @@ static bool run_gemm_f32_sides(dim3 g, int op, const MatDev* mats, const MatDyn*
 
 // sides: bit 0 = left-side matrices present, bit 1 = right-side ones.  The products with the gradient or the
 // weight read their operands along other dimensions on the right side: one kernel with both forms for fp32 sets that
-// have both sides, else one launch per side that is present.
+// have both sides, else one launch per side that is present.  (Sets with sketch planes have left-side matrices only.)
 hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int n_mats, int max_m, int max_n,
                            int max_k, long long tiles, int grad_dtype, StepScalars sc, int max_split,
-                           const SymPlanes* sym, int sides, hipStream_t stream) {
+                           const SymPlanes* sym, int sides, bool planeless, hipStream_t stream) {
     // layouts and types of the operands are properties of the product and the side
     auto view = [&](int side) {
         MatDev probe{};
@@ -692,7 +693,7 @@ hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int
     for (int side = 0; side < 2; ++side) {
         if (by_side ? !(sides & (1 << side)) : side == 1) continue;
         const GemmView& v = side == NG_SIDE_RIGHT && by_side ? right : left;
-        const int filter = by_side && sides == 3 ? side : -1;
+        const int filter = planeless ? kOnlyPlaneless : by_side && sides == 3 ? side : -1;
         if (big) run_gemm_f32<128>(g, (int)op, mats, dyn, grad_dtype, sc, v.sAi == 1, v.sBj == 1, v.a_bf16, v.b_bf16, v.sym != 0, sym, filter, stream);
         else run_gemm_f32<64>(g, (int)op, mats, dyn, grad_dtype, sc, v.sAi == 1, v.sBj == 1, v.a_bf16, v.b_bf16, v.sym != 0, sym, filter, stream);
     }

@@ -34,17 +34,19 @@ __device__ __forceinline__ float gaussian(unsigned long long key, long long i) {
     return sqrtf(-2.0f * logf(u1)) * cosf(6.28318530717958647692f * u2);
 }
 
-// PLANE: eight rows of one column per thread, rounded to bf16, as the octets that a gradient product reads
-template <bool PLANE>
+// Matrices with sketch planes: eight rows of one column per thread, rounded to bf16, as the octets that a gradient
+// product reads.  PLANES: the set has such matrices.
+template <bool PLANES>
 __global__ __launch_bounds__(256) void k_fill_gaussian(const MatDev* __restrict__ mats, unsigned long long seed,
                                                        unsigned long long call_id) {
     const MatDev& md = mats[blockIdx.y];
     const unsigned long long key =
         mix64(seed ^ (call_id * 0x9E3779B97F4A7C15ULL) ^ ((unsigned long long)(blockIdx.y + 1) * 0xD1B54A32D192ED03ULL));
     const int n = md.n, l = md.l;
-    const long long total = PLANE ? (long long)((n + 7) / 8) * l : (long long)n * l;
+    const bool plane = PLANES && md.Yp != nullptr;
+    const long long total = plane ? (long long)((n + 7) / 8) * l : (long long)n * l;
     for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
-        if (!PLANE) {
+        if (!plane) {
             md.Yb[i] = gaussian(key, i);
             continue;
         }
@@ -58,12 +60,12 @@ __global__ __launch_bounds__(256) void k_fill_gaussian(const MatDev* __restrict_
     }
 }
 
-hipError_t launch_fill_gaussian(const MatDev* mats, int n_mats, int max_rows, bool plane, unsigned long long seed,
+hipError_t launch_fill_gaussian(const MatDev* mats, int n_mats, int max_rows, bool planes, unsigned long long seed,
                                 unsigned long long call_id, hipStream_t stream) {
     int gx = (max_rows + 3) / 4;   // grid-stride loop covers the rest
     if (gx < 1) gx = 1;
     if (gx > 4096) gx = 4096;
-    if (plane) hipLaunchKernelGGL(k_fill_gaussian<true>, dim3((gx + 7) / 8, n_mats), dim3(256), 0, stream, mats, seed, call_id);
+    if (planes) hipLaunchKernelGGL(k_fill_gaussian<true>, dim3((gx + 7) / 8, n_mats), dim3(256), 0, stream, mats, seed, call_id);
     else hipLaunchKernelGGL(k_fill_gaussian<false>, dim3(gx, n_mats), dim3(256), 0, stream, mats, seed, call_id);
     return hipGetLastError();
 }

@@ -177,7 +177,8 @@ void derive(const ng_matrix_desc& user, const ng_hparams& hp, int skinny_rk, Siz
 struct Plan {
     std::vector<Sizes> sz;
     std::vector<TileRef> proj, upd, dots, patches, skinny;
-    bool sketch_planes;                         // the refresh's gradient products read bf16 planes (launch_sketch_product)
+    bool sketch_planes;                         // refresh's gradient products read bf16 planes (launch_sketch_product) ...
+    bool planeless;                             // ... and not those of every matrix
     std::vector<TileRef> sketch[3];             // their tiles, by form - 1
     int skinny_rk;                              // 0: the MFMA / fp32-GEMM projection and update
     long long tiles4;                           // 256 x 256 tiles of the left-side projection
@@ -259,22 +260,26 @@ void make_plan(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* 
     }
     xcd_order(upd, cost_upd, &p->upd);
     // The refresh's products with bf16 gradients: sets on the left side (the right side's gradients are read along their
-    // other dimension) of at least 8 columns (see projection_tile_direct).  Forms 1 and 2 list a matrix's column tiles of one
+    // other dimension), matrices of at least 8 columns (see projection_tile_direct; narrower ones take the fp32 GEMM).  Forms 1 and 2 list a matrix's column tiles of one
     // gradient tile next to each other, form 3 its row tiles: they share the gradient tile in one XCD's L2.
-    p->sketch_planes = hp.grad_dtype == NG_BF16 && all_left;
-    for (int i = 0; i < n_mats; ++i) p->sketch_planes = p->sketch_planes && projection_tile_direct(d[i].n);
+    p->sketch_planes = p->planeless = false;
+    for (int i = 0; i < n_mats; ++i) {
+        const bool planes = hp.grad_dtype == NG_BF16 && all_left && projection_tile_direct(d[i].n);
+        if (!planes) p->sz[i].ws_yp = 0;
+        (planes ? p->sketch_planes : p->planeless) = true;
+    }
     for (int f = 0; f < 3; ++f) p->sketch[f].clear();
-    for (int i = 0; i < n_mats; ++i)
-        if (!p->sketch_planes) p->sz[i].ws_yp = 0;
     for (int f = 0; f < 3 && p->sketch_planes; ++f) {
         std::vector<TileRef> logical;
         std::vector<int> cost;
-        for (int i = 0; i < n_mats; ++i)
+        for (int i = 0; i < n_mats; ++i) {
+            if (p->sz[i].ws_yp == 0) continue;
             for (int ti = 0; ti < ceil_div(f == 0 ? d[i].m : f == 1 ? d[i].n : p->sz[i].ldn, kSketchTileG); ++ti)
                 for (int tj = 0; tj < ceil_div(p->sz[i].l, kSketchTileL); ++tj) {
                     logical.push_back(TileRef{i, ti, tj, 0});
                     cost.push_back(f == 0 ? d[i].n : d[i].m);
                 }
+        }
         xcd_order(logical, cost, &p->sketch[f]);
     }
     // Gram-row parts are appended in make_mats (they need dot_nparts)
@@ -466,6 +471,18 @@ int gradient_product(ng_state* st, GemmOp op, bool last, hipStream_t stream, con
     const int form = op == OP_QT_G ? 3 : op == OP_GT_C2B ? 2 : 1;
     NG_HIP(launch_sketch_product(form, sketch_planes(op, last), st->d_mats, st->d_dyn, st->d_sketch[form - 1],
                                  (int)st->plan.sketch[form - 1].size(), (const char*)st->d_status + 64, stream));
+    if (!st->plan.planeless) return NG_OK;
+    int max_m = 1, max_n = 1, max_k = 1;
+    for (const MatDev& md : st->mats)
+        if (md.Yp == nullptr) {
+            int M, N, K;
+            gemm_f32_dims(op, md, &M, &N, &K);
+            max_m = M > max_m ? M : max_m;
+            max_n = N > max_n ? N : max_n;
+            max_k = K > max_k ? K : max_k;
+        }
+    NG_HIP(launch_gemm_f32(op, st->d_mats, st->d_dyn, st->n_mats, max_m, max_n, max_k, 0, st->hp.grad_dtype, sc, 0, nullptr,
+                           st->sides, true, stream));
     return NG_OK;
 }
 
@@ -476,7 +493,7 @@ const SymPlanes* planes_of(const ng_state* st, GemmOp op) {
 
 int gemm(ng_state* st, GemmOp op, hipStream_t stream, const StepScalars& sc, const MatDyn* dyn) {
     NG_HIP(launch_gemm_f32(op, st->d_mats, dyn ? dyn : st->d_dyn, st->n_mats, st->max_ti[op], st->max_tj[op], st->max_tk[op], st->tiles[op],
-                           st->hp.grad_dtype, sc, st->max_cut[op], planes_of(st, op), st->sides, stream));
+                           st->hp.grad_dtype, sc, st->max_cut[op], planes_of(st, op), st->sides, false, stream));
     return NG_OK;
 }
 

@@ -66,7 +66,7 @@ struct MatDev {
     float* Yb;        // [max(m,n)][l]
     float* Yc;        // [max(m,n)][l]
     bf16_t* Yp;       // three planes [max(m,n) / 8][l][8] of the sketch that a gradient product reads, yp_plane
-    long long yp_plane;   // elements apart (null: the set's gradient products run on the fp32 GEMM)
+    long long yp_plane;   // elements apart (null: the matrix's gradient products run on the fp32 GEMM)
     float* Bm;        // [l][ldn]   B = Q^T G; later the l x r rotation
     double* T;        // [lp][lp]   Gram matrix / Cholesky factor of orders above kFactorMax
     float* Linv;      // [lp][lp]   inverse Cholesky factor (float); during the Rayleigh-Ritz step the rows
@@ -271,9 +271,11 @@ inline int sym_index(int op) {      // -1: not a symmetric product
 // contraction counted (grid and tile choice)
 // max_split: largest number of pieces that a matrix's contraction is cut into, 0 or 1 for none (symmetric products:
 // SymPlanes::count, the projection: MatDev::proj_chunks); sym: symmetric products only
+// planeless: only the matrices without sketch planes (a product with the gradient, the others having gone through
+// launch_sketch_product; the dimensions are then theirs)
 hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int n_mats,
                            int max_m, int max_n, int max_k, long long tiles, int grad_dtype, StepScalars sc,
-                           int max_split, const SymPlanes* sym, int sides, hipStream_t stream);
+                           int max_split, const SymPlanes* sym, int sides, bool planeless, hipStream_t stream);
 
 // bf16 MFMA GEMMs of the step (k_gemm_bf16.hip)
 // which: 0 projection (direct-to-LDS kernel), 1 update, 2 projection (register-staged kernel)
@@ -339,8 +341,8 @@ __host__ __device__ inline int ritz_place(const double* v, int n, int i) {
 }
 
 // refresh helpers (k_refresh.hip)
-// fills Yb (n x l), or the first sketch plane with the same values rounded to bf16
-hipError_t launch_fill_gaussian(const MatDev* mats, int n_mats, int max_rows, bool plane, unsigned long long seed,
+// fills Yb (n x l), or, where a matrix has sketch planes, the first of them with the same values rounded to bf16
+hipError_t launch_fill_gaussian(const MatDev* mats, int n_mats, int max_rows, bool planes, unsigned long long seed,
                                 unsigned long long call_id, hipStream_t stream);
 // Linv = inverse Cholesky factor of the symmetric product `op` (its planes, plus shift_rel * trace on the
 // diagonal)

@@ -1165,14 +1165,17 @@ __global__ __launch_bounds__(C::NT, 2) void k_sketch_product(const MatDev* __res
     else gc.init(dy.g, md.ld_g, m, n, g0, lane, wv,
                  md.tail8_off >= 0 ? (const void*)step_scratch<char>(dyn, md.tail8_off) : zero16, zp);
     Planes pl;
-    pl.init(md.Yp, l, FORM == 1 ? n >> 3 : (m + 7) >> 3, l0, lane, wv);
-    const long long plane = md.yp_plane * 2;                       // bytes from one plane to the next
+    const bf16_t* planes = sketch_plane(md, FORM == 3, 0);
+    pl.init(planes, l, FORM == 1 ? n >> 3 : (m + 7) >> 3, l0, lane, wv);
+    long long plane[NP];                                           // bytes from the first plane
+#pragma unroll
+    for (int p = 0; p < NP; ++p) plane[p] = (sketch_plane(md, FORM == 3, p) - planes) * 2;
     auto issue = [&](int kt) {
         unsigned char* stage = smem + (kt % NST) * C::STAGE;
         if (FORM == 1) gr.issue(kt, stage, zp, wv);
         else gc.issue(kt, stage, zp, wv);
 #pragma unroll
-        for (int p = 0; p < NP; ++p) pl.issue(kt, stage + C::G_BYTES + p * C::P_BYTES, zp, wv, p * plane);
+        for (int p = 0; p < NP; ++p) pl.issue(kt, stage + C::G_BYTES + p * C::P_BYTES, zp, wv, plane[p]);
     };
 
     // fragment addresses inside a stage
@@ -1277,7 +1280,7 @@ __global__ __launch_bounds__(C::NT, 2) void k_sketch_product(const MatDev* __res
             for (int y = 0; y < NL; ++y) {
                 const int col = l0 + wl * C::WL + 32 * y + li;
                 const bool in = h == 0 && col < l;
-                const u32x4_t q = *(const NG_AS1 u32x4_t*)((const NG_AS1 bf16_t*)md.Yp + p * md.yp_plane + ((long long)(k0 >> 3) * l + (col < l ? col : 0)) * 8);
+                const u32x4_t q = *(const NG_AS1 u32x4_t*)((const NG_AS1 bf16_t*)sketch_plane(md, FORM == 3, p) + ((long long)(k0 >> 3) * l + (col < l ? col : 0)) * 8);
                 v.y[p][y] = zero_unless(in, q);
             }
         multiply(v);

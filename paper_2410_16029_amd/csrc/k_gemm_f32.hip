@@ -533,7 +533,9 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
     // the sketch planes that a gradient product reads next: octets of rows (a lane's four rows are half an octet), rows past
     // the last zero
     if (v.b_tri && sc.planes > 0 && md.Yp != nullptr) {
-        const long long plane = md.yp_plane;
+        bf16_t* planes[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) planes[p] = sketch_plane(md, op == OP_APPLY_C2A, p);
 #pragma unroll
         for (int bi = 0; bi < NB; ++bi)
 #pragma unroll
@@ -549,10 +551,10 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
                     split2<3>(x[0], x[1], lo);
                     split2<3>(x[2], x[3], hi);
                     if (oct < v.M && col < v.N) {
-                        NG_AS1 bf16_t* dst = (NG_AS1 bf16_t*)md.Yp + ((long long)(oct >> 3) * md.l + col) * 8 + 4 * h;
+                        const long long at = ((long long)(oct >> 3) * md.l + col) * 8 + 4 * h;
 #pragma unroll
                         for (int p = 0; p < 3; ++p)
-                            if (p < sc.planes) *(NG_AS1 u32x2_t*)(dst + p * plane) = (u32x2_t){lo[p], hi[p]};
+                            if (p < sc.planes) *(NG_AS1 u32x2_t*)((NG_AS1 bf16_t*)planes[p] + at) = (u32x2_t){lo[p], hi[p]};
                     }
                 }
             }

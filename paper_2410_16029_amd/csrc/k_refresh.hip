@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256) void k_fill_gaussian(const MatDev* __restrict_
 #pragma unroll
         for (int e = 0; e < 8; ++e)
             v[e] = (__bf16)(8 * oct + e < n ? gaussian(key, (long long)(8 * oct + e) * l + col) : 0.f);
-        *reinterpret_cast<bf16x8_t*>(md.Yp + 8 * i) = v;
+        *reinterpret_cast<bf16x8_t*>(sketch_plane(md, false, 0) + 8 * i) = v;
     }
 }
 

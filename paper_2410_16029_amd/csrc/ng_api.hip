@@ -63,7 +63,7 @@ struct Sizes {   // per-matrix derived sizes
     size_t k_gram_off, k_w64_off, k_w32_off;
     size_t aux_pb_off, aux_pbt_off;
     // refresh scratch
-    size_t ws_y, ws_yp, ws_bm, ws_t, ws_linv, ws_ritz, ws_order, ws_flag, ws_parts, ws_carry, ws_proj;
+    size_t ws_y, ws_yp, plane, plane_last, ws_bm, ws_t, ws_linv, ws_ritz, ws_order, ws_flag, ws_parts, ws_carry, ws_proj;
     int proj_chunks, proj_rows;   // row chunks of the fp32 projection (0: none)
 };
 
@@ -159,7 +159,6 @@ void derive(const ng_matrix_desc& user, const ng_hparams& hp, int skinny_rk, Siz
     }
     const size_t rows = (size_t)(d.m > d.n ? d.m : d.n);
     z->ws_y = align_up(rows * l * 4, 256);
-    z->ws_yp = align_up((rows + 7) / 8 * 8 * l * 2, 256) * 3;      // (sketch planes; dropped where the set does not use them)
     z->ws_bm = align_up((size_t)l * z->ldn * 4, 256);
     z->ws_t = align_up((size_t)z->lp * z->lp * 8, 256);
     z->ws_linv = align_up((size_t)z->lp * z->lp * 4, 256);
@@ -265,7 +264,14 @@ void make_plan(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* 
     p->sketch_planes = p->planeless = false;
     for (int i = 0; i < n_mats; ++i) {
         const bool planes = hp.grad_dtype == NG_BF16 && all_left && projection_tile_direct(d[i].n);
-        if (!planes) p->sz[i].ws_yp = 0;
+        if (planes) {
+            Sizes& z = p->sz[i];
+            const size_t rows = (size_t)(d[i].m > d[i].n ? d[i].m : d[i].n);
+            z.plane = align_up((rows + 7) / 8 * 8 * z.l * 2, 256);
+            z.plane_last = align_up(((size_t)d[i].m + 7) / 8 * 8 * z.l * 2, 256);
+            if (z.ws_y < 2 * z.plane) z.ws_y = 2 * z.plane;
+            z.ws_yp = z.ws_y < 3 * z.plane_last ? z.plane_last : 0;
+        }
         (planes ? p->sketch_planes : p->planeless) = true;
     }
     for (int f = 0; f < 3; ++f) p->sketch[f].clear();
@@ -273,7 +279,7 @@ void make_plan(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* 
         std::vector<TileRef> logical;
         std::vector<int> cost;
         for (int i = 0; i < n_mats; ++i) {
-            if (p->sz[i].ws_yp == 0) continue;
+            if (p->sz[i].plane == 0) continue;
             for (int ti = 0; ti < ceil_div(f == 0 ? d[i].m : f == 1 ? d[i].n : p->sz[i].ldn, kSketchTileG); ++ti)
                 for (int tj = 0; tj < ceil_div(p->sz[i].l, kSketchTileL); ++tj) {
                     logical.push_back(TileRef{i, ti, tj, 0});
@@ -507,7 +513,7 @@ int inverse_factor(ng_state* st, GemmOp op, double shift_rel, hipStream_t stream
 }
 
 // CholeskyQR of the sketch X (Ya if is_a, else Yb).
-//   twice = false: one pass with a small diagonal shift, result left in Yc -- enough to keep the
+//   twice = false: one pass with a small diagonal shift, result left in Yc (as planes: see sketch_plane) -- enough to keep the
 //                  power iteration from collapsing;
 //   twice = true : a second, unshifted pass repairs the first pass's loss of orthogonality and
 //                  puts the result back in X (the basis handed to the Rayleigh-Ritz step).
@@ -786,8 +792,10 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
             // Yb ([max(m,n)][l] floats, l >= r), which is free from the Rayleigh-Ritz step on
             if (hp->proj_dtype == NG_BF16) md.P = md.Yb;
             md.Yc = (float*)(ws + off); off += z.ws_y;
-            md.Yp = z.ws_yp ? (bf16_t*)(ws + off) : nullptr; off += z.ws_yp;
-            md.yp_plane = (long long)(z.ws_yp / 3 / 2);
+            md.yp_plane = (long long)(z.plane / 2);
+            md.yp_last = (long long)(z.plane_last / 2);
+            md.Yp = z.plane == 0 ? nullptr : z.ws_yp ? (bf16_t*)(ws + off) : (bf16_t*)md.Yb + 2 * md.yp_last;
+            off += z.ws_yp;
             md.Bm = (float*)(ws + off); off += z.ws_bm;
             md.T = (double*)(ws + off); off += z.ws_t;
             md.Linv = (float*)(ws + off); off += z.ws_linv;

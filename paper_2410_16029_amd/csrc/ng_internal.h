@@ -65,8 +65,8 @@ struct MatDev {
     float* Ya;        // [max(m,n)][l]
     float* Yb;        // [max(m,n)][l]
     float* Yc;        // [max(m,n)][l]
-    bf16_t* Yp;       // three planes [max(m,n) / 8][l][8] of the sketch that a gradient product reads, yp_plane
-    long long yp_plane;   // elements apart (null: the matrix's gradient products run on the fp32 GEMM)
+    bf16_t* Yp;       // third plane of the last basis (null: the matrix's gradient products run on the fp32 GEMM)
+    long long yp_plane, yp_last;   // elements from one sketch plane to the next, those of the last basis (see sketch_plane)
     float* Bm;        // [l][ldn]   B = Q^T G; later the l x r rotation
     double* T;        // [lp][lp]   Gram matrix / Cholesky factor of orders above kFactorMax
     float* Linv;      // [lp][lp]   inverse Cholesky factor (float); during the Rayleigh-Ritz step the rows
@@ -162,9 +162,20 @@ struct StepScalars {
     int hist_bf16;       // history slots are bf16 (else float)
     int norm_count;      // Fisher normaliser 1/count (valid slots) instead of 1/s
     int slot;            // history slot an OP_CARRY_SLOT product works on
-    int planes;          // sketch planes that an OP_APPLY_* product stores (MatDev::Yp); 0: none
+    int planes;          // sketch planes that an OP_APPLY_* product stores (sketch_plane); 0: none
     int planes_only;     // ... and not its float result
 };
+
+// Plane q of the sketch that a product with the gradient reads, [rows / 8][l][8] bf16, rows past the last zero.  The planes lie
+// in sketch buffers that are free while they live: two of the random matrix or of a basis inside the subspace iteration in Yc,
+// the third in Bm, which the product B = Q^T G fills later.  The last basis comes from Yc and goes to Ya as floats too, and
+// that product reads its planes: they lie in Yb, the third behind the others where Yb is long enough (n from about 3/2 m
+// on), else in memory of its own, 2 bytes per element of Q.  (Planes of their own took 6 bytes per element of
+// max(m, n) x l, 35 % of the workspace; this is 4 to 8 %.)
+__host__ __device__ inline bf16_t* sketch_plane(const MatDev& md, bool last, int q) {
+    if (q == 2) return last ? md.Yp : (bf16_t*)md.Bm;
+    return last ? (bf16_t*)md.Yb + q * md.yp_last : (bf16_t*)md.Yc + q * md.yp_plane;
+}
 
 // Grouped-launch work item: which matrix and which tile / part of it a workgroup takes.
 // mat < 0 marks a padding entry (the workgroup exits).
@@ -292,7 +303,7 @@ hipError_t launch_project_bf16(const MatDev* mats, const MatDyn* dyn, const Tile
 hipError_t launch_update_bf16(const MatDev* mats, const MatDyn* dyn, const TileRef* tiles, int n_tiles,
                               StepScalars sc, const void* zero16, int sides, hipStream_t stream);
 
-// Refresh products of a bf16 gradient with an fp32 sketch matrix Y, held as bf16 planes (MatDev::Yp), on the bf16 MFMA;
+// Refresh products of a bf16 gradient with an fp32 sketch matrix Y, held as bf16 planes (sketch_plane), on the bf16 MFMA;
 // left side, at least 8 columns.  form 1: Ya = G Y, form 2: Yb = G^T Y, form 3: Bm = Y^T G; planes: how many of Y's three
 // planes enter (form 1: 1 to 3, form 2: 2 or 3, form 3: 3).  tiles: ti counts kSketchTileG rows or columns of the
 // gradient, tj kSketchTileL sketch columns.

@@ -86,6 +86,22 @@ def test_query_sizes_c1_and_bf16_layout():
     assert sizes[0][B.NG_BUF_H] == 512 * stored * 4
 
 
+@pytest.mark.parametrize("shapes,r", [
+    ([(512, 512)] * 4 + [(512, 1376)] * 2 + [(1376, 512)], 128),
+    ([(1024, 1024)] * 4 + [(1024, 2736)] * 2 + [(2736, 1024)], 256),
+    ([(2048, 2048)] * 4 + [(2048, 5461)] * 2 + [(5461, 2048)], 512)])
+def test_sketch_planes_of_a_bf16_refresh_share_the_workspace(shapes, r):
+    # three float sketches of max(m, n) x l, Q^T G and the r x r systems are what a refresh works on in either type; its
+    # sketches as bf16 planes may add 2 bytes per element of the last basis where no sketch buffer has room
+    hp = B.ng_default_hparams()
+    hp.s, hp.grad_dtype = 8, B.NG_BF16
+    _, with_planes = B.ng_query_sizes(B.make_descs(shapes * 2, r), hp)
+    _, without = B.ng_query_sizes(B.make_descs(shapes * 2 + [(r, r)], r, sides=[0] * 2 * len(shapes) + [1]), hp)
+    extra = 2 * sum(m * r * 2 for m, n in shapes if 2 * n < 3 * m)
+    assert with_planes <= without + extra + 100_000
+    assert with_planes <= 1.09 * without
+
+
 @pytest.mark.parametrize("mutate,code", [
     (lambda d, hp: setattr(hp, "lambda_", 0.0), B.NG_ERR_HPARAM),
     (lambda d, hp: setattr(hp, "lambda_", -1.0), B.NG_ERR_HPARAM),

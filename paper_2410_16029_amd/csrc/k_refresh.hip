@@ -1431,10 +1431,15 @@ __global__ __launch_bounds__(64 * NW, 3) void k_jacobi_round(const MatDev* __res
     if (cross ? (bp * 16 >= md.l || bq * 16 >= md.l) : (bp * 16 >= md.l && bq * 16 >= md.l)) return;
     // Which wavefront runs the small sweep: those of the workgroups that share a CU (ids 256 apart) are to be on
     // different SIMDs, because one alone fills its SIMD's issue (two on one take twice as long).  For two wavefronts per
-    // visit and up to six visits per CU the choice was measured: second wavefront in the third turn only: 2.4 % off
-    // the refresh of the 350M set against the third and fourth; first, third and fourth 1.5 %, third to fifth 1.3 %.
-    const int turn = (int)(blockIdx.x / 256);
-    const int sweeper = NW == 2 ? turn % 6 == 2 : turn % NW;
+    // visit the choice was measured, by visits per CU: the first always with four, else the second in the third of six
+    // turns only.  Refresh in us with the first always / the second in the third turn / the second in every other pair of turns:
+    //   3 per CU, 84 matrices of order 256 5260 / 5220 / 5222, 160 of 128 1774 / 1762 / 1762
+    //   4         112 of 256 5545 / 5734 / 5681, 128 of 256 5744 / 5978 / 5925, 256 of 128 1937 / 2024 / 2012
+    //   5         144 of 256 6769 / 6756 / 7043, 96 of 384 18657 / 18534 / 19017
+    //   6         168 of 256 6979 / 7004 / 7231, 84 of 512 30669 / 30689 / 30932
+    //   8         256 of 256 9962 / 9787 / 9873
+    const int turn = (int)(blockIdx.x / 256), per_cu = (int)((gridDim.x + 255) / 256);
+    const int sweeper = NW == 2 ? per_cu != 4 && turn % 6 == 2 : turn % NW;
     const int nrot = jacobi_visit<NW>(jacobi_rows(md), lp, bp, bq, cross, sweeper, smem);
     if (nrot) atomicAdd(&md.jflag[sweep], nrot);
 }

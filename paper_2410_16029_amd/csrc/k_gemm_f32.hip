@@ -624,6 +624,13 @@ __global__ __launch_bounds__(256, TS == 128 ? 2 : 4) void k_gemm_f32_sides(int o
 // of them 122 -> 103; refresh of that set 1790 -> 1700; of 84 768-wide matrices (1248 tiles, runs of 256) 7259 -> 7149; but
 // 14 and 28 matrices of the 350M set in fp32 (1568 and 3136 tiles, runs of 256) 404 -> 406 and 700 -> 714, refresh of
 // that set in bf16 12.49 -> 12.75 ms, projection of the 28 in fp32 (672 tiles, runs of 1024 and more): step 689 -> 712.
+bool f32_tile_large(GemmOp op, int max_m, int max_n, int max_k, long long tiles, int max_split) {
+    // (a split projection is a small one: its chunks were counted in 64 x 64 tiles)
+    if (op == OP_PROJECT_F32 && max_split > 0) return false;
+    const int run = max_k / (max_split > 1 ? max_split : 1);
+    return max_m >= 128 && max_n >= 128 && run >= 256 && tiles >= 512 && tiles * run >= 1536 * 256;
+}
+
 template <int TS>
 static void run_gemm_f32(dim3 g, int op, const MatDev* mats, const MatDyn* dyn, int grad_dtype, StepScalars sc,
                          bool ai, bool bj, bool abf, bool bbf, bool sym,
@@ -683,10 +690,7 @@ hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int
         const long long nx = (max_n + ts - 1) / ts, ny = (max_m + ts - 1) / ts;
         return (left.sym ? ny * (ny + 1) / 2 : nx * ny) * (max_split > 1 ? max_split : 1);
     };
-    // (a split projection is a small one: its chunks were counted in 64 x 64 tiles)
-    const int run = max_k / (max_split > 1 ? max_split : 1);
-    const bool big = max_m >= 128 && max_n >= 128 && run >= 256 && tiles >= 512 && tiles * run >= 1536 * 256 &&
-                     !(op == OP_PROJECT_F32 && max_split > 0);
+    const bool big = f32_tile_large(op, max_m, max_n, max_k, tiles, max_split);
     const dim3 g((unsigned)((count(big ? 128 : 64) + 7) / 8 * 8), 1, n_mats);
     if (by_side && sides == 3 && grad_dtype == NG_F32 &&
         (big ? run_gemm_f32_sides<128>(g, (int)op, mats, dyn, sc, left, right, stream)

@@ -278,6 +278,9 @@ inline int sym_index(int op) {      // -1: not a symmetric product
     return op >= OP_GRAM_A && op <= OP_GRAM_CB ? op - OP_GRAM_A : op == OP_B_BT ? 4 : op == OP_GRAM_P ? 5 : -1;
 }
 
+// whether a product takes the 128 x 128 tile; arguments as launch_gemm_f32
+bool f32_tile_large(GemmOp op, int max_m, int max_n, int max_k, long long tiles, int max_split);
+
 // max_m, max_n, max_k: largest dimensions of the product over the layer set, tiles: its 128 x 128 tiles, each piece of a cut
 // contraction counted (grid and tile choice)
 // max_split: largest number of pieces that a matrix's contraction is cut into, 0 or 1 for none (symmetric products:

@@ -7,10 +7,11 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <utility>
 #include <vector>
 
 #include "ng.h"
-#include "ng_internal.h"   // ng::xcd_order, ng::TileRef, ng::sym_planes, ng::ritz_place, ... (internal, host side)
+#include "ng_internal.h"   // ng::xcd_order, ng::f32_tile_large, ng::TileRef, ng::sym_planes, ng::ritz_place, ... (internal, host side)
 
 static int g_failed = 0;
 #define CHECK(cond)                                                         \
@@ -52,6 +53,40 @@ static int make(Set& s, const ng_hparams& hp, uint32_t flags) {
         for (int b = 0; b < NG_NBUF; ++b) s.bufs[i].buf[b] = aligned(s, bytes[(size_t)i * NG_NBUF + b]);
     s.ws = aligned(s, s.ws_bytes);
     return ng_init_state(s.descs.data(), s.bufs.data(), n, &hp, s.ws, s.ws_bytes, flags, nullptr, &s.st);
+}
+
+// The layer sets with which test_gpu_kernel_edges.py means to reach the large tile of the fp32 products do reach it, and the
+// small ones do not: dimensions and tiles of each product as ng_init_state adds them up.
+static bool takes_large_tile(ng::GemmOp op, const std::vector<std::pair<int, int>>& shapes, int r, int sketch, int max_split) {
+    int max_m = 1, max_n = 1, max_k = 1;
+    long long tiles = 0;
+    for (const auto& x : shapes) {      // x: the projected problem's shape (the longer side second)
+        ng::MatDev md{};
+        md.m = x.first; md.n = x.second; md.r = r; md.l = sketch; md.ldn = (x.second + 31) / 32 * 32;
+        int M, N, K;
+        ng::gemm_f32_dims(op, md, &M, &N, &K);
+        if (M > max_m) max_m = M;
+        if (N > max_n) max_n = N;
+        if (K > max_k) max_k = K;
+        tiles += (long long)((M + 127) / 128) * ((N + 127) / 128);
+    }
+    return ng::f32_tile_large(op, max_m, max_n, max_k, tiles, max_split);
+}
+
+static void check_f32_tiles() {
+    std::vector<std::pair<int, int>> set(40, {600, 1031});          // test_fp32_products_of_extreme_values, "large"
+    CHECK(takes_large_tile(ng::OP_PROJECT_F32, set, 256, 256, 0));
+    CHECK(takes_large_tile(ng::OP_UPDATE_F32, set, 256, 256, 0));
+    set = {{130, 263}, {300, 131}};                                 // ... "small"
+    CHECK(!takes_large_tile(ng::OP_PROJECT_F32, set, 41, 41, 0));
+    CHECK(!takes_large_tile(ng::OP_UPDATE_F32, set, 41, 41, 0));
+    set.clear();                                                    // test_fp32_set_with_both_sides_in_large_tiles
+    for (int i = 0; i < 12; ++i) set.insert(set.end(), {{700, 900}, {700, 900}, {690, 911}, {701, 905}});
+    for (ng::GemmOp op : {ng::OP_PROJECT_F32, ng::OP_UPDATE_F32, ng::OP_G_B2A, ng::OP_G_C2A, ng::OP_GT_C2B, ng::OP_QT_G})
+        CHECK(takes_large_tile(op, set, 270, 278, 0));
+    set.assign(40, {2048, 4096});                                   // a cut projection keeps the small tile
+    CHECK(takes_large_tile(ng::OP_PROJECT_F32, set, 256, 256, 0));
+    CHECK(!takes_large_tile(ng::OP_PROJECT_F32, set, 256, 256, 2));
 }
 
 // The tile-table order: every tile exactly once, eight runs (entry k of run x at 8 k + x) of about equal
@@ -181,6 +216,7 @@ static void check_ritz_order() {
 
 int main() {
     check_tile_order();
+    check_f32_tiles();
     check_ritz_order();
     check_sym_planes();
     ng_hparams hp;

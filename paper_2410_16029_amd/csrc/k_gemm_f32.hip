@@ -15,6 +15,8 @@
 // 32, two LDS buffers and three register sets (one workgroup per CU): 290 us.
 // MFMA 32x32x16 bf16 operand layout: lane L supplies eight consecutive k, 8 (L/32) .. of A row L%32 and of B column L%32;
 // the 16 accumulators of lane L are D[8*g + 4*(L/32) + e][L%32], index 4*g + e.
+#include <type_traits>
+
 #include "ng_internal.h"
 
 namespace ng {
@@ -332,8 +334,10 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // A wavefront's blocks once more, on the fp32 MFMA and straight from memory: the planes cannot stand for an infinity, whose
 // lower planes are NaN and whose products with the other operand's lower planes are infinities of either sign, nor for
 // values from 2^112 on, nor for sums from 2^96 on (both carry the planes' factor).  Each shows as a result that is not
-// finite, so such results are formed again; i, j: this lane's first row and column.
-template <int NB, bool ABF, bool BBF>
+// finite, so such results are formed again; i, j: this lane's first row and column.  Step of 56 matrices (60M set, rank 128)
+// with finite gradients / an infinity in each / nothing but NaN: 270 / 462 / 518 us, of 28 of the 350M set 692 / 1336 / 1529
+// (all products on the fp32 MFMA, from LDS tiles: 491 / 543 / 521 and 896 / 948 / 910).
+template <int NB, bool AI, bool BJ, bool ABF, bool BBF>
 __device__ __forceinline__ void fp32_again(floatx16 (&acc)[NB][NB], const GemmView& v, int i, int j, int h) {
     const NG_AS1 unsigned char *pa[NB], *pb[NB];
 #pragma unroll
@@ -347,8 +351,39 @@ __device__ __forceinline__ void fp32_again(floatx16 (&acc)[NB][NB], const GemmVi
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
     }
-#pragma unroll 4
-    for (int k0 = 0; k0 < v.K; k0 += 2) {
+    auto multiply = [&](const float (&a)[NB], const float (&b)[NB]) {
+#pragma unroll
+        for (int x = 0; x < NB; ++x)
+#pragma unroll
+            for (int y = 0; y < NB; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x], b[y], acc[x][y], 0, 0, 0);
+    };
+    // four consecutive k per half of the wavefront: one vector of an operand that has them side by side
+    auto four = [](auto bf, bool fast, const NG_AS1 unsigned char* p, int k, long long sk) {
+        constexpr bool BF = decltype(bf)::value;
+        if (fast) return load4<BF>(p + (long long)k * (BF ? 2 : 4));
+        return (f32x4_t){load1<BF>(p, k * sk), load1<BF>(p, (k + 1) * sk), load1<BF>(p, (k + 2) * sk), load1<BF>(p, (k + 3) * sk)};
+    };
+    const int whole = v.K / 8 * 8;
+#pragma unroll 2
+    for (int k0 = 0; k0 < whole; k0 += 8) {
+        f32x4_t a4[NB], b4[NB];
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+            a4[x] = four(std::bool_constant<ABF>(), !AI, pa[x], k0 + 4 * h, v.sAk);
+            b4[x] = four(std::bool_constant<BBF>(), !BJ, pb[x], k0 + 4 * h, v.sBk);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float a[NB], b[NB];
+#pragma unroll
+            for (int x = 0; x < NB; ++x) {
+                a[x] = a4[x][e];
+                b[x] = b4[x][e];
+            }
+            multiply(a, b);
+        }
+    }
+    for (int k0 = whole; k0 < v.K; k0 += 2) {
         const bool in = k0 + h < v.K;
         const int k = in ? k0 + h : v.K - 1;
         float a[NB], b[NB];
@@ -357,10 +392,7 @@ __device__ __forceinline__ void fp32_again(floatx16 (&acc)[NB][NB], const GemmVi
             a[x] = in ? load1<ABF>(pa[x], k * v.sAk) : 0.f;
             b[x] = in ? load1<BBF>(pb[x], k * v.sBk) : 0.f;
         }
-#pragma unroll
-        for (int x = 0; x < NB; ++x)
-#pragma unroll
-            for (int y = 0; y < NB; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x], b[y], acc[x][y], 0, 0, 0);
+        multiply(a, b);
     }
 }
 
@@ -516,7 +548,7 @@ __device__ __forceinline__ void gemm_f32_tile(int op, const MatDev* __restrict__
                 acc[x][y][e] = down * (acc[x][y][e] + low[x][y][e]);
                 finite = finite && fabsf(acc[x][y][e]) <= 3.402823466e38f;
             }
-    if (__any(!finite)) fp32_again<NB, ABF, BBF>(acc, v, i0 + wm * (TS / 2) + li, j0 + wn * (TS / 2) + li, h);
+    if (__any(!finite)) fp32_again<NB, AI, BJ, ABF, BBF>(acc, v, i0 + wm * (TS / 2) + li, j0 + wn * (TS / 2) + li, h);
 
     // columns from Nvalid on (the padding of a state's rows) are zero
     if (j0 + TS > v.Nvalid) {

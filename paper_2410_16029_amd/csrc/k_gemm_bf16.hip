@@ -1078,8 +1078,9 @@ __global__ __launch_bounds__(C::NT) void k_project_bf16_dl(const MatDev* __restr
 // from memory straight into LDS, three k-steps deep or two.  (Split on its way into LDS, once per row tile of the result, Y
 // cost more vector-ALU time than the products took of the matrix cores, and a k-step waited for its own loads: 168
 // products of 1024 x 1024 .. 2736 with 256 columns took 523 / 600 / 740 us with 1 / 2 / 3 planes; now 305 / 355 / 500,
-// i.e. up to 930 TFLOP/s; the 60M set's 61 / 66 / 80 us are 33 / 33 / 43.)  One plane is bound by its operands' way into
-// LDS, three by the matrix cores at the clock they hold.  256-row tiles with one workgroup of eight wavefronts per CU:
+// i.e. up to 930 TFLOP/s; the 60M set's 61 / 66 / 80 us are 33 / 33 / 43.)  What bounds it: the wavefronts wait half to three
+// fifths of their time, for operands on their way into LDS and at the barrier of a k-step; the matrix cores are busy 22 /
+// 42-45 / 45 % of the cycles, LDS 11 / 16 / 15 %.  256-row tiles with one workgroup of eight wavefronts per CU:
 // 299 / 343 / 490 us, but 38 / 41 / 57 on the 60M set, whose 278 tiles are one wave.
 //
 // FORM 1: C = Ya [m][l] = G Y        (Y [n][l]; G's rows are contraction-contiguous)

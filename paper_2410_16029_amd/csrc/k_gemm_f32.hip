@@ -9,7 +9,8 @@
 // terms relative to the root of the sum of its squared terms, 4.4e-7 / 1.4e-7: 168 Gram matrices of 1024..2736 x 256
 // 266 / 182 us, 168 products with a 256 x 256 factor 293 / 188 us, fp32 step of eight mid-size blocks 974 / 658 us.
 // What bounds them now: 128 x 128 tiles of 6 to 10 k-steps, each with its split, two barriers and the latency of the
-// first loads; the matrix cores are busy a third of the time.
+// first loads: in the refresh of 168 matrices of 1024..2736 at rank 256 the matrix cores are busy 25-40 % of the cycles, the
+// wavefronts wait a third to two fifths of theirs, with 1.3-1.6 of the two per SIMD there on average.
 //
 // Tile 128 x 128 per workgroup (4 wavefronts of 64 x 64, two workgroups per CU), BK = 32.  Tried: eight wavefronts of 64 x
 // 32, two LDS buffers and three register sets (one workgroup per CU): 290 us.
@@ -198,7 +199,8 @@ __device__ __forceinline__ f32x4_t load4(const NG_AS1 unsigned char* p) {
 // Every operand value x goes into LDS as three bf16 planes, 2^16 x = x0 + x1 + x2 (each the rounding of what the ones before
 // leave: 24 bits, the float itself; every float is a multiple of 2^-149, bf16's subnormals of 2^-133, hence the factor: without
 // it operands below 2^-110 lost bits, 2.7e-6 of a product at 1e-35), and a product of two operands is six bf16 MFMA products,
-//   a b = a0 b0 + (a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0),      dropped: a1 b2, a2 b1, a2 b2, together at most 2^-24 (1 + 2^-10) |a b|.
+//   a b = a0 b0 + (a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0),
+// which drops a1 b2 + a2 b1 + a2 b2, together at most 2^-24 (1 + 2^-10) |a b|.
 // a0 b0 has an accumulator of its own, which is rounded once per 16 contraction steps (the fp32 MFMA rounds every
 // two), and the other five share one that is some 2^-8 as large: the sums are closer to 64 bits than the fp32
 // MFMA's, at three eighths of its matrix-core time.
@@ -208,8 +210,9 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
-// the NP planes of two values, a in the low halves
 constexpr float kSplitUp = 65536.f;
+
+// the NP planes of two values, a in the low halves
 template <int NP>
 __device__ __forceinline__ void split2(float a, float b, unsigned (&p)[NP]) {
 #pragma unroll

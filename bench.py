@@ -184,6 +184,11 @@ def main() -> int:
 
     ms_per_step = elapsed * 1e3 / args.steps
     work = algorithmic_work(cfg, mats, args.hist_dtype)
+    # Matrices whose two history passes are one launch have their share of the Gram row and the solve in the
+    # phase "adam", with the history read once.
+    separate = [x for i, x in enumerate(mats) if B._lib.ng_debug_history_tiles(st, i) == 0]
+    for name in ("gram", "solve"):
+        work[name] = algorithmic_work(cfg, separate, args.hist_dtype)[name]
     phases = {}
     if not args.no_phase_events:
         ms, nsteps = B.ng_get_phase_ms(st, reset=True)

@@ -223,7 +223,8 @@ int ng_step(ng_state* st, const void* const* grads, void* const* weights, float 
  * on that GPU: calls of ng_step_static that overlap on one GPU (two streams, two threads) race;
  * calls ordered on one stream, also from different handles, are fine (each call rewrites all it
  * reads; nothing in the array has to start at zero).  A layer set whose step scratch exceeds the
- * array returns NG_ERR_WORKSPACE (the per-matrix share is 2 KiB * s for the reduction plus, for
+ * array returns NG_ERR_WORKSPACE (the per-matrix share is 2 KiB * s for the reduction -- up to
+ * 4 KiB * s and 2.25 KiB where both passes over the history are one launch, which is only done where it fits -- plus, for
  * fp32 sets of rank <= 16, ceil(m/128) * rank class * ldn * 4 bytes; the row chunks that the projection of
  * small fp32 sets of larger rank is cut into are taken only where they fit); nothing is launched then.
  * Calls no hipMalloc / hipFree.  The first call on a GPU looks the array's address up
@@ -253,7 +254,8 @@ int ng_get_status(ng_state* st, ng_stream stream);
 
 /* Phase timing with HIP events on the stream of the call.  When enabled, ng_step
  * records an event before each phase (project, gram, solve, adam, update) and
- * one after the last.  ng_get_phase_ms synchronises on the last event and adds
+ * one after the last.  Matrices whose two passes over the history are one launch have
+ * their share of gram and solve in adam.  ng_get_phase_ms synchronises on the last event and adds
  * the elapsed milliseconds of every profiled step since the last reset into
  * ms[0..4]; *steps = number of steps accumulated.  reset != 0 clears the sums. */
 enum { NG_PHASE_PROJECT = 0, NG_PHASE_GRAM, NG_PHASE_SOLVE, NG_PHASE_ADAM, NG_PHASE_UPDATE,

@@ -9,94 +9,17 @@
 // the section's g/lambda - U z/lambda^2 (push U through the inverse: the current
 // gradient is slot `head` of the stack) but has no cancellation, which the printed
 // form has at about log10(||R||^2 / (s lambda)) digits.
-#include "eliminate16.h"
-#include "ng_internal.h"
+#include "state_math.h"
 
 namespace ng {
 
-// Pointers read out of the per-matrix table are cast to the global address space so that the
-// streaming kernels use global_load / global_store instead of flat accesses.
-#define NG_AS1 __attribute__((address_space(1)))
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-
-// ------------------------------------------------------------------ helpers
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-
-// two floats -> two bf16 (round to nearest even) in one v_cvt_pk_bf16_f32; a in the low half
-__device__ __forceinline__ unsigned int pack_bf16x2(float a, float b) {
-    const f32x2_t f = {a, b};
-    bf16x2_t hv = __builtin_convertvector(f, bf16x2_t);
-    return *reinterpret_cast<unsigned int*>(&hv);
-}
-__device__ __forceinline__ unsigned short f32_to_bf16_rne(float x) { return (unsigned short)(pack_bf16x2(x, 0.f) & 0xffffu); }
-
-// The value of the lane's partner at level L: lane ^ 32, lane ^ 16 (by exchanging halves of rows, see wave_sums), lane ^ 8,
-// and inside a group of eight the mirrored lane, inside four the mirrored one, inside two the other one.
-template <int L>
-__device__ __forceinline__ double partner_dpp(double v) {
-    constexpr int kCtrl = L == 2 ? 0x128 : L == 3 ? 0x141 : L == 4 ? 0x1B : 0xB1;   // row_ror:8, half mirror, quad_perm
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), kCtrl, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), kCtrl, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-// a keeps its own lower half of the wavefront (L 0) or of every pair of rows (L 1) and gets b's lower half in the upper
-// one's place, b the reverse: afterwards a + b is the first value's sum in the lower lanes, the second's in the upper ones
-template <int L>
-__device__ __forceinline__ double swap_add(double a, double b) {
-    u32x2_t lo, hi;
-    if (L == 0) {
-        lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
-        hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
-    } else {
-        lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
-        hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
-    }
-    return __hiloint2double((int)hi.x, (int)lo.x) + __hiloint2double((int)hi.y, (int)lo.y);
-}
-// Sums of N = 2^q values over the 64 lanes.  Each level adds the partner lanes and, while there is more than one value,
-// leaves either lane of a pair half of the values: N - 1 + (6 - q) exchanges instead of 6 N, none of them through LDS.  On
-// return v[0] is the sum of value wave_sums_slot(N, lane).  (Six LDS exchanges per value were the larger part of what
-// the Gram row of a small slot did besides its loads: 60M set 33.4 -> 29.4 us, three mid-size fp32 matrices 10.8 -> 8.7,
-// 350M set 608 -> 602.)
-template <int N, int L>
-__device__ __forceinline__ void wave_sums(double* v, int lane) {
-    if constexpr (L < 6) {
-        if constexpr (N > 1) {
-            constexpr int H = N / 2;
-            const bool upper = (lane >> (5 - L)) & 1;
-#pragma unroll
-            for (int j = 0; j < H; ++j) {
-                if constexpr (L < 2) {
-                    v[j] = swap_add<L>(v[j], v[j + H]);
-                } else {
-                    const double give = upper ? v[j] : v[j + H], keep = upper ? v[j + H] : v[j];
-                    v[j] = keep + partner_dpp<L>(give);
-                }
-            }
-            wave_sums<H, L + 1>(v, lane);
-        } else {
-            if constexpr (L < 2) v[0] = swap_add<L>(v[0], v[0]);
-            else v[0] += partner_dpp<L>(v[0]);
-            wave_sums<1, L + 1>(v, lane);
-        }
-    }
-}
-template <int N>
-__device__ __forceinline__ int wave_sums_slot(int lane) {
-    int slot = 0;
-#pragma unroll
-    for (int h = N / 2, b = 5; h > 0; h >>= 1, --b) slot += ((lane >> b) & 1) ? h : 0;
-    return slot;
-}
-constexpr int pow2_from(int n) { return n <= 1 ? 1 : 2 * pow2_from((n + 1) / 2); }
-
 // ------------------------------------------------------------------ per-step table upload
-__global__ void k_upload_dyn(MatDyn* table, DynChunk chunk, int first, int n, const MatDev* mats) {
+__global__ void k_upload_dyn(MatDyn* table, DynChunk chunk, int first, int n, const MatDev* mats, unsigned long long zero_off,
+                             unsigned n16) {
     int i = threadIdx.x;
-    if (i >= n) return;
+    uint4* z = reinterpret_cast<uint4*>(reinterpret_cast<char*>(table) + zero_off);
+    for (unsigned q = blockIdx.x * 128 + i; q < n16; q += gridDim.x * 128) z[q] = make_uint4(0, 0, 0, 0);
+    if (i >= n || blockIdx.x > 0) return;
     table[first + i] = chunk.e[i];
     if (mats == nullptr) return;
     // the zero-padded copy of the last gradient row's final partial 8-column chunk (bf16 projection)
@@ -109,8 +32,11 @@ __global__ void k_upload_dyn(MatDyn* table, DynChunk chunk, int first, int n, co
 }
 
 hipError_t launch_upload_dyn(MatDyn* table, const DynChunk& chunk, int first, int n, const MatDev* mats,
-                             hipStream_t stream) {
-    hipLaunchKernelGGL(k_upload_dyn, dim3(1), dim3(128), 0, stream, table, chunk, first, n, mats);
+                             size_t zero_off, size_t zero_bytes, hipStream_t stream) {
+    const unsigned n16 = (unsigned)(zero_bytes / 16);
+    const unsigned blocks = n16 > 64 * 512 ? 64 : n16 / 512 + 1;
+    hipLaunchKernelGGL(k_upload_dyn, dim3(blocks), dim3(128), 0, stream, table, chunk, first, n, mats,
+                       (unsigned long long)zero_off, n16);
     return hipGetLastError();
 }
 
@@ -354,38 +280,17 @@ hipError_t launch_gram_row(const MatDev* mats, const MatDyn* dyn, const TileRef*
 // wavefront, eight loads in flight and the factor in LDS, three barriers a column: 30 us for 168
 // matrices at s = 16, 11 us for 56 at s = 8; now 9 and 5.8.)  Systems of up to 4 and 8 stop after as many of the elimination's
 // dependent steps (72 matrices at s = 4 5.5 -> 4.8 us, one 5.6 -> 4.3).
-constexpr int kSolveSub = 16;      // threads that share the sum of one slot's partials
 __global__ __launch_bounds__(256) void k_solve(const MatDev* __restrict__ mats, const MatDyn* __restrict__ dyn,
                                                int first, StepScalars sc, int row_override, int* status) {
     __shared__ double A[kMaxS][kMaxS + 1];
     __shared__ double bc[256];
     const MatDev& md = mats[first + blockIdx.x];
+    if (row_override < 0 && md.hist_tiles > 0) return;     // k_history solves for this one
     const int s = sc.s;
     const int head = row_override >= 0 ? row_override : dyn[first + blockIdx.x].head;
     const int tid = threadIdx.x;
 
-    // partial sums: thread (sub, j) adds parts sub, sub + nsub, ... of slot j in order; the nsub sub-sums of a
-    // slot are then added in order (a fixed order: the result does not depend on timing)
-    const int nsub = 256 / s < kSolveSub ? 256 / s : kSolveSub;
-    {
-        const int j = tid % s, sub = tid / s;
-        double v = 0.0;
-        if (sub < nsub) {
-            const int np = md.dot_nparts;
-            const NG_AS1 double* parts = (const NG_AS1 double*)step_scratch<double>(dyn, md.dot_parts_off) + j;
-            for (int p = sub; p < np; p += 16 * nsub) {
-                double x[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const int pu = p + u * nsub;
-                    x[u] = parts[(long long)(pu < np ? pu : p) * s];
-                }
-#pragma unroll
-                for (int u = 0; u < 16; ++u) v += p + u * nsub < np ? x[u] : 0.0;
-            }
-        }
-        bc[tid] = v;
-    }
+    const int nsub = sum_dot_parts<false>(step_scratch<double>(dyn, md.dot_parts_off), md.dot_nparts, s, tid, bc);
     // old Gram matrix into LDS (its row and column `head` are replaced below)
     if (row_override < 0)
         for (int q = tid; q < s * s; q += 256) {
@@ -410,25 +315,7 @@ __global__ __launch_bounds__(256) void k_solve(const MatDev* __restrict__ mats, 
     bool bad = false;
     const int i = tid;
     if (s <= 16) {
-        const int c = tid & 15;
-        double a[16], v[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            a[k] = k < s && c < s ? A[k < s ? k : 0][c < s ? c : 0] * inv_s + (k == c ? lam : 0.0) : (k == c ? 1.0 : 0.0);
-            v[k] = k == c ? 1.0 : 0.0;
-        }
-        if (s <= 4) eliminate16<0, 4>(a, v, 0.0, bad);
-        else if (s <= 8) eliminate16<0, 8>(a, v, 0.0, bad);
-        else eliminate16<0>(a, v, 0.0, bad);
-        // v: column c of X = L^{-1}; column `head` goes to all lanes through LDS (one wavefront: in order)
-        if (c == head) {
-#pragma unroll
-            for (int k = 0; k < 16; ++k) bc[k] = v[k];
-        }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        double w = 0.0;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) w = fma(v[k], bc[k], w);
+        const double w = solve16<kMaxS + 1>(&A[0][0], bc, s, head, tid, lam, inv_s, bad);
         if (tid < s) {
             if (!(fabs(w) < 1.0e300)) bad = true;
             md.w64[tid] = w;
@@ -499,24 +386,6 @@ hipError_t launch_solve(const MatDev* mats, const MatDyn* dyn, int first, int n_
 // N is stored either as float [r][ldn] or as bf16 [r/8][ldn][8] (eight
 // consecutive rows of one column adjacent: the k-packing the update GEMM's MFMA
 // operand wants, so that kernel needs no transpose).
-// Four consecutive history elements of one row: a float4, or 4 bf16 (8 bytes) widened to float.
-// `slot` is uniform over the workgroup and `off` a 32-bit byte offset, so the load takes its base
-// from scalar registers and needs one address register per row (the host checks that a slot is
-// below 2 GiB).
-template <bool HB>
-__device__ __forceinline__ f32x4_t load_hist4(const NG_AS1 unsigned char* slot, unsigned off) {
-    if (HB) {
-        const u32x2_t v = __builtin_nontemporal_load((const NG_AS1 u32x2_t*)(slot + off));
-        f32x4_t o;
-        o.x = __uint_as_float(v.x << 16);
-        o.y = __uint_as_float(v.x & 0xffff0000u);
-        o.z = __uint_as_float(v.y << 16);
-        o.w = __uint_as_float(v.y & 0xffff0000u);
-        return o;
-    }
-    return __builtin_nontemporal_load((const NG_AS1 f32x4_t*)(slot + off));
-}
-
 // A lane owns a 4 (rows) x 4 (columns) patch; the two lanes of a pair (even: rows 0..3, odd: rows
 // 4..7 of an 8-row band) share the columns, so together they produce the 16-byte octets of N.  The
 // small patch keeps the register count low and the occupancy high, which is what feeds HBM here.
@@ -580,7 +449,6 @@ __global__ __launch_bounds__(256) void k_transform_adam(const MatDev* __restrict
         for (int e = 0; e < RT; ++e) g[e] = load_hist4<HB>(Hbase, eoff[e] * HS);
     }
 
-    const float b1 = sc.beta1, b2 = sc.beta2, ob1 = 1.0f - sc.beta1, ob2 = 1.0f - sc.beta2;
     const float bc1 = dyn[pr.mat].bc1, bc2 = dyn[pr.mat].bc2;
     NG_AS1 unsigned char* Mb = (NG_AS1 unsigned char*)md.M;
     NG_AS1 unsigned char* Vb = (NG_AS1 unsigned char*)md.V;
@@ -599,34 +467,13 @@ __global__ __launch_bounds__(256) void k_transform_adam(const MatDev* __restrict
         for (int u = 0; u < 2; ++u) {
             const int e = 2 * pr2 + u;
             f32x4_t m = mv[u], v = vv[u];
-            const f32x4_t ge = g[e];
-            m.x = fmaf(b1, m.x, ob1 * ge.x);
-            m.y = fmaf(b1, m.y, ob1 * ge.y);
-            m.z = fmaf(b1, m.z, ob1 * ge.z);
-            m.w = fmaf(b1, m.w, ob1 * ge.w);
-            v.x = fmaf(b2, v.x, ob2 * ge.x * ge.x);
-            v.y = fmaf(b2, v.y, ob2 * ge.y * ge.y);
-            v.z = fmaf(b2, v.z, ob2 * ge.z * ge.z);
-            v.w = fmaf(b2, v.w, ob2 * ge.w * ge.w);
-            f32x4_t o;
-            if (sc.adam_mode == NG_ADAM_STANDARD) {
-                o.x = (m.x * bc1) / (sqrtf(v.x) * bc2 + sc.eps);
-                o.y = (m.y * bc1) / (sqrtf(v.y) * bc2 + sc.eps);
-                o.z = (m.z * bc1) / (sqrtf(v.z) * bc2 + sc.eps);
-                o.w = (m.w * bc1) / (sqrtf(v.w) * bc2 + sc.eps);
-            } else {
-                o.x = m.x / sqrtf(v.x + sc.eps);
-                o.y = m.y / sqrtf(v.y + sc.eps);
-                o.z = m.z / sqrtf(v.z + sc.eps);
-                o.w = m.w / sqrtf(v.w + sc.eps);
-            }
+            const f32x4_t o = adam4(m, v, g[e], sc, bc1, bc2);
             const bool live = e < nrow;
             if (live) {
                 __builtin_nontemporal_store(m, (NG_AS1 f32x4_t*)(Mb + eoff[e] * 4u));
                 __builtin_nontemporal_store(v, (NG_AS1 f32x4_t*)(Vb + eoff[e] * 4u));
             }
-            bad |= live && (!(fabsf(o.x) <= 3.0e38f) | !(fabsf(o.y) <= 3.0e38f) | !(fabsf(o.z) <= 3.0e38f) |
-                            !(fabsf(o.w) <= 3.0e38f));
+            bad |= live && any_not_finite(o);
             nv[u].x = live ? o.x : 0.f;
             nv[u].y = live ? o.y : 0.f;
             nv[u].z = live ? o.z : 0.f;

@@ -176,13 +176,18 @@ void derive(const ng_matrix_desc& user, const ng_hparams& hp, int skinny_rk, Siz
 struct Plan {
     std::vector<Sizes> sz;
     std::vector<TileRef> proj, upd, dots, patches, skinny;
+    bool history;                               // both passes over the history in one launch (launch_history) ...
+    std::vector<TileRef> hist;                  // ... its items, and the tiles of each matrix
+    std::vector<int> hist_tiles;
+    size_t step_sync_off, step_sync_bytes;      // what the step clears first
+    std::vector<size_t> sync_off;
     bool sketch_planes;                         // refresh's gradient products read bf16 planes (launch_sketch_product) ...
     bool planeless;                             // ... and not those of every matrix
     std::vector<TileRef> sketch[3];             // their tiles, by form - 1
     int skinny_rk;                              // 0: the MFMA / fp32-GEMM projection and update
     long long tiles4;                           // 256 x 256 tiles of the left-side projection
     int proj_direct, proj_staged, proj_right;   // lengths of the three runs of proj
-    size_t off_status, off_mats, off_step, off_proj, off_upd, off_dots, off_patches, off_skinny, off_sym, off_sketch[3], off_scratch;
+    size_t off_status, off_mats, off_step, off_proj, off_upd, off_dots, off_patches, off_skinny, off_hist, off_sym, off_sketch[3], off_scratch;
     // the scratch block of one step: the per-step table, then what the step's kernels hand to each
     // other (offsets from the start of the block; per matrix)
     size_t step_tail8_off, step_bytes;
@@ -191,6 +196,27 @@ struct Plan {
     int max_split;   // largest proj_chunks of the MFMA projection
     size_t total;
 };
+
+// The items of launch_history, matrix by matrix, a matrix's solver first.  Returns false if no matrix takes that route: without
+// history, or with more than 16 slots (the registers hold no more).
+bool plan_history(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* p) {
+    p->hist.clear();
+    p->hist_tiles.assign(n_mats, 0);
+    if (hp.s < 1 || hp.s > 16) return false;
+    int rt = 0, wave_cols = 0, most = 0;
+    history_shape(hp.s, hist_is_bf16(hp), hp.grad_dtype == NG_BF16, &rt, &wave_cols, &most);
+    for (int i = 0; i < n_mats; ++i) {
+        const int nbs = d[i].r <= 8 ? 0 : d[i].r <= 16 || rt == 2 ? 1 : 2;
+        const int rows = 8 << nbs, cols = wave_cols * (4 >> nbs), ldn = p->sz[i].ldn;
+        if ((long long)ceil_div(d[i].r, rows) * ceil_div(ldn, cols) > most) continue;
+        p->hist.push_back(TileRef{i, 0, 0, nbs << 2 | kHistorySolve});
+        int t = 0;
+        for (int ti = 0; ti < d[i].r; ti += rows)
+            for (int tj = 0; tj < ldn; tj += cols, ++t) p->hist.push_back(TileRef{i, ti, tj, t << 4 | nbs << 2 | kHistoryTile});
+        p->hist_tiles[i] = t;
+    }
+    return !p->hist.empty();
+}
 
 void make_plan(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* p) {
     p->sz.resize(n_mats);
@@ -242,8 +268,6 @@ void make_plan(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* 
             }
             cost_upd.resize(upd.size(), d[i].r);
         }
-        for (int ti = 0; ti < ceil_div(d[i].r, 32); ++ti)
-            for (int tj = 0; tj < ceil_div(z.ldn, kAdamPatchCols); ++tj) p->patches.push_back(TileRef{i, ti, tj, 0});
     }
     {
         std::vector<TileRef> a, b, c;
@@ -331,26 +355,51 @@ void make_plan(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* 
                 }
         }
     }
-    {
-        size_t so = align_up(sizeof(MatDyn) * (size_t)n_mats, 256);
-        p->step_tail8_off = so;
-        so += align_up((size_t)16 * (size_t)n_mats, 256);
-        p->step_parts_off.resize(n_mats);
-        p->step_proj_off.resize(n_mats);
+    // The step's scratch.  Partial sums per tile and the workgroups' meeting points take more of it than the plain Gram row's
+    // sums: where that would push a step out of the library's own array, the set keeps the separate launches.
+    p->step_tail8_off = align_up(sizeof(MatDyn) * (size_t)n_mats, 256);
+    p->step_parts_off.resize(n_mats);
+    p->step_proj_off.resize(n_mats);
+    p->sync_off.assign(n_mats, 0);
+    size_t plain = 0;
+    p->history = plan_history(d, n_mats, hp, p);
+    for (int pass = p->history ? 0 : 1; pass < 2; ++pass) {      // first without, to know whether it fits that way
+        size_t so = p->step_tail8_off + align_up((size_t)16 * (size_t)n_mats, 256);
+        p->step_sync_off = so;
+        if (p->history && pass == 1) {
+            for (int i = 0; i < n_mats; ++i) {
+                p->sync_off[i] = so;
+                so += sizeof(HistoryLine) * kHistoryLines + align_up((size_t)ceil_div(p->hist_tiles[i], 32) * 4, 256);
+            }
+        }
+        p->step_sync_bytes = so - p->step_sync_off;
+        so = align_up(so, 256);
         for (int i = 0; i < n_mats; ++i) {
+            const size_t tile_parts = p->history && pass == 1 ? align_up((size_t)p->hist_tiles[i] * hp.s * 8, 256) : 0;
             p->step_parts_off[i] = so;
-            so += p->sz[i].ws_parts;
+            so += p->sz[i].ws_parts > tile_parts ? p->sz[i].ws_parts : tile_parts;
             p->step_proj_off[i] = so;
             so += p->sz[i].ws_proj;
         }
         p->step_bytes = so;
+        if (pass == 0) plain = so;
+        else if (p->history && so > kStaticScratchBytes && plain <= kStaticScratchBytes) {
+            p->history = false;
+            p->hist.clear();
+            p->hist_tiles.assign(n_mats, 0);
+            pass = 0;
+        }
     }
+    for (int i = 0; i < n_mats; ++i)
+        for (int ti = 0; p->hist_tiles[i] == 0 && ti < ceil_div(d[i].r, 32); ++ti)
+            for (int tj = 0; tj < ceil_div(p->sz[i].ldn, kAdamPatchCols); ++tj) p->patches.push_back(TileRef{i, ti, tj, 0});
     p->off_step = off;   off += p->step_bytes;
     p->off_proj = off;   off += align_up(sizeof(TileRef) * p->proj.size(), 256);
     p->off_upd = off;    off += align_up(sizeof(TileRef) * p->upd.size(), 256);
     p->off_dots = off;   off += align_up(sizeof(TileRef) * (size_t)n_mats * kDotPartsMax, 256);
     p->off_patches = off; off += align_up(sizeof(TileRef) * p->patches.size(), 256);
     p->off_skinny = off;  off += align_up(sizeof(TileRef) * p->skinny.size(), 256);
+    p->off_hist = off;    off += align_up(sizeof(TileRef) * p->hist.size(), 256);
     p->off_sym = off;     off += align_up(sizeof(SymPlanes) * kSymOps * (size_t)n_mats, 256);
     for (int f = 0; f < 3; ++f) {
         p->off_sketch[f] = off;
@@ -383,9 +432,10 @@ struct ng_state {
     MatDev* d_mats;
     MatDyn* d_dyn;
     int* d_status;
-    TileRef *d_proj, *d_upd, *d_dots, *d_patches, *d_skinny, *d_sketch[3];
+    TileRef *d_proj, *d_upd, *d_dots, *d_patches, *d_skinny, *d_hist, *d_sketch[3];
+    unsigned history_wait;   // see launch_history
     SymPlanes* d_sym;   // [kSymOps][n_mats]
-    int n_dots;
+    int n_dots, n_dots_step;   // workgroups of the Gram row; of the matrices that a step has it for, which come first
     int max_m, max_n, max_r, max_l, max_lp, max_rows, max_ldn;
     int max_ti[OP_COUNT], max_tj[OP_COUNT], max_tk[OP_COUNT];   // largest M, N, K of each fp32 product
     int max_cut[OP_COUNT];                                      // most pieces its contraction is cut into
@@ -434,8 +484,8 @@ int upload_dyn(ng_state* st, MatDyn* dyn, const void* const* grads, void* const*
                 e.bc2 = 1.f;
             }
         }
-        NG_HIP(launch_upload_dyn(dyn, chunk, first, n,
-                                 st->hp.grad_dtype == NG_BF16 ? st->d_mats : nullptr, stream));
+        NG_HIP(launch_upload_dyn(dyn, chunk, first, n, st->hp.grad_dtype == NG_BF16 ? st->d_mats : nullptr,
+                                 st->plan.step_sync_off, stepping && first == 0 ? st->plan.step_sync_bytes : 0, stream));
     }
     return NG_OK;
 }
@@ -591,15 +641,22 @@ int step_on_scratch(ng_state* st, const void* const* grads, void* const* weights
     else if ((rc = gemm(st, OP_PROJECT_F32, stream, sc, dyn)) != NG_OK) return rc;
 
     if (prof) NG_HIP(hipEventRecord(st->ev[slot][NG_PHASE_GRAM], stream));
-    if (sc.use_fisher) NG_HIP(launch_gram_row(st->d_mats, dyn, st->d_dots, st->n_dots, sc.s, sc.hist_bf16, parts, -1, stream));
-    else if (parts) NG_HIP(launch_reduce_parts(st->d_mats, dyn, st->n_mats, st->max_ldn, st->max_r, stream));
+    // matrices of launch_history have their share of these three phases in the third
+    const bool separate = !st->plan.patches.empty();
+    if (separate && sc.use_fisher)
+        NG_HIP(launch_gram_row(st->d_mats, dyn, st->d_dots, st->n_dots_step, sc.s, sc.hist_bf16, parts, -1, stream));
+    else if (separate && parts) NG_HIP(launch_reduce_parts(st->d_mats, dyn, st->n_mats, st->max_ldn, st->max_r, stream));
 
     if (prof) NG_HIP(hipEventRecord(st->ev[slot][NG_PHASE_SOLVE], stream));
-    if (sc.use_fisher) NG_HIP(launch_solve(st->d_mats, dyn, 0, st->n_mats, sc, -1, st->d_status, stream));
+    if (separate && sc.use_fisher) NG_HIP(launch_solve(st->d_mats, dyn, 0, st->n_mats, sc, -1, st->d_status, stream));
 
     if (prof) NG_HIP(hipEventRecord(st->ev[slot][NG_PHASE_ADAM], stream));
-    NG_HIP(launch_transform_adam(st->d_mats, dyn, st->d_patches, (int)st->plan.patches.size(), sc,
-                                 st->hp.grad_dtype, st->d_status, stream));
+    if (separate)
+        NG_HIP(launch_transform_adam(st->d_mats, dyn, st->d_patches, (int)st->plan.patches.size(), sc,
+                                     st->hp.grad_dtype, st->d_status, stream));
+    if (st->plan.history)
+        NG_HIP(launch_history(st->d_mats, dyn, st->d_hist, (int)st->plan.hist.size(), sc, st->hp.grad_dtype, st->history_wait,
+                              st->d_status, stream));
 
     if (prof) NG_HIP(hipEventRecord(st->ev[slot][NG_PHASE_UPDATE], stream));
     if (skinny_rk) NG_HIP(launch_update_skinny(st->d_mats, dyn, st->d_skinny, (int)st->plan.skinny.size(), skinny_rk,
@@ -742,11 +799,13 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
         st->d_dots = (TileRef*)(ws + pl.off_dots);
         st->d_patches = (TileRef*)(ws + pl.off_patches);
         st->d_skinny = (TileRef*)(ws + pl.off_skinny);
+        st->d_hist = (TileRef*)(ws + pl.off_hist);
+        st->history_wait = kHistoryWait;
         st->d_sym = (SymPlanes*)(ws + pl.off_sym);
         for (int f = 0; f < 3; ++f) st->d_sketch[f] = (TileRef*)(ws + pl.off_sketch[f]);
 
         st->mats.resize(n_mats);
-        std::vector<TileRef> dots;
+        std::vector<TileRef> dots, dots_last;
         size_t off = pl.off_scratch;
         st->max_m = st->max_n = st->max_r = st->max_l = st->max_lp = st->max_rows = st->max_ldn = 0;
         st->max_jpairs = 0;
@@ -783,6 +842,8 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
             }
             md.tail8_off = hp->grad_dtype == NG_BF16 ? (long long)(pl.step_tail8_off + (size_t)16 * i) : -1;
             md.dot_parts_off = (long long)pl.step_parts_off[i];
+            md.hist_sync_off = (long long)pl.sync_off[i];
+            md.hist_tiles = pl.hist_tiles[i];
             md.proj_parts_off = z.ws_proj ? (long long)pl.step_proj_off[i] : -1;
             md.proj_chunks = z.proj_chunks;
             md.proj_rows = z.proj_rows;
@@ -814,7 +875,7 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
             md.dot_iters = (int)iters;
             md.dot_nparts = (int)((total4 + iters * 256 - 1) / (iters * 256));
             if (hp->s > 0)
-                for (int p = 0; p < md.dot_nparts; ++p) dots.push_back(TileRef{i, p, 0, 0});
+                for (int p = 0; p < md.dot_nparts; ++p) (md.hist_tiles ? dots_last : dots).push_back(TileRef{i, p, 0, 0});
             if (md.m > st->max_m) st->max_m = md.m;
             if (md.n > st->max_n) st->max_n = md.n;
             if (md.r > st->max_r) st->max_r = md.r;
@@ -834,6 +895,8 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
                 if (sym_index(op) < 0) st->tiles[op] += (long long)ceil_div(M, 128) * ceil_div(N, 128);
             }
         }
+        st->n_dots_step = (int)dots.size();
+        dots.insert(dots.end(), dots_last.begin(), dots_last.end());
         st->n_dots = (int)dots.size();
         // The contraction of a symmetric product is cut so that the set gives about 2048 workgroups of one
         // 128 x 128 tile each (eight per CU: their lengths differ by the matrices' row counts), but not
@@ -883,6 +946,8 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
             e = hipMemcpy(st->d_patches, pl.patches.data(), sizeof(TileRef) * pl.patches.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess && !pl.skinny.empty())
             e = hipMemcpy(st->d_skinny, pl.skinny.data(), sizeof(TileRef) * pl.skinny.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess && !pl.hist.empty())
+            e = hipMemcpy(st->d_hist, pl.hist.data(), sizeof(TileRef) * pl.hist.size(), hipMemcpyHostToDevice);
         for (int f = 0; f < 3; ++f)
             if (e == hipSuccess && !pl.sketch[f].empty())
                 e = hipMemcpy(st->d_sketch[f], pl.sketch[f].data(), sizeof(TileRef) * pl.sketch[f].size(), hipMemcpyHostToDevice);
@@ -1151,6 +1216,20 @@ size_t ng_struct_size(int which) {
         case 3: return sizeof(ng_matrix_layout);
         default: return 0;
     }
+}
+
+// Not in the header, for tests: how long a workgroup of launch_history waits before it gives way; 0 sends every tile
+// through the paths that otherwise only a crowded chip takes.
+int ng_debug_history_wait(ng_state* st, uint32_t ticks) {
+    if (!st) return NG_ERR_INVALID_ARG;
+    st->history_wait = ticks;
+    return NG_OK;
+}
+
+// Not in the header, for tests and the benchmark's accounting: tiles of a matrix in launch_history (0: it has the separate
+// launches).
+int ng_debug_history_tiles(const ng_state* st, int mat) {
+    return st && mat >= 0 && mat < st->n_mats ? st->plan.hist_tiles[mat] : -1;
 }
 
 void ng_destroy(ng_state* st) {

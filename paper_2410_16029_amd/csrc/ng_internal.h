@@ -82,6 +82,9 @@ struct MatDev {
     long long tail8_off;   // 8 bf16: the last gradient row's columns from the last multiple of 8 on,
                            // zero-padded (rewritten every step, see launch_upload_dyn)
     int lp;           // l rounded up to a whole number of Jacobi block pairs: order and row pitch of T, Linv
+    // k_history: place of the matrix's HistoryLines in the step's scratch, and its tiles (0: see k_gram_row)
+    long long hist_sync_off;
+    int hist_tiles;
 };
 
 // Per-step values: uploaded into the step's scratch block by a tiny kernel that receives them by value.
@@ -152,6 +155,23 @@ __device__ __forceinline__ T* step_scratch(const MatDyn* dyn, long long off) {
     return reinterpret_cast<T*>(reinterpret_cast<char*>(const_cast<MatDyn*>(dyn)) + off);
 }
 
+// What the workgroups of one matrix share in k_history, kHistoryLines lines per matrix; zeroed at the start of every step, as
+// are the bits behind them (one per tile: left to the workgroup that solves).  A workgroup counts itself in and looks for w
+// in line (tile mod kHistoryLines): hundreds of them on one line took turns there (4 to 9 ns a tile for the count alone).
+struct HistoryLine {
+    unsigned long long w[16];         // solved weights: the float, marked by a 1 above it (3: tiles have been left)
+    unsigned long long arrived_late;  // tiles of this line whose partial sums are in memory, and above, whether one was left
+    unsigned full;                    // line 0: lines whose tiles have all arrived
+    unsigned state;                   // line 0: kSolverGone or kAllThere, whichever came first
+    unsigned pad[28];
+};
+constexpr int kHistoryLines = 8;
+constexpr unsigned kSolverGone = 1, kAllThere = 2;
+constexpr unsigned kHistoryWait = 10000;   // 100 us, several times what the largest matrix takes to arrive
+// Items of k_history (TileRef): a tile (its first row and column, and in `pad` log2(bands) << 2 | tile << 4), or the solver of a
+// matrix.
+enum { kHistoryTile = 0, kHistorySolve = 1 };
+
 struct StepScalars {
     float lambda;
     float beta1, beta2, eps;
@@ -198,8 +218,9 @@ __host__ __device__ inline bool projection_tile_direct(int n) { return n >= 8; }
 // Every launcher enqueues on `stream` and returns hipGetLastError().
 
 // mats != null: also refresh MatDev::tail8 of the left-side matrices from the bf16 gradients in the chunk
+// zero_bytes (a multiple of 16) from byte zero_off of the block that the table starts are cleared
 hipError_t launch_upload_dyn(MatDyn* table, const DynChunk& chunk, int first, int n, const MatDev* mats,
-                             hipStream_t stream);
+                             size_t zero_off, size_t zero_bytes, hipStream_t stream);
 hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t stream);   // bytes % 4 == 0
 // zero the history ring and the Gram block of every matrix (buffer sizes as ng_query_sizes reports them)
 hipError_t launch_clear_history(const MatDev* mats, int n_mats, int s, int h_elem_bytes, size_t k_bytes,
@@ -333,6 +354,12 @@ hipError_t launch_gram_row(const MatDev* mats, const MatDyn* dyn, const TileRef*
                            int s, int hist_bf16, bool parts, int row_override, hipStream_t stream);
 hipError_t launch_solve(const MatDev* mats, const MatDyn* dyn, int first, int n_mats, StepScalars sc,
                         int row_override, int* status, hipStream_t stream);
+// Both passes over the history in one launch, s <= 16 (k_history.hip).  wait_ticks: 100 MHz ticks that a workgroup waits for
+// its matrix's weights before it leaves its tile to the one that solves.
+// history_shape: rows of a lane, columns of a wavefront, and the most tiles of a matrix that goes this way
+void history_shape(int s, int hist_bf16, int bf16_n, int* lane_rows, int* wave_cols, int* most_tiles);
+hipError_t launch_history(const MatDev* mats, const MatDyn* dyn, const TileRef* items, int n_items, StepScalars sc,
+                          int grad_dtype, unsigned wait_ticks, int* status, hipStream_t stream);
 hipError_t launch_save_projector(const MatDev* mats, int n_mats, hipStream_t stream);   // Yc <- P
 hipError_t launch_carry_store(const MatDev* mats, int n_mats, int slot, int hist_bf16, hipStream_t stream);
 hipError_t launch_transform_adam(const MatDev* mats, const MatDyn* dyn, const TileRef* patches, int n_patches,

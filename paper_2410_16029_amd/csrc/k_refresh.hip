@@ -519,6 +519,31 @@ __device__ __forceinline__ bool factor_diag(double* __restrict__ A, double* __re
     return bad;
 }
 
+// A workgroup's part of a ClearShare.  A CU stores 18 to 28 GB/s of zeros however many wavefronts it has at it, so a launch of
+// its own takes the whole chip to clear at 4.7 TB/s (350M set, 4.2 GB: 0.89 ms).  The Jacobi's rounds use next to no memory
+// bandwidth: beside 60 of them the refresh of that set takes 13.02 -> 12.00 ms.  Where the
+// visits leave CUs to spare, a round is the latency of one visit and the clearing is better beside the factors, which have one
+// workgroup per matrix (60M set 1663 -> 1658 us beside the rounds, 1672 -> 1642 beside seven factors; the
+// 350M set 12.55 ms beside the factors, whose 88 idle CUs and 195 us are not enough for it).
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void clear_share(const MatDev* __restrict__ mats, int n_mats, const ClearShare& cs, int block) {
+    constexpr int kPieces = 8;                   // of a matrix's share, one workgroup's work at a time
+    const u32x4_t zero = {0u, 0u, 0u, 0u};
+    for (int i = block; i < kPieces * n_mats; i += cs.blocks) {
+        const MatDev& md = mats[i / kPieces];
+        const unsigned long long n16 =
+            (((unsigned long long)md.slot_elems * (unsigned)cs.h_elem_bytes * (unsigned)(cs.s > 0 ? cs.s : 1) + 255ull) & ~255ull) / 16;
+        const unsigned piece = (unsigned)cs.part * kPieces + (unsigned)(i % kPieces), pieces = (unsigned)cs.parts * kPieces;
+        const unsigned long long last = n16 * (piece + 1) / pieces;
+        u32x4_t* __restrict__ h = reinterpret_cast<u32x4_t*>(md.H);
+        for (unsigned long long q = n16 * piece / pieces + threadIdx.x; q < last; q += blockDim.x) __builtin_nontemporal_store(zero, h + q);
+        if (piece == 0) {
+            u32x4_t* __restrict__ k = reinterpret_cast<u32x4_t*>(md.K);
+            for (unsigned long long q = threadIdx.x; q < cs.k_bytes / 16; q += blockDim.x) k[q] = zero;
+        }
+    }
+}
+
 //
 // FACTOR: the rows of L^T instead (zero below the diagonal and in the padding), where the Jacobi works on
 // them: the same elimination without its right-hand side.  Pivots are kept above a quarter of the shift.
@@ -527,7 +552,12 @@ __device__ __forceinline__ bool factor_diag(double* __restrict__ A, double* __re
 // 256 registers; orders up to 128 take 10 x 1, every block of a panel at work at once and a fraction of the code.
 template <bool FACTOR, int WAVES, int SLOTS>
 __global__ __launch_bounds__(64 * (WAVES + 1)) void k_inverse_factor(const MatDev* __restrict__ mats,
-                                                           const SymPlanes* __restrict__ sym, double shift_rel, int max_nb, int* status) {
+                                                           const SymPlanes* __restrict__ sym, double shift_rel, int max_nb,
+                                                           int n_mats, ClearShare share, int* status) {
+    if ((int)blockIdx.x >= n_mats) {
+        clear_share(mats, n_mats, share, (int)blockIdx.x - n_mats);
+        return;
+    }
     extern __shared__ __attribute__((aligned(16))) double fac_smem[];
     __shared__ double red[WAVES];
     const MatDev& md = mats[blockIdx.x];
@@ -752,7 +782,11 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void k_inverse_factor(const MatDe
 template <bool FACTOR>
 __global__ __launch_bounds__(64) void k_inverse_factor_small(const MatDev* __restrict__ mats,
                                                              const SymPlanes* __restrict__ sym,
-                                                             double shift_rel, int* status) {
+                                                             double shift_rel, int n_mats, ClearShare share, int* status) {
+    if ((int)blockIdx.x >= n_mats) {
+        clear_share(mats, n_mats, share, (int)blockIdx.x - n_mats);
+        return;
+    }
     __shared__ __attribute__((aligned(16))) double Am[kFacBlock], Dm[kFacBlock], Lt[FACTOR ? kFacBlock : 1];
     const MatDev& md = mats[blockIdx.x];
     const SymPlanes sp = sym[blockIdx.x];
@@ -808,32 +842,39 @@ __global__ __launch_bounds__(64) void k_inverse_factor_small(const MatDev* __res
 
 template <bool FACTOR, int WAVES, int SLOTS>
 static hipError_t run_factor_blocks(const MatDev* mats, const SymPlanes* sym, int n_mats, int nb, double shift_rel,
-                                    int* status, hipStream_t stream) {
+                                    const ClearShare& clear, int* status, hipStream_t stream) {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(k_inverse_factor<FACTOR, WAVES, SLOTS>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                                        2 * kFacNB * kFacBlock * (int)sizeof(double));
     (void)attr;
     const size_t lds = (size_t)2 * nb * kFacBlock * sizeof(double);
-    hipLaunchKernelGGL((k_inverse_factor<FACTOR, WAVES, SLOTS>), dim3(n_mats), dim3(64 * (WAVES + 1)), lds, stream, mats,
-                       sym, shift_rel, nb, status);
+    hipLaunchKernelGGL((k_inverse_factor<FACTOR, WAVES, SLOTS>), dim3(n_mats + clear.blocks), dim3(64 * (WAVES + 1)), lds,
+                       stream, mats, sym, shift_rel, nb, n_mats, clear, status);
     return hipGetLastError();
 }
 
 template <bool FACTOR>
 static hipError_t run_factor(const MatDev* mats, const SymPlanes* sym, int n_mats, int max_order, double shift_rel,
-                             int* status, hipStream_t stream) {
+                             const ClearShare& clear, int* status, hipStream_t stream) {
     if (max_order <= 32) {
-        hipLaunchKernelGGL(k_inverse_factor_small<FACTOR>, dim3(n_mats), dim3(64), 0, stream, mats, sym, shift_rel, status);
+        hipLaunchKernelGGL(k_inverse_factor_small<FACTOR>, dim3(n_mats + clear.blocks), dim3(64), 0, stream, mats, sym, shift_rel,
+                           n_mats, clear, status);
         return hipGetLastError();
     }
     const int nb = (max_order + 31) / 32;
-    if (nb <= 4) return run_factor_blocks<FACTOR, 10, 1>(mats, sym, n_mats, nb, shift_rel, status, stream);
-    return run_factor_blocks<FACTOR, 7, 6>(mats, sym, n_mats, nb, shift_rel, status, stream);
+    if (nb <= 4) return run_factor_blocks<FACTOR, 10, 1>(mats, sym, n_mats, nb, shift_rel, clear, status, stream);
+    return run_factor_blocks<FACTOR, 7, 6>(mats, sym, n_mats, nb, shift_rel, clear, status, stream);
+}
+
+int clear_share_blocks(int n_mats, int max_order, int max_pairs) {
+    if (max_order <= 32) return 512;             // (of one wavefront)
+    if (max_order > kFactorMax || (long long)n_mats * max_pairs > 512 || n_mats > 192) return 0;
+    return 256 - n_mats;
 }
 
 hipError_t launch_inverse_factor(GemmOp op, const MatDev* mats, const SymPlanes* sym, int n_mats, int max_order,
-                                 double shift_rel, int* status, hipStream_t stream) {
-    if (max_order <= kFactorMax) return run_factor<false>(mats, sym, n_mats, max_order, shift_rel, status, stream);
+                                 double shift_rel, ClearShare clear, int* status, hipStream_t stream) {
+    if (max_order <= kFactorMax) return run_factor<false>(mats, sym, n_mats, max_order, shift_rel, clear, status, stream);
     const int which = op == OP_GRAM_P ? 1 : 0;
     hipLaunchKernelGGL(k_sum_planes, dim3(64, n_mats), dim3(256), 0, stream, mats, sym);
     hipError_t e = launch_cholesky(mats, n_mats, which, max_order, shift_rel, false, status, stream);
@@ -892,7 +933,7 @@ hipError_t launch_jacobi_prepare(const MatDev* mats, const SymPlanes* sym, int n
                                  hipStream_t stream) {
     // the shift leaves the eigenvectors alone and covers the rounding of T; what it hides: see the comment on the rows
     constexpr double kShift = 1e-6;
-    if (max_l <= kFactorMax) return run_factor<true>(mats, sym, n_mats, max_l, kShift, status, stream);
+    if (max_l <= kFactorMax) return run_factor<true>(mats, sym, n_mats, max_l, kShift, ClearShare(), status, stream);
     hipLaunchKernelGGL(k_sum_planes, dim3(64, n_mats), dim3(256), 0, stream, mats, sym);
     const hipError_t e = launch_cholesky(mats, n_mats, 0, max_l, kShift, true, status, stream);
     if (e != hipSuccess) return e;
@@ -1414,8 +1455,12 @@ __device__ __forceinline__ int jacobi_visit(float* __restrict__ X, int lp, int b
 // of the sweep.
 template <int NW>
 __global__ __launch_bounds__(64 * NW, 3) void k_jacobi_round(const MatDev* __restrict__ mats, int n_mats, int pairs, bool local,
-                                                             int sweep, int round) {
+                                                             int sweep, int round, int visits, ClearShare share) {
     __shared__ __attribute__((aligned(16))) double smem[jacobi_visit_lds<NW>()];
+    if ((int)blockIdx.x >= visits) {
+        clear_share(mats, n_mats, share, (int)blockIdx.x - visits);
+        return;
+    }
     const int seq = (int)(local ? blockIdx.x >> 3 : blockIdx.x);
     const int mat = local ? seq / pairs * 8 + (int)(blockIdx.x & 7) : seq / pairs, pair = seq % pairs;
     if (mat >= n_mats) return;
@@ -1438,7 +1483,7 @@ __global__ __launch_bounds__(64 * NW, 3) void k_jacobi_round(const MatDev* __res
     //   5         144 of 256 6769 / 6756 / 7043, 96 of 384 18657 / 18534 / 19017
     //   6         168 of 256 6979 / 7004 / 7231, 84 of 512 30669 / 30689 / 30932
     //   8         256 of 256 9962 / 9787 / 9873
-    const int turn = (int)(blockIdx.x / 256), per_cu = (int)((gridDim.x + 255) / 256);
+    const int turn = (int)(blockIdx.x / 256), per_cu = (visits + 255) / 256;
     const int sweeper = NW == 2 ? per_cu != 4 && turn % 6 == 2 : turn % NW;
     const int nrot = jacobi_visit<NW>(jacobi_rows(md), lp, bp, bq, cross, sweeper, smem);
     if (nrot) atomicAdd(&md.jflag[sweep], nrot);
@@ -1474,9 +1519,10 @@ __global__ __launch_bounds__(256, 2) void k_jacobi_sweeps(const MatDev* __restri
     }
 }
 
-hipError_t launch_jacobi(const MatDev* mats, int n_mats, int max_pairs, int sweeps, hipStream_t stream) {
+hipError_t launch_jacobi(const MatDev* mats, int n_mats, int max_pairs, int sweeps, ClearShare clear, bool* cleared, hipStream_t stream) {
     if (max_pairs < 1) max_pairs = 1;
     int done = 0;
+    *cleared = false;
     if (max_pairs > 1) {
         // Sweeps needed, the last one without a rotation included, with 0 to 2 power passes on noise, signals of half and
         // of the full rank over floors of 1e-2 and 1e-4, graded and clustered columns, a single spike: at most 8 up
@@ -1489,14 +1535,22 @@ hipError_t launch_jacobi(const MatDev* mats, int n_mats, int max_pairs, int swee
         // change blocks every round); where that would load the XCDs unevenly beyond one visit per CU, they are spread.
         const int turns = (n_mats + 7) / 8;
         const bool local = turns * max_pairs <= 32 || turns * 8 <= n_mats + n_mats / 4;
-        const dim3 g(max_pairs * (local ? 8 * turns : n_mats));
+        const int visits = max_pairs * (local ? 8 * turns : n_mats);
         // Four wavefronts per visit where the visits leave CUs to spare (the products of a visit in half the
         // time), two otherwise (twice the visits per CU).
         const bool few = (long long)max_pairs * n_mats <= 512;
+        // The clearing, if there is some to do, goes beside the rounds of the first four sweeps, which nearly every matrix
+        // needs, in the places that the visits leave on the chip.
+        const int places = few ? 3 * 256 : 6 * 256, idle = (places - visits % places) % places;
+        clear.blocks = clear.parts == 0 || idle < 64 ? 0 : idle < 256 ? idle : 256;
+        clear.parts = (done < 4 ? done : 4) * (2 * max_pairs - 1);
+        *cleared = clear.blocks > 0;
         for (int sw = 0; sw < done; ++sw)
             for (int round = 0; round < 2 * max_pairs - 1; ++round) {
-                if (few) hipLaunchKernelGGL(k_jacobi_round<4>, g, dim3(256), 0, stream, mats, n_mats, max_pairs, local, sw, round);
-                else hipLaunchKernelGGL(k_jacobi_round<2>, g, dim3(128), 0, stream, mats, n_mats, max_pairs, local, sw, round);
+                clear.part = sw * (2 * max_pairs - 1) + round;
+                const dim3 g(visits + (clear.part < clear.parts ? clear.blocks : 0));
+                if (few) hipLaunchKernelGGL(k_jacobi_round<4>, g, dim3(256), 0, stream, mats, n_mats, max_pairs, local, sw, round, visits, clear);
+                else hipLaunchKernelGGL(k_jacobi_round<2>, g, dim3(128), 0, stream, mats, n_mats, max_pairs, local, sw, round, visits, clear);
             }
     }
     if (done < sweeps) hipLaunchKernelGGL(k_jacobi_sweeps, dim3(n_mats), dim3(256), 0, stream, mats, done, sweeps);

@@ -553,12 +553,13 @@ int gemm(ng_state* st, GemmOp op, hipStream_t stream, const StepScalars& sc, con
     return NG_OK;
 }
 
-// Linv <- inverse Cholesky factor of the symmetric product op
-int inverse_factor(ng_state* st, GemmOp op, double shift_rel, hipStream_t stream, const StepScalars& sc) {
+// Linv <- inverse Cholesky factor of the symmetric product op; the launch takes the next share of the clearing with it
+int inverse_factor(ng_state* st, GemmOp op, double shift_rel, hipStream_t stream, const StepScalars& sc, ClearShare* clear) {
     int rc;
     if ((rc = gemm(st, op, stream, sc)) != NG_OK) return rc;
-    NG_HIP(launch_inverse_factor(op, st->d_mats, planes_of(st, op), st->n_mats, st->max_ti[op], shift_rel,
+    NG_HIP(launch_inverse_factor(op, st->d_mats, planes_of(st, op), st->n_mats, st->max_ti[op], shift_rel, *clear,
                                  st->d_status, stream));
+    ++clear->part;
     return NG_OK;
 }
 
@@ -568,15 +569,15 @@ int inverse_factor(ng_state* st, GemmOp op, double shift_rel, hipStream_t stream
 //   twice = true : a second, unshifted pass repairs the first pass's loss of orthogonality and
 //                  puts the result back in X (the basis handed to the Rayleigh-Ritz step).
 // planes: what the product that reads the result next takes; one pass then leaves the planes only.
-int orthonormalise(ng_state* st, bool is_a, bool twice, int planes, hipStream_t stream, StepScalars sc) {
+int orthonormalise(ng_state* st, bool is_a, bool twice, int planes, hipStream_t stream, StepScalars sc, ClearShare* clear) {
     int rc;
     StepScalars result = sc;
     result.planes = st->plan.sketch_planes ? planes : 0;
     result.planes_only = !twice;
-    if ((rc = inverse_factor(st, is_a ? OP_GRAM_A : OP_GRAM_B, 2e-7, stream, sc)) != NG_OK) return rc;
+    if ((rc = inverse_factor(st, is_a ? OP_GRAM_A : OP_GRAM_B, 2e-7, stream, sc, clear)) != NG_OK) return rc;
     if ((rc = gemm(st, is_a ? OP_APPLY_A2C : OP_APPLY_B2C, stream, twice ? sc : result)) != NG_OK) return rc;
     if (!twice) return NG_OK;
-    if ((rc = inverse_factor(st, is_a ? OP_GRAM_CA : OP_GRAM_CB, 0.0, stream, sc)) != NG_OK) return rc;
+    if ((rc = inverse_factor(st, is_a ? OP_GRAM_CA : OP_GRAM_CB, 0.0, stream, sc, clear)) != NG_OK) return rc;
     if ((rc = gemm(st, is_a ? OP_APPLY_C2A : OP_APPLY_C2B, stream, result)) != NG_OK) return rc;
     return NG_OK;
 }
@@ -1006,27 +1007,44 @@ int ng_refresh_projector(ng_state* st, const void* const* grads, ng_stream strea
     NG_HIP(launch_fill_gaussian(st->d_mats, st->n_mats, st->max_n, st->plan.sketch_planes, st->hp.seed,
                                 (unsigned long long)st->n_refresh[0], stream));
     const int q = st->hp.refresh_power_iters;
+    const bool carry = st->hp.carry_history && st->hp.s > 0 && st->projector_valid;
+    // The history is cleared beside other work of the refresh, none of which touches it: beside the 2 q + 3 factors or the Jacobi's
+    // rounds.
+    ClearShare clear;
+    memset(&clear, 0, sizeof(clear));
+    clear.s = st->hp.s;
+    clear.h_elem_bytes = hist_is_bf16(st->hp) ? 2 : 4;
+    clear.k_bytes = st->plan.sz[0].bytes[NG_BUF_K];
+    bool cleared = false;
+    if (!carry) clear.blocks = clear_share_blocks(st->n_mats, st->max_l, st->max_jpairs);
+    if (clear.blocks > 0) {
+        clear.parts = 2 * q + 3;
+        cleared = true;
+    }
     if ((rc = gradient_product(st, OP_G_B2A, q == 0, stream, sc)) != NG_OK) return rc;
-    if ((rc = orthonormalise(st, true, q == 0, q == 0 ? 3 : 2, stream, sc)) != NG_OK) return rc;
+    if ((rc = orthonormalise(st, true, q == 0, q == 0 ? 3 : 2, stream, sc, &clear)) != NG_OK) return rc;
     for (int it = 0; it < q; ++it) {
         // intermediate bases live in Yc (single-pass orthonormalisation)
         if ((rc = gradient_product(st, OP_GT_C2B, false, stream, sc)) != NG_OK) return rc;
-        if ((rc = orthonormalise(st, false, false, sketch_planes(OP_G_C2A, it + 1 == q), stream, sc)) != NG_OK) return rc;
+        if ((rc = orthonormalise(st, false, false, sketch_planes(OP_G_C2A, it + 1 == q), stream, sc, &clear)) != NG_OK) return rc;
         if ((rc = gradient_product(st, OP_G_C2A, it + 1 == q, stream, sc)) != NG_OK) return rc;
-        if ((rc = orthonormalise(st, true, it + 1 == q, it + 1 == q ? 3 : 2, stream, sc)) != NG_OK) return rc;
+        if ((rc = orthonormalise(st, true, it + 1 == q, it + 1 == q ? 3 : 2, stream, sc, &clear)) != NG_OK) return rc;
     }
     // Rayleigh-Ritz: B = Q^T G, T = B B^T = U diag(ritz^2) U^T, P = Q U[:, top r]
     if ((rc = gradient_product(st, OP_QT_G, true, stream, sc)) != NG_OK) return rc;
     if ((rc = gemm(st, OP_B_BT, stream, sc)) != NG_OK) return rc;
     NG_HIP(launch_jacobi_prepare(st->d_mats, planes_of(st, OP_B_BT), st->n_mats, st->max_l, st->max_lp, st->d_status, stream));
-    NG_HIP(launch_jacobi(st->d_mats, st->n_mats, st->max_jpairs, st->hp.refresh_sweeps, stream));
+    ClearShare beside = clear;
+    beside.parts = !carry && !cleared ? 1 : 0;
+    bool by_jacobi = false;
+    NG_HIP(launch_jacobi(st->d_mats, st->n_mats, st->max_jpairs, st->hp.refresh_sweeps, beside, &by_jacobi, stream));
+    cleared = cleared || by_jacobi;
     NG_HIP(launch_jacobi_finish(st->d_mats, st->n_mats, st->hp.refresh_sweeps, st->d_status, stream));
     // history carry-over needs the outgoing projector: keep it in Yc (free from here on)
-    const bool carry = st->hp.carry_history && st->hp.s > 0 && st->projector_valid;
     if (carry) NG_HIP(launch_save_projector(st->d_mats, st->n_mats, stream));
     if ((rc = gemm(st, OP_ROTATE, stream, sc)) != NG_OK) return rc;
     // one CholeskyQR pass on P (m x r) restores orthonormality to rounding level, then fix signs
-    if ((rc = inverse_factor(st, OP_GRAM_P, 0.0, stream, sc)) != NG_OK) return rc;
+    if ((rc = inverse_factor(st, OP_GRAM_P, 0.0, stream, sc, &clear)) != NG_OK) return rc;
     if ((rc = gemm(st, OP_APPLY_P2A, stream, sc)) != NG_OK) return rc;
     NG_HIP(launch_sign_fix(st->d_mats, st->n_mats, st->max_r, stream));
 
@@ -1044,7 +1062,7 @@ int ng_refresh_projector(ng_state* st, const void* const* grads, ng_stream strea
             NG_HIP(launch_solve(st->d_mats, st->d_dyn, 0, st->n_mats, sc, row, st->d_status, stream));
         }
     }
-    if ((rc = finish_projector(st, !carry, true, stream)) != NG_OK) return rc;
+    if ((rc = finish_projector(st, !carry && !cleared, true, stream)) != NG_OK) return rc;
     st->projector_valid = true;
     for (int i = 0; i < st->n_mats; ++i) {
         if (!carry) {

@@ -381,19 +381,30 @@ __host__ __device__ inline int ritz_place(const double* v, int n, int i) {
     return place;
 }
 
+// Part `part` of `parts` of clearing the history ring of every matrix (and, in the first, the Gram blocks), done by extra
+// workgroups of a launch that leaves units and memory idle; parts == 0: none.
+struct ClearShare {
+    int part, parts, blocks;
+    int s, h_elem_bytes;
+    unsigned long long k_bytes;
+};
+
 // refresh helpers (k_refresh.hip)
 // fills Yb (n x l), or, where a matrix has sketch planes, the first of them with the same values rounded to bf16
 hipError_t launch_fill_gaussian(const MatDev* mats, int n_mats, int max_rows, bool planes, unsigned long long seed,
                                 unsigned long long call_id, hipStream_t stream);
 // Linv = inverse Cholesky factor of the symmetric product `op` (its planes, plus shift_rel * trace on the
-// diagonal)
+// diagonal).  clear: beside orders up to kFactorMax only
 hipError_t launch_inverse_factor(GemmOp op, const MatDev* mats, const SymPlanes* sym, int n_mats, int max_order,
-                                 double shift_rel, int* status, hipStream_t stream);
+                                 double shift_rel, ClearShare clear, int* status, hipStream_t stream);
+// extra workgroups of those launches that clearing is to have; 0 where it is better elsewhere
+int clear_share_blocks(int n_mats, int max_order, int max_pairs);
 // the rows that the Jacobi starts from: L^T of T = B B^T = L L^T (planes of OP_B_BT)
 hipError_t launch_jacobi_prepare(const MatDev* mats, const SymPlanes* sym, int n_mats, int max_l, int max_lp, int* status,
                                  hipStream_t stream);
 // up to `sweeps` (1 .. 64) sweeps over every matrix, each matrix until one of its sweeps rotates nothing
-hipError_t launch_jacobi(const MatDev* mats, int n_mats, int max_pairs, int sweeps, hipStream_t stream);
+// clear.parts != 0: something is to be cleared; *cleared tells whether it was
+hipError_t launch_jacobi(const MatDev* mats, int n_mats, int max_pairs, int sweeps, ClearShare clear, bool* cleared, hipStream_t stream);
 hipError_t launch_jacobi_finish(const MatDev* mats, int n_mats, int sweeps, int* status, hipStream_t stream);
 hipError_t launch_sign_fix(const MatDev* mats, int n_mats, int max_r, hipStream_t stream);
 

@@ -953,7 +953,7 @@ hipError_t launch_jacobi_prepare(const MatDev* mats, const SymPlanes* sym, int n
 //   X <- V X           fp64 MFMA, each wavefront owns 16-column tiles, written straight back to memory
 // so the 32 rows are read twice per visit instead of 2 x 31 times.
 //
-// The small sweep is a chain of dependent rounds, and one wavefront runs it in registers; a second one follows
+// The small sweep is a chain of dependent rounds, and one wavefront (two where there are four: SweepHalf) runs it in registers; another one follows
 // it round by round and accumulates V.  (With S and V in LDS and eight wavefronts a round was two barriers
 // and 14 LDS accesses per thread, 0.7 us.)  The rounds go through the pairs (i, i xor x).  A phase is the
 // x with highest bit f: the 16 indexes with bit f clear are "lower", the others "upper", both numbered by
@@ -1140,6 +1140,18 @@ __device__ __forceinline__ void sweep_barrier() { asm volatile("s_waitcnt lgkmcn
 // Coefficients of a round in LDS: p, q of the 16 pairs, then their tangents.
 constexpr int kJgRoundCoef = 48;
 
+// lanes with the bit set give their lower column to, and take the upper column of, the lane without it
+template <int A, int B>
+__device__ __forceinline__ void exchange_pair(double& lo, double& up, bool set) {
+    double pl = dpp_d<A>(lo), pu = dpp_d<A>(up);
+    if (B != 0) {
+        pl = dpp_d<B ? B : A>(pl);
+        pu = dpp_d<B ? B : A>(pu);
+    }
+    lo = set ? pu : lo;
+    up = set ? up : pl;
+}
+
 // The wavefront that runs the sweep on S.
 struct SweepMain {
     JacobiRows S;
@@ -1227,17 +1239,6 @@ struct SweepMain {
     }
     template <int LOW, int BIT>
     __device__ __forceinline__ void next_group() { S.template next_group<LOW, BIT>(z); }
-    // lanes with the bit set give their lower column to, and take the upper column of, the lane without it
-    template <int A, int B>
-    __device__ __forceinline__ void exchange_pair(double& lo, double& up, bool set) {
-        double pl = dpp_d<A>(lo), pu = dpp_d<A>(up);
-        if (B != 0) {
-            pl = dpp_d<B ? B : A>(pl);
-            pu = dpp_d<B ? B : A>(pu);
-        }
-        lo = set ? pu : lo;
-        up = set ? up : pl;
-    }
     template <int A, int B>
     __device__ __forceinline__ void exchange_columns(bool set) {
 #pragma unroll
@@ -1264,7 +1265,184 @@ struct SweepMain {
     }
 };
 
-// The wavefront that accumulates V: lane (k, z) holds columns k and 16 + k.
+// Where a visit has wavefronts to spare (NW = 4), two run the sweep, eight of the sixteen row pairs each: a round is the latency
+// of one wavefront's chain and issue, and half of its rows is half of its multiply-adds, moves and selections.
+// Wavefront h holds the rows 8 h + 2 z + i, lower and upper, i = 0, 1: bit 0 of a row's number is the register, bits 1 and 2
+// are the row of 16 lanes and bit 3 the wavefront.  So what SweepMain does with register bit 1 is an exchange between rows of
+// 16 lanes here, what it does with z bit 1 one between the wavefronts, through LDS; both wavefronts hold all
+// columns and keep the scales.  The rotations are the same, bit for bit.  (Refresh of
+// the 60M set 1658 -> 1615 us, of one 32-row matrix 344 -> 340.  What is left of a round, some 1000 cycles, is the way of
+// the coefficients: 110 to write them to LDS, 75 at the barrier, 290 to read them, against 100 for the multiply-adds; without
+// the tangent's divisions, or without the accumulation of V, it takes as long.)
+struct SweepHalf {
+    double lo[2][2], up[2][2];
+    double scl, scu, iscl, iscu;
+    double smax;
+    double* rc;
+    double* xbuf;                     // [2 wavefronts][4][64]
+    int k, z, h, nrot;
+
+    __device__ __forceinline__ void init(const double* S0, double* coef, double* exchange_buffer, bool cross, int lane, int half) {
+        k = lane & 15;
+        z = lane >> 4;
+        h = half;
+        rc = coef;
+        xbuf = exchange_buffer;
+        nrot = 0;
+        scl = scu = iscl = iscu = 1.0;
+        const int f = cross ? 4 : 0;
+        const int cl = jacobi_index(f, k, 0), cu = jacobi_index(f, k, 1);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const double* rl = S0 + jacobi_index(f, 8 * h + 2 * z + i, 0) * kJgLd;
+            const double* ru = S0 + jacobi_index(f, 8 * h + 2 * z + i, 1) * kJgLd;
+            lo[i][0] = rl[cl];
+            lo[i][1] = rl[cu];
+            up[i][0] = ru[cl];
+            up[i][1] = ru[cu];
+        }
+        smax = S0[(lane & 31) * kJgLd + (lane & 31)];
+#pragma unroll
+        for (int off = 16; off > 0; off >>= 1) smax = fmax(smax, __shfl_xor(smax, off, 64));
+    }
+    template <int BIT>
+    __device__ __forceinline__ void flip() {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) up[i][c] = row_flip<BIT>(up[i][c], z);
+    }
+    // these four values of a lane change places with the other wavefront's
+    __device__ __forceinline__ void trade(double (&mine)[2][2]) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) xbuf[256 * h + 64 * v + 16 * z + k] = mine[v >> 1][v & 1];
+        sweep_barrier();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) mine[v >> 1][v & 1] = xbuf[256 * (1 - h) + 64 * v + 16 * z + k];
+    }
+    template <int R>
+    __device__ __forceinline__ void round() {
+        constexpr int X = R & 1;
+        if (R == 3) flip<0>();                       // rounds 0 1 3 2: bit 1 is set from here on
+        const bool k0 = k & 1;
+        const double ee = scl * scu;
+        const double ga = ee * select_d(k0, up[1 ^ X][0], up[0 ^ X][0]);
+        const double al = scl * scl * select_d(k0, lo[1][0], lo[0][0]);
+        const double be = scu * scu * select_d(k0, up[1 ^ X][1], up[0 ^ X][1]);
+        const bool rotate = (al > 0.0) && (be > 0.0) && (ga * ga > 1.0e-15 * al * be);
+        double tn = rotation_tan(al, be, ga);
+        tn = rotate ? tn : 0.0;
+        const bool owner = z == ((k >> 1) & 3) && h == (k >> 3);
+        if (owner) {
+            rc[2 * k] = tn * (scu * iscl);
+            rc[2 * k + 1] = tn * (scl * iscu);
+            rc[32 + k] = tn;
+        }
+        sweep_barrier();
+        if (owner && rotate && fabs(ga) > 8.0e-15 * smax && ga * ga > 1.0e-7 * al * be) ++nrot;   // (as SweepMain)
+        double p[2], q[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            p[i] = rc[2 * (8 * h + 2 * z + i)];
+            q[i] = rc[2 * (8 * h + 2 * z + i) + 1];
+        }
+        const double pc = rc[2 * k], qc = rc[2 * k + 1], t = rc[32 + k];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const double l = fma(-p[i], up[i ^ X][c], lo[i][c]);
+                up[i ^ X][c] = fma(q[i], lo[i][c], up[i ^ X][c]);
+                lo[i][c] = l;
+            }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const double l = fma(-pc, lo[i][1], lo[i][0]), u = fma(-pc, up[i][1], up[i][0]);
+            lo[i][1] = fma(qc, lo[i][0], lo[i][1]);
+            up[i][1] = fma(qc, up[i][0], up[i][1]);
+            lo[i][0] = l;
+            up[i][0] = u;
+        }
+        const double c2 = fma(t, t, 1.0), c = rsq_nr(c2), ic = c2 * c;
+        scl *= c;
+        scu *= c;
+        iscl *= ic;
+        iscu *= ic;
+        rc += kJgRoundCoef;
+    }
+    template <int CTRL>
+    __device__ __forceinline__ void step() {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            lo[i][1] = dpp_d<CTRL>(lo[i][1]);
+            up[i][1] = dpp_d<CTRL>(up[i][1]);
+        }
+        scu = dpp_d<CTRL>(scu);
+        iscu = dpp_d<CTRL>(iscu);
+    }
+    template <int LOW, int BIT>
+    __device__ __forceinline__ void next_group() {
+        if (LOW == 0) {                              // bits 0 and 2; bit 1 back from rounds 3 and 2
+#pragma unroll
+            for (int c = 0; c < 2; ++c) swap_d(up[0][c], up[1][c]);
+            flip<0>();
+            flip<1>();
+        } else {                                     // bits 1, which rounds 3 and 2 have set, and 3
+            trade(up);
+        }
+    }
+    template <int A, int B>
+    __device__ __forceinline__ void exchange_columns(bool set) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            exchange_pair<A, B>(lo[i][0], lo[i][1], set);
+            exchange_pair<A, B>(up[i][0], up[i][1], set);
+        }
+        exchange_pair<A, B>(scl, scu, set);
+        exchange_pair<A, B>(iscl, iscu, set);
+    }
+    __device__ __forceinline__ void exchange(int f) {
+        const bool set = (k >> f) & 1;
+        if (f == 0) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c) swap_d(lo[1][c], up[0][c]);
+            exchange_columns<kDppXor1, 0>(set);
+        } else if (f == 1) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) row_swap<0>(lo[i][c], up[i][c]);
+            exchange_columns<kDppXor2, 0>(set);
+        } else if (f == 2) {
+            flip<0>();                               // bit 1 back from rounds 3 and 2
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) row_swap<1>(lo[i][c], up[i][c]);
+            exchange_columns<kDppXor7, kDppXor3>(set);
+        } else {
+            double mine[2][2];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) mine[v >> 1][v & 1] = select_d(h == 0, up[v >> 1][v & 1], lo[v >> 1][v & 1]);
+            trade(mine);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                up[v >> 1][v & 1] = select_d(h == 0, mine[v >> 1][v & 1], up[v >> 1][v & 1]);
+                lo[v >> 1][v & 1] = select_d(h == 0, lo[v >> 1][v & 1], mine[v >> 1][v & 1]);
+            }
+            exchange_columns<kDppXor8, 0>(set);
+        }
+    }
+    __device__ __forceinline__ void finish(double* scales) const {      // phase 4 ended at g = 8
+        if (h == 0 && z == 0) {
+            scales[k] = scl;
+            scales[16 + (k ^ 8)] = scu;
+        }
+    }
+};
+
+// The wavefront that accumulates V: lane (k, z) holds columns k and 16 + k.  SPLIT: beside two SweepHalf, whose barriers it joins.
+template <bool SPLIT>
 struct SweepVectors {
     JacobiRows V;
     const double* rc;
@@ -1297,8 +1475,14 @@ struct SweepVectors {
     template <int CTRL>
     __device__ __forceinline__ void step() {}
     template <int LOW, int BIT>
-    __device__ __forceinline__ void next_group() { V.template next_group<LOW, BIT>(z); }
-    __device__ __forceinline__ void exchange(int f) { V.exchange_rows(f); }
+    __device__ __forceinline__ void next_group() {
+        if (SPLIT && LOW == 1) sweep_barrier();
+        V.template next_group<LOW, BIT>(z);
+    }
+    __device__ __forceinline__ void exchange(int f) {
+        if (SPLIT && f == 3) sweep_barrier();
+        V.exchange_rows(f);
+    }
     __device__ __forceinline__ void store(double* Vout, const double* scales) const {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -1393,21 +1577,29 @@ __device__ __forceinline__ int jacobi_visit(float* __restrict__ X, int lp, int b
     __syncthreads();
     int nrot = 0;
     double* scales = coef + kJgRounds * kJgRoundCoef;
-    if (wv == sweeper) {
+    constexpr bool kSplit = NW == 4;
+    if (wv == (sweeper + 1) % NW) {
+        SweepVectors<kSplit> v;
+        v.init(coef, cross, lane);
+        jacobi_rounds(v, cross);
+        __syncthreads();
+        v.store(smem, scales);
+    } else if (kSplit && (wv == sweeper || wv == (sweeper + 2) % NW)) {
+        SweepHalf m;
+        m.init(smem, coef, smem + 32 * kJgLd, cross, lane, wv == sweeper ? 0 : 1);
+        jacobi_rounds(m, cross);
+        m.finish(scales);
+        nrot = m.nrot;
+        __syncthreads();
+    } else if (!kSplit) {
         SweepMain m;
         m.init(smem, coef, cross, lane);
         jacobi_rounds(m, cross);
         m.finish(scales);
         nrot = m.nrot;
         __syncthreads();
-    } else if (wv == (sweeper + 1) % NW) {
-        SweepVectors v;
-        v.init(coef, cross, lane);
-        jacobi_rounds(v, cross);
-        __syncthreads();
-        v.store(smem, scales);
     } else {
-        for (int n = cross ? 16 : kJgRounds; n > 0; --n) sweep_barrier();
+        for (int n = cross ? 17 : kJgRounds + 2; n > 0; --n) sweep_barrier();
         __syncthreads();
     }
     __syncthreads();

@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "ng_internal.h"
+#include "split_bf16.h"
 
 namespace ng {
 
@@ -206,24 +207,9 @@ __device__ __forceinline__ f32x4_t load4(const NG_AS1 unsigned char* p) {
 // MFMA's, at three eighths of its matrix-core time.
 // A gradient (or history slot) stored as bf16 has one plane.
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
 constexpr float kSplitUp = 65536.f;
-
-// the NP planes of two values, a in the low halves
-template <int NP>
-__device__ __forceinline__ void split2(float a, float b, unsigned (&p)[NP]) {
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        const f32x2_t f = {a, b};
-        const bf16x2_t hv = __builtin_convertvector(f, bf16x2_t);      // v_cvt_pk_bf16_f32: nearest even
-        p[i] = *reinterpret_cast<const unsigned int*>(&hv);
-        a -= __uint_as_float(p[i] << 16);
-        b -= __uint_as_float(p[i] & 0xffff0000u);
-    }
-}
 
 // One operand of a tile: T (tile index) x K (contraction), TS x BK per k-step, moved as vectors of four
 // elements along the stride-1 dimension -- the tile index (TF) or the contraction -- and kept in LDS as NP planes

@@ -17,6 +17,7 @@
 //                       column made positive
 #include "eliminate16.h"
 #include "ng_internal.h"
+#include "split_bf16.h"
 
 namespace ng {
 
@@ -840,6 +841,241 @@ __global__ __launch_bounds__(64) void k_inverse_factor_small(const MatDev* __res
     }
 }
 
+// CholeskyQR of a sketch of up to 32 columns in one launch, a workgroup per matrix: X (rows x nn) becomes X L^{-T}, where
+// X^T X (+ shift on the diagonal) = L L^T, once or twice over.  Each pass reads the sketch twice, once as the rows that a
+// lane group contracts over and once as the rows of a result; kOrthoWaves wavefronts take 32 rows at a time for both
+// products, another one the factor in between, during which the first rows for the second product are on their way.
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+
+constexpr int kOrthoWaves = 8;
+
+// The arithmetic of both products: fp64 for the last basis and the new projector, fp32 for the bases inside the subspace
+// iteration, which have to stay apart and no more.  (With fp32 throughout the projector of a 256 x 512 gradient was 4.66e-7
+// from the exact one, a root mean square over eight draws; with products of three bf16 planes, which round once per 16
+// products and not once per product, 4.58e-7.  A 16 x 16 x 4 product is 64 cycles in fp64, 32 in fp32.)
+// row_of: the row of a result's 16 that element e of lane group g holds.
+template <bool EXACT>
+struct OrthoMath {
+    using T = double;
+    using T4 = double4_t;
+    static __device__ __forceinline__ T4 mul(double a, double b, T4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+    static __device__ __forceinline__ int row_of(int e, int g) { return 4 * e + g; }
+};
+template <>
+struct OrthoMath<false> {
+    using T = float;
+    using T4 = f32x4_t;
+    static __device__ __forceinline__ T4 mul(float a, float b, T4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+    static __device__ __forceinline__ int row_of(int e, int g) { return 4 * g + e; }
+};
+
+// A chunk's 32 rows as the two products take them, zero past the last row and column.  (Its start and the steps to its
+// rows are the same for every lane: one address in scalar registers per load and one offset per lane.)
+// rows 16 x + 4 g + e, columns c + 16 t: what the Gram matrix is contracted over
+__device__ __forceinline__ void ortho_gram_rows(const float* src, int row0, int rows, int nn, int c, int g, float (&y)[2][4][2]) {
+    const unsigned at[2] = {(unsigned)(4 * g * nn + (c < nn ? c : 0)), (unsigned)(4 * g * nn + (c + 16 < nn ? c + 16 : 0))};
+    if (row0 + 32 <= rows) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) y[x][e][t] = (src + (row0 + 16 * x + e) * nn)[at[t]];
+    } else {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const bool in = row0 + 16 * x + 4 * g + e < rows;
+                    const float q = in ? (src + (row0 + 16 * x + e) * nn)[at[t]] : 0.f;
+                    y[x][e][t] = q;
+                }
+    }
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) y[x][e][t] = c + 16 * t < nn ? y[x][e][t] : 0.f;
+}
+
+// rows 16 x + c, columns 16 h + 4 g + u: what the second product multiplies; in fp64 row 4 (c % 4) + c / 4 in place of c, which
+// makes the four results of a lane consecutive rows there as well
+template <bool EXACT>
+__device__ __forceinline__ void ortho_rows(const float* src, int row0, int rows, int nn, int lane_c, int g, f32x4_t (&y)[2][2]) {
+    const int c = EXACT ? 4 * (lane_c & 3) + (lane_c >> 2) : lane_c;
+    if ((nn & 3) == 0) {                     // (uniform)
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const bool in = row0 + 16 * x + c < rows && 16 * h + 4 * g < nn;
+                const unsigned at = (unsigned)(in ? (16 * x + c) * nn + 16 * h + 4 * g : 0);
+                const f32x4_t q = *reinterpret_cast<const f32x4_t*>(src + row0 * nn + at);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) y[x][h][u] = in ? q[u] : 0.f;
+            }
+    } else {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const bool in = row0 + 16 * x + c < rows && 16 * h + 4 * g + u < nn;
+                    const unsigned at = (unsigned)(in ? (16 * x + c) * nn + 16 * h + 4 * g + u : 0);
+                    const float q = (src + row0 * nn)[at];
+                    y[x][h][u] = in ? q : 0.f;
+                }
+    }
+}
+
+// Rows row0, row0 + 32 kOrthoWaves, ... of src times L^{-T} (Dm: L^{-1}); y: the first 32 of them.
+template <bool EXACT>
+__device__ __forceinline__ void ortho_apply(const MatDev& md, const double* Dm, const float* src, float* dst, int row0, int rows, int nn,
+                                            int c, int g, int np, bool twice, f32x4_t (&y)[2][2]) {
+    using M = OrthoMath<EXACT>;
+    using T = typename M::T;
+    // element (k, j) of L^{-T}, k = 16 h + 4 g + u, j = c (+ 16): zero below the diagonal
+    T b0[4], b1[2][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        b0[u] = 4 * g + u <= c ? (T)Dm[c * kFacPitch + 4 * g + u] : (T)0;
+        b1[0][u] = (T)Dm[(16 + c) * kFacPitch + 4 * g + u];
+        b1[1][u] = 4 * g + u <= c ? (T)Dm[(16 + c) * kFacPitch + 16 + 4 * g + u] : (T)0;
+    }
+    for (; row0 < rows; row0 += 32 * kOrthoWaves) {
+        f32x4_t next[2][2];
+        if (row0 + 32 * kOrthoWaves < rows) ortho_rows<EXACT>(src, row0 + 32 * kOrthoWaves, rows, nn, c, g, next);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            typename M::T4 q[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                q[0] = M::mul(y[x][0][u], b0[u], q[0]);
+                q[1] = M::mul(y[x][0][u], b1[0][u], q[1]);
+                q[1] = M::mul(y[x][1][u], b1[1][u], q[1]);
+            }
+            const int r0 = row0 + 16 * x + 4 * g;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int col = c + 16 * t;
+                float z[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) z[e] = (float)q[t][e];
+                if (np > 0 && col < nn && (r0 & ~7) < rows) {
+                    // half an octet of a sketch plane, rows past the last zero
+                    unsigned lo[3], hi[3];
+                    split2<3>(r0 < rows ? z[0] : 0.f, r0 + 1 < rows ? z[1] : 0.f, lo);
+                    split2<3>(r0 + 2 < rows ? z[2] : 0.f, r0 + 3 < rows ? z[3] : 0.f, hi);
+                    const long long at = ((long long)(r0 >> 3) * nn + col) * 8 + (r0 & 4);
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+                        if (p < np) *reinterpret_cast<u32x2_t*>(sketch_plane(md, twice, p) + at) = (u32x2_t){lo[p], hi[p]};
+                }
+                if (np == 0 || twice) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (r0 + e < rows && col < nn) (dst + (row0 + 16 * x + e) * nn)[(unsigned)(4 * g * nn + col)] = z[e];
+                }
+            }
+            y[x][0] = next[x][0];
+            y[x][1] = next[x][1];
+        }
+    }
+}
+
+template <bool EXACT>
+__global__ __launch_bounds__(64 * (kOrthoWaves + 1)) void k_orthonormalise_small(const MatDev* __restrict__ mats, int which, int passes,
+                                                                                 double shift_rel, int planes, int n_mats,
+                                                                                 ClearShare share, int* status) {
+    if ((int)blockIdx.x >= n_mats) {
+        clear_share(mats, n_mats, share, (int)blockIdx.x - n_mats);
+        return;
+    }
+    __shared__ __attribute__((aligned(16))) double Am[kFacBlock], sums[kOrthoWaves * 3 * 256 * sizeof(typename OrthoMath<EXACT>::T) / sizeof(double)];
+    using M = OrthoMath<EXACT>;
+    using T = typename M::T;
+    T* const part = reinterpret_cast<T*>(sums);      // [kOrthoWaves][3][256]
+    double* const Dm = sums;                 // (the partial sums are in Am by the time the factor is written)
+    static_assert(sizeof(sums) >= kFacBlock * sizeof(double), "");
+    const MatDev& md = mats[blockIdx.x];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4;
+    const int nn = which == kOrthoP ? md.r : md.l, rows = which == kOrthoB ? md.n : md.m;
+    float* const first = which == kOrthoP ? md.P : which == kOrthoB ? md.Yb : md.Ya;
+    float* const other = which == kOrthoP ? md.Ya : md.Yc;
+    if (w == kOrthoWaves) {
+        for (int pass = 0; pass < passes; ++pass) {
+            __syncthreads();
+            __syncthreads();
+            if (pass == 0 && shift_rel > 0.0) {
+                const double d = lane < nn ? Am[lane * (kFacPitch + 1)] : 0.0;
+                double tr = d;
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) tr += __shfl_xor(tr, off, 64);
+                if (lane < nn) Am[lane * (kFacPitch + 1)] = d + shift_rel * tr;
+                lds_order();
+            }
+            if (factor_diag<false>(Am, Dm, nullptr, 0.0, lane) && lane == 0) atomicOr(status, 4);
+            __syncthreads();
+            __syncthreads();
+        }
+        return;
+    }
+    for (int pass = 0; pass < passes; ++pass) {
+        const float* src = pass ? other : first;
+        float* dst = pass ? first : other;
+        typename M::T4 g00 = {0, 0, 0, 0}, g10 = g00, g11 = g00;
+        for (int row0 = 32 * w; row0 < rows; row0 += 32 * kOrthoWaves) {
+            float y[2][4][2];
+            ortho_gram_rows(src, row0, rows, nn, c, g, y);
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    g00 = M::mul(y[x][e][0], y[x][e][0], g00);
+                    g10 = M::mul(y[x][e][1], y[x][e][0], g10);
+                    g11 = M::mul(y[x][e][1], y[x][e][1], g11);
+                }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            part[768 * w + 64 * e + lane] = g00[e];
+            part[768 * w + 256 + 64 * e + lane] = g10[e];
+            part[768 * w + 512 + 64 * e + lane] = g11[e];
+        }
+        __syncthreads();
+        for (int i = tid; i < 3 * 256; i += 64 * kOrthoWaves) {
+            double sum = 0.0;
+#pragma unroll
+            for (int q = 0; q < kOrthoWaves; ++q) sum += (double)part[768 * q + i];
+            const int row = (i >= 256 ? 16 : 0) + M::row_of((i & 255) >> 6, (i & 63) >> 4), col = (i >= 512 ? 16 : 0) + (i & 15);
+            Am[row * kFacPitch + col] = row < nn && col < nn ? sum : row == col ? 1.0 : 0.0;      // identity past the order
+        }
+        __syncthreads();
+        f32x4_t y[2][2];
+        if (32 * w < rows) ortho_rows<EXACT>(src, 32 * w, rows, nn, c, g, y);
+        __syncthreads();
+        const int np = pass + 1 == passes && md.Yp != nullptr ? planes : 0;
+        ortho_apply<EXACT>(md, Dm, src, dst, 32 * w, rows, nn, c, g, np, passes == 2, y);
+        __syncthreads();
+    }
+}
+
+hipError_t launch_orthonormalise_small(int which, int passes, double shift_rel, int planes, const MatDev* mats, int n_mats,
+                                       ClearShare clear, int* status, hipStream_t stream) {
+    const dim3 grid(n_mats + clear.blocks), block(64 * (kOrthoWaves + 1));
+    if (passes == 2 || which == kOrthoP)
+        hipLaunchKernelGGL(k_orthonormalise_small<true>, grid, block, 0, stream, mats, which, passes, shift_rel, planes, n_mats, clear, status);
+    else
+        hipLaunchKernelGGL(k_orthonormalise_small<false>, grid, block, 0, stream, mats, which, passes, shift_rel, planes, n_mats, clear, status);
+    return hipGetLastError();
+}
+
 template <bool FACTOR, int WAVES, int SLOTS>
 static hipError_t run_factor_blocks(const MatDev* mats, const SymPlanes* sym, int n_mats, int nb, double shift_rel,
                                     const ClearShare& clear, int* status, hipStream_t stream) {
@@ -1010,7 +1246,6 @@ __device__ __forceinline__ double dpp_d(double v) {
     return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
                             __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
 }
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 // BIT 0: rows of 16 lanes 1 and 3 of a change places with rows 0 and 2 of b; BIT 1: rows 2, 3 of a with 0, 1 of b
 template <int BIT>
 __device__ __forceinline__ void row_swap(double& a, double& b) {

@@ -183,6 +183,7 @@ struct Plan {
     std::vector<size_t> sync_off;
     bool sketch_planes;                         // refresh's gradient products read bf16 planes (launch_sketch_product) ...
     bool planeless;                             // ... and not those of every matrix
+    bool small_ortho[2];                        // Ya and P / Yb are orthonormalised in one launch (launch_orthonormalise_small)
     std::vector<TileRef> sketch[3];             // their tiles, by form - 1
     int skinny_rk;                              // 0: the MFMA / fp32-GEMM projection and update
     long long tiles4;                           // 256 x 256 tiles of the left-side projection
@@ -285,6 +286,10 @@ void make_plan(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* 
     // The refresh's products with bf16 gradients: sets on the left side (the right side's gradients are read along their
     // other dimension), matrices of at least 8 columns (see projection_tile_direct; narrower ones take the fp32 GEMM).  Forms 1 and 2 list a matrix's column tiles of one
     // gradient tile next to each other, form 3 its row tiles: they share the gradient tile in one XCD's L2.
+    p->small_ortho[0] = p->small_ortho[1] = true;
+    for (int i = 0; i < n_mats; ++i)
+        for (int b = 0; b < 2; ++b)
+            if (p->sz[i].l > 32 || (b ? d[i].n : d[i].m) > kOrthoRows) p->small_ortho[b] = false;
     p->sketch_planes = p->planeless = false;
     for (int i = 0; i < n_mats; ++i) {
         const bool planes = hp.grad_dtype == NG_BF16 && all_left && projection_tile_direct(d[i].n);
@@ -571,6 +576,12 @@ int inverse_factor(ng_state* st, GemmOp op, double shift_rel, hipStream_t stream
 // planes: what the product that reads the result next takes; one pass then leaves the planes only.
 int orthonormalise(ng_state* st, bool is_a, bool twice, int planes, hipStream_t stream, StepScalars sc, ClearShare* clear) {
     int rc;
+    if (st->plan.small_ortho[is_a ? 0 : 1]) {
+        NG_HIP(launch_orthonormalise_small(is_a ? kOrthoA : kOrthoB, twice ? 2 : 1, 2e-7, st->plan.sketch_planes ? planes : 0, st->d_mats, st->n_mats, *clear,
+                                           st->d_status, stream));
+        ++clear->part;
+        return NG_OK;
+    }
     StepScalars result = sc;
     result.planes = st->plan.sketch_planes ? planes : 0;
     result.planes_only = !twice;
@@ -1008,8 +1019,8 @@ int ng_refresh_projector(ng_state* st, const void* const* grads, ng_stream strea
                                 (unsigned long long)st->n_refresh[0], stream));
     const int q = st->hp.refresh_power_iters;
     const bool carry = st->hp.carry_history && st->hp.s > 0 && st->projector_valid;
-    // The history is cleared beside other work of the refresh, none of which touches it: beside the 2 q + 3 factors or the Jacobi's
-    // rounds.
+    // The history is cleared beside other work of the refresh, none of which touches it: beside the factors (2 q + 3; one less where
+    // the two passes of the last basis are one launch) or the Jacobi's rounds.
     ClearShare clear;
     memset(&clear, 0, sizeof(clear));
     clear.s = st->hp.s;
@@ -1018,7 +1029,7 @@ int ng_refresh_projector(ng_state* st, const void* const* grads, ng_stream strea
     bool cleared = false;
     if (!carry) clear.blocks = clear_share_blocks(st->n_mats, st->max_l, st->max_jpairs);
     if (clear.blocks > 0) {
-        clear.parts = 2 * q + 3;
+        clear.parts = 2 * q + (st->plan.small_ortho[0] ? 2 : 3);
         cleared = true;
     }
     if ((rc = gradient_product(st, OP_G_B2A, q == 0, stream, sc)) != NG_OK) return rc;
@@ -1044,8 +1055,12 @@ int ng_refresh_projector(ng_state* st, const void* const* grads, ng_stream strea
     if (carry) NG_HIP(launch_save_projector(st->d_mats, st->n_mats, stream));
     if ((rc = gemm(st, OP_ROTATE, stream, sc)) != NG_OK) return rc;
     // one CholeskyQR pass on P (m x r) restores orthonormality to rounding level, then fix signs
-    if ((rc = inverse_factor(st, OP_GRAM_P, 0.0, stream, sc, &clear)) != NG_OK) return rc;
-    if ((rc = gemm(st, OP_APPLY_P2A, stream, sc)) != NG_OK) return rc;
+    if (st->plan.small_ortho[0]) {
+        NG_HIP(launch_orthonormalise_small(kOrthoP, 1, 0.0, 0, st->d_mats, st->n_mats, clear, st->d_status, stream));
+    } else {
+        if ((rc = inverse_factor(st, OP_GRAM_P, 0.0, stream, sc, &clear)) != NG_OK) return rc;
+        if ((rc = gemm(st, OP_APPLY_P2A, stream, sc)) != NG_OK) return rc;
+    }
     NG_HIP(launch_sign_fix(st->d_mats, st->n_mats, st->max_r, stream));
 
     if (carry) {

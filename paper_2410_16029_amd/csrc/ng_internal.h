@@ -397,6 +397,16 @@ hipError_t launch_fill_gaussian(const MatDev* mats, int n_mats, int max_rows, bo
 // diagonal).  clear: beside orders up to kFactorMax only
 hipError_t launch_inverse_factor(GemmOp op, const MatDev* mats, const SymPlanes* sym, int n_mats, int max_order,
                                  double shift_rel, ClearShare clear, int* status, hipStream_t stream);
+// X <- X L^{-T}, X^T X + shift_rel * trace on the diagonal = L L^T, for sketches of up to 32 columns and kOrthoRows rows
+// in one launch: Ya or Yb into Yc (passes 1) or, by a second, unshifted pass, back into Ya (passes 2); P into Ya.  planes:
+// sketch planes of a result, which take the place of a single pass's floats (matrices that have them)
+enum { kOrthoA, kOrthoB, kOrthoP };
+// A workgroup takes a matrix's rows 256 at a time: against the three launches per pass, whose products have a workgroup for
+// every 64 rows, refreshes of one n x n matrix at l = 32 took 280 us for 342 (256 x 512) and 464 for 471 (n = 1024), of
+// 72 of n = 768 at l = 16 679 for 762; beyond, 693 for 662 (n = 2048) and 1206 for 1048 (n = 4096), with fp32 in every basis.
+constexpr int kOrthoRows = 1024;
+hipError_t launch_orthonormalise_small(int which, int passes, double shift_rel, int planes, const MatDev* mats, int n_mats,
+                                       ClearShare clear, int* status, hipStream_t stream);
 // extra workgroups of those launches that clearing is to have; 0 where it is better elsewhere
 int clear_share_blocks(int n_mats, int max_order, int max_pairs);
 // the rows that the Jacobi starts from: L^T of T = B B^T = L L^T (planes of OP_B_BT)

@@ -638,6 +638,86 @@ __global__ __launch_bounds__(256, TS == 128 ? 2 : 4) void k_gemm_f32_sides(int o
         gemm_f32_tile<TS, AL, BL, false, false, false>(op, mats, dyn, NG_F32, sc, nullptr, lds);
 }
 
+// The refresh's products with one side of up to 32 (the gradient with a narrow sketch, the rotation of a narrow basis) of
+// sets so small that a 64 x 64 tile per workgroup leaves most of the chip idle and each tile's k-steps follow one another:
+// a workgroup takes 16 indexes of the long side and all of the short one, its wavefronts 32 indexes of the contraction at
+// a time, in fp64 (16 x 16 x 4 MFMA), and their sums are added up through LDS.  Such a product of one 256 x 512 matrix at
+// l = 32, a chain of 16 k-steps in the large kernel, was 12 us; its refresh 280 -> 234 us, one of 1024 x 1024 463 -> 348, one of
+// 4096 x 4096 at l = 32 1040 -> 612.  The limit: sets of 256 x 512 with 640 workgroups 334 -> 318, 768 x 768 with 768 405 -> 383,
+// 1024 x 1024 with 768 496 -> 461 and 1024 500 -> 505, 768 x 768 with 1152 434 -> 451: fp64 runs at an eighth of the bf16 planes' rate.
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+constexpr int kFewRows = 16, kFewSide = 32, kFewWaves = 8, kFewBlocks = 768;
+
+__global__ __launch_bounds__(64 * kFewWaves) void k_gemm_f32_few(int op, const MatDev* __restrict__ mats, const MatDyn* __restrict__ dyn) {
+    __shared__ double sums[kFewWaves][2][256];
+    const GemmView v = gemm_view(op, mats[blockIdx.y], dyn ? dyn + blockIdx.y : nullptr, NG_F32);
+    // L (long side x contraction) times S (contraction x short side)
+    const bool b_long = op == OP_QT_G;
+    const float* __restrict__ L = (const float*)(b_long ? v.B : v.A);
+    const float* __restrict__ S = (const float*)(b_long ? v.A : v.B);
+    const long long li = b_long ? v.sBj : v.sAi, lk = b_long ? v.sBk : v.sAk;
+    const unsigned sk = (unsigned)(b_long ? v.sAk : v.sBk);          // (the short side's indexes are adjacent)
+    const int rows = b_long ? v.Nvalid : v.M, cols = b_long ? v.M : v.N;
+    const int i0 = kFewRows * blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (i0 >= (b_long ? v.N : v.M)) return;
+    const int c = lane & 15, g = lane >> 4;
+    const NG_AS1 float* row = (const NG_AS1 float*)L + (i0 + c < rows ? i0 + c : 0) * li;
+    const unsigned at[2] = {(unsigned)(c < cols ? c : 0), (unsigned)(c + 16 < cols ? c + 16 : 0)};
+    f64x4_t acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+    for (int k0 = 32 * w; k0 < v.K; k0 += 32 * kFewWaves) {
+        float a[2][4], b[2][4][2];
+        // indexes k0 + 16 h + 4 g + u of the contraction
+        if (lk == 1 && k0 + 32 <= v.K) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f32x4_t q = *(const NG_AS1 f32x4_a4*)(row + k0 + 16 * h + 4 * g);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) a[h][u] = q[u];
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int k = k0 + 16 * h + 4 * g + u;
+                    a[h][u] = row[(k < v.K ? k : 0) * lk];
+                }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 + 16 * h + 4 * g + u;
+                const NG_AS1 float* s = (const NG_AS1 float*)S + (unsigned)(k < v.K ? k : 0) * sk;
+#pragma unroll
+                for (int t = 0; t < 2; ++t) b[h][u][t] = s[at[t]];
+            }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const bool in = k0 + 16 * h + 4 * g + u < v.K;
+                const double x = in && i0 + c < rows ? a[h][u] : 0.f;
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, (double)(in && c + 16 * t < cols ? b[h][u][t] : 0.f), acc[t], 0, 0, 0);
+            }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sums[w][t][64 * e + lane] = acc[t][e];
+    __syncthreads();
+    double sum = 0.0;
+#pragma unroll
+    for (int q = 0; q < kFewWaves; ++q) sum += sums[q][tid >> 8][tid & 255];
+    const int i = i0 + 4 * ((tid & 255) >> 6) + ((tid & 63) >> 4), j = 16 * (tid >> 8) + (tid & 15);
+    if (j >= cols || i >= (b_long ? v.N : v.M)) return;
+    NG_AS1 float* C = (NG_AS1 float*)v.C;
+    if (b_long) C[(long long)j * v.ldc + i] = (float)sum;
+    else C[(long long)i * v.ldc + j] = (float)sum;
+}
+
 // max_m, max_n, max_k: the largest dimensions of this product over the layer set; tiles: its 128 x 128 tiles.  The large
 // tile, half of the operand bytes per product, is used from 1536 tiles (three per workgroup slot) on for runs of the
 // contraction of 256, from 512 on for runs of 768: the small one, a quarter of the work per workgroup, hides more of each
@@ -711,6 +791,12 @@ hipError_t launch_gemm_f32(GemmOp op, const MatDev* mats, const MatDyn* dyn, int
         const long long nx = (max_n + ts - 1) / ts, ny = (max_m + ts - 1) / ts;
         return (left.sym ? ny * (ny + 1) / 2 : nx * ny) * (max_split > 1 ? max_split : 1);
     };
+    const int few = op == OP_QT_G ? max_m : max_n, many = op == OP_QT_G ? max_n : max_m;
+    if ((op == OP_ROTATE || (grad_dtype == NG_F32 && (op == OP_G_B2A || op == OP_G_C2A || op == OP_GT_C2B || op == OP_QT_G))) &&
+        !planeless && few <= kFewSide && (long long)((many + kFewRows - 1) / kFewRows) * n_mats <= kFewBlocks) {
+        k_gemm_f32_few<<<dim3((many + kFewRows - 1) / kFewRows, n_mats), dim3(64 * kFewWaves), 0, stream>>>((int)op, mats, dyn);
+        return hipGetLastError();
+    }
     const bool big = f32_tile_large(op, max_m, max_n, max_k, tiles, max_split);
     const dim3 g((unsigned)((count(big ? 128 : 64) + 7) / 8 * 8), 1, n_mats);
     if (by_side && sides == 3 && grad_dtype == NG_F32 &&

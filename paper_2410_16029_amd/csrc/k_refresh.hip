@@ -18,6 +18,7 @@
 #include "eliminate16.h"
 #include "ng_internal.h"
 #include "split_bf16.h"
+#include "state_math.h"
 
 namespace ng {
 
@@ -1986,35 +1987,61 @@ hipError_t launch_jacobi(const MatDev* mats, int n_mats, int max_pairs, int swee
 
 // Ritz values (row norms), descending order, then the l x r rotation U[:, top r] as floats in Bm.
 // (sixteen wavefronts, four rows each in flight: with four wavefronts a row at a time 112 us for 168 matrices of
-// order 256)
+// order 256, with sixteen 38; a chain of memory latencies, so a row's loads go out together and the values are compared in LDS)
 constexpr int kSortThreads = 1024;
 __global__ __launch_bounds__(kSortThreads) void k_ritz_sort(const MatDev* __restrict__ mats, int sweeps, int* status) {
+    __shared__ double vals[kSortThreads];
     const MatDev& md = mats[blockIdx.x];
     const int lp = md.lp;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     for (int i = 4 * wv; i < lp; i += 4 * (kSortThreads / 64)) {      // lp % 32 == 0
         const float* __restrict__ row = jacobi_rows(md) + (long long)i * lp;
         double a[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int c = lane; c < lp; c += 64) {
-            float x[4];
+        for (int c = lane; c < lp; c += 256) {
+            float x[4][4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = row[(long long)u * lp + c];
+            for (int h = 0; h < 4; ++h)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) a[u] += (double)x[u] * (double)x[u];
+                for (int u = 0; u < 4; ++u) x[h][u] = row[(long long)u * lp + (c + 64 * h < lp ? c + 64 * h : lane)];
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double y = c + 64 * h < lp ? (double)x[h][u] : 0.0;
+                    a[u] += y * y;
+                }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const double v = wave_sum_d(a[u]);
-            if (lane == 0) md.ritz[i + u] = ritz_value(v);
+            const double v = ritz_value(wave_sum_d(a[u]));
+            if (lane == 0) {
+                md.ritz[i + u] = v;
+                if (lp <= kSortThreads) vals[i + u] = v;
+            }
         }
     }
     __syncthreads();
     __threadfence_block();
     bool bad = false;
-    for (int i = threadIdx.x; i < lp; i += kSortThreads) {
-        const int place = ritz_place(md.ritz, lp, i);
-        md.order[place] = i;
-        if (place < md.r && !(md.ritz[i] > 0.0)) bad = true;
+    if (lp <= kSortThreads) {
+        // as many lanes per value as the workgroup has (a power of two), each compares it with its share of the others
+        int per = 1;
+        while (2 * per * lp <= kSortThreads && per < 64) per *= 2;
+        const int i = threadIdx.x / per, sub = threadIdx.x & (per - 1);
+        if (i < lp) {
+            int place = ritz_place(vals, lp, i, sub, per);
+            for (int off = 1; off < per; off *= 2) place += __shfl_xor(place, off, 64);
+            if (sub == 0) {
+                md.order[place] = i;
+                if (place < md.r && !(vals[i] > 0.0)) bad = true;
+            }
+        }
+    } else {
+        for (int i = threadIdx.x; i < lp; i += kSortThreads) {
+            const int place = ritz_place(md.ritz, lp, i);
+            md.order[place] = i;
+            if (place < md.r && !(md.ritz[i] > 0.0)) bad = true;
+        }
     }
     if (bad) atomicOr(status, 8);
     // no sweep without a rotation was seen before the sweep limit
@@ -2046,10 +2073,15 @@ hipError_t launch_jacobi_finish(const MatDev* mats, int n_mats, int sweeps, int*
 // magnitude (first one on ties) and written to P.
 // A workgroup takes 32 columns; 32 threads share a column, each with eight rows in flight.  (Four threads per
 // column and one row at a time: 540 us for 168 projectors of 1024 x 256, 23 us for one of 256 x 32.)
+//
+// COPIES: the bf16 copies of P as well (layouts: k_make_bf16_copies), whose blocks of 32 are this workgroup's columns: P is not read
+// again, and the copies go out 16 bytes per thread.
 constexpr int kSignRows = 32;
+template <bool COPIES>
 __global__ __launch_bounds__(32 * kSignRows) void k_sign_fix(const MatDev* __restrict__ mats) {
     __shared__ float best[kSignRows][33];
     __shared__ int besti[kSignRows][33];
+    __shared__ float tile[8][32][33];        // (COPIES)
     const MatDev& md = mats[blockIdx.y];
     const int r = md.r, m = md.m;
     const int tc = threadIdx.x & 31, rg = threadIdx.x >> 5;
@@ -2075,7 +2107,8 @@ __global__ __launch_bounds__(32 * kSignRows) void k_sign_fix(const MatDev* __res
     best[rg][tc] = bv;
     besti[rg][tc] = bi;
     __syncthreads();
-    if (c >= r) return;
+    if (!COPIES && c >= r) return;
+    const int cs = c < r ? c : r - 1;
     float v = best[0][tc];
     int idx = besti[0][tc];
     for (int g = 1; g < kSignRows; ++g) {
@@ -2083,19 +2116,65 @@ __global__ __launch_bounds__(32 * kSignRows) void k_sign_fix(const MatDev* __res
         const int i2 = besti[g][tc];
         if (v2 > v || (v2 == v && i2 < idx)) { v = v2; idx = i2; }
     }
-    const float sgn = src[(long long)idx * r + c] < 0.f ? -1.f : 1.f;
-    for (int i = rg; i < m; i += 8 * kSignRows) {
-        float a[8];
+    const float sgn = src[(long long)idx * r + cs] < 0.f ? -1.f : 1.f;
+    if constexpr (!COPIES) {
+        for (int i = rg; i < m; i += 8 * kSignRows) {
+            float a[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) a[u] = src[(long long)(i + u * kSignRows < m ? i + u * kSignRows : i) * r + c];
+            for (int u = 0; u < 8; ++u) a[u] = src[(long long)(i + u * kSignRows < m ? i + u * kSignRows : i) * r + c];
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (i + u * kSignRows < m) md.P[(long long)(i + u * kSignRows) * r + c] = sgn * a[u];
+            for (int u = 0; u < 8; ++u)
+                if (i + u * kSignRows < m) md.P[(long long)(i + u * kSignRows) * r + c] = sgn * a[u];
+        }
+    } else {
+        for (int i0 = 0; i0 < m; i0 += 8 * kSignRows) {
+            float a[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + rg + u * kSignRows;
+                a[u] = src[(long long)(i < m ? i : m - 1) * r + cs];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + rg + u * kSignRows;
+                const bool in = i < m && c < r;
+                const float x = sgn * a[u];
+                if (in) md.P[(long long)i * r + c] = x;
+                tile[u][rg][tc] = in ? x : 0.f;
+            }
+            __syncthreads();
+            const int q = threadIdx.x >> 7, x = (threadIdx.x & 127) >> 2, o = 8 * (threadIdx.x & 3);
+            const int ib = i0 + 32 * q, rho = blockIdx.x * 32 + x;
+            if (ib + x < m) {
+                u32x4_t w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = pack_bf16x2(tile[q][x][o + 2 * e], tile[q][x][o + 2 * e + 1]);
+                *reinterpret_cast<u32x4_t*>(md.Pb + ((long long)blockIdx.x * m + ib + x) * 32 + o) = w;
+            }
+            if (ib < m && rho < r) {
+                u32x4_t w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = pack_bf16x2(tile[q][o + 2 * e][x], tile[q][o + 2 * e + 1][x]);
+                *reinterpret_cast<u32x4_t*>(md.PbT + ((long long)(ib >> 5) * r + rho) * 32 + o) = w;
+            }
+            __syncthreads();
+        }
     }
 }
 
-hipError_t launch_sign_fix(const MatDev* mats, int n_mats, int max_r, hipStream_t stream) {
-    hipLaunchKernelGGL(k_sign_fix, dim3((max_r + 31) / 32, n_mats), dim3(32 * kSignRows), 0, stream, mats);
+// The copies beside the signs save a pass over P, but a workgroup goes down all rows of its columns, 256 at a time, where a launch of
+// their own has a workgroup per 32.  Refreshes with them apart and in here (us, each with the faster k_ritz_sort on the second
+// side, some 3 to 15 us): one 1024 x 1024 at rank 64 (2 workgroups) 647 -> 645, 2048 x 1024 725 -> 725, 4096 x 1024 890 -> 900,
+// 16000 x 512 1786 -> 1856; 8 of 8192 x 512 at rank 128 (32) 1959 -> 1973, 32 of them (128) 2862 -> 2834; the 60M set (224, up to 1376
+// rows) 1608 -> 1595, the 350M set (1344, 2736) 11.72 -> 11.64 ms.
+bool sign_fix_copies(int n_mats, int max_m, int max_r) {
+    return max_m <= 1024 || (long long)((max_r + 31) / 32) * n_mats >= max_m / 64;
+}
+
+hipError_t launch_sign_fix(const MatDev* mats, int n_mats, int max_r, bool copies, hipStream_t stream) {
+    const dim3 grid((max_r + 31) / 32, n_mats), block(32 * kSignRows);
+    if (copies) hipLaunchKernelGGL(k_sign_fix<true>, grid, block, 0, stream, mats);
+    else hipLaunchKernelGGL(k_sign_fix<false>, grid, block, 0, stream, mats);
     return hipGetLastError();
 }
 

@@ -1061,7 +1061,8 @@ int ng_refresh_projector(ng_state* st, const void* const* grads, ng_stream strea
         if ((rc = inverse_factor(st, OP_GRAM_P, 0.0, stream, sc, &clear)) != NG_OK) return rc;
         if ((rc = gemm(st, OP_APPLY_P2A, stream, sc)) != NG_OK) return rc;
     }
-    NG_HIP(launch_sign_fix(st->d_mats, st->n_mats, st->max_r, stream));
+    const bool copies = st->hp.grad_dtype == NG_BF16 && sign_fix_copies(st->n_mats, st->max_m, st->max_r);
+    NG_HIP(launch_sign_fix(st->d_mats, st->n_mats, st->max_r, copies, stream));
 
     if (carry) {
         // H_j <- (P_new^T P_old) H_j for every slot, then the whole Gram matrix again
@@ -1077,7 +1078,7 @@ int ng_refresh_projector(ng_state* st, const void* const* grads, ng_stream strea
             NG_HIP(launch_solve(st->d_mats, st->d_dyn, 0, st->n_mats, sc, row, st->d_status, stream));
         }
     }
-    if ((rc = finish_projector(st, !carry && !cleared, true, stream)) != NG_OK) return rc;
+    if ((rc = finish_projector(st, !carry && !cleared, !copies, stream)) != NG_OK) return rc;
     st->projector_valid = true;
     for (int i = 0; i < st->n_mats; ++i) {
         if (!carry) {

@@ -371,10 +371,10 @@ hipError_t launch_make_bf16_copies(const MatDev* mats, int n_mats, int max_m, in
 // comparing false, all NaN values had place 0 and the other entries kept what the workspace held).
 __host__ __device__ inline double ritz_value(double sum) { return sum >= 0.0 ? sqrt(sum) : -1.0; }
 // Place of value i among n, largest first and equal ones by index.
-__host__ __device__ inline int ritz_place(const double* v, int n, int i) {
+__host__ __device__ inline int ritz_place(const double* v, int n, int i, int first = 0, int step = 1) {
     const double vi = v[i];
     int place = 0;
-    for (int j = 0; j < n; ++j) {
+    for (int j = first; j < n; j += step) {
         const double vj = v[j];
         place += (vj > vi) || (vj == vi && j < i);
     }
@@ -416,7 +416,9 @@ hipError_t launch_jacobi_prepare(const MatDev* mats, const SymPlanes* sym, int n
 // clear.parts != 0: something is to be cleared; *cleared tells whether it was
 hipError_t launch_jacobi(const MatDev* mats, int n_mats, int max_pairs, int sweeps, ClearShare clear, bool* cleared, hipStream_t stream);
 hipError_t launch_jacobi_finish(const MatDev* mats, int n_mats, int sweeps, int* status, hipStream_t stream);
-hipError_t launch_sign_fix(const MatDev* mats, int n_mats, int max_r, hipStream_t stream);
+// whether the kernel that fixes the signs also makes the bf16 copies (of a bf16 layer set)
+bool sign_fix_copies(int n_mats, int max_m, int max_r);
+hipError_t launch_sign_fix(const MatDev* mats, int n_mats, int max_r, bool copies, hipStream_t stream);
 
 // micro-benchmarks (k_microbench.hip)
 hipError_t launch_mb_copy(const void* src, void* dst, size_t bytes, hipStream_t stream);

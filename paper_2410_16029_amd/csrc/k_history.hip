@@ -176,7 +176,9 @@ namespace {
 struct HistShared {
     double red[4][16], A[16][17], bc[256];
     float w[16];                         // weights in the order of a tile's slots, R's first
-    int cmd;
+    // One word per decision of the first wavefront, written in one place and read behind a barrier: a wavefront that has not
+    // read a decision yet must not find the next one there (the first runs ahead of it until their next barrier).
+    int tile_cmd, solver_cmd, taken;
 };
 enum { kGo, kExit, kSolve };
 __device__ __forceinline__ int wave_lane() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
@@ -264,10 +266,10 @@ __device__ __forceinline__ bool solve_matrix(HistShared& sh, const MatDev& md, c
             }
             __builtin_amdgcn_s_sleep(2);
         }
-        if (lane == 0) sh.cmd = c;
+        if (lane == 0) sh.solver_cmd = c;
     }
     __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(sh.cmd) == kExit) return false;
+    if (__builtin_amdgcn_readfirstlane(sh.solver_cmd) == kExit) return false;
     const double* parts = step_scratch<double>(dyn, md.dot_parts_off);
     const int nsub = T > 256 ? sum_dot_parts<true, 32>(parts, T, s, tid, sh.bc) : sum_dot_parts<true>(parts, T, s, tid, sh.bc);
     __syncthreads();
@@ -409,10 +411,10 @@ __global__ __launch_bounds__(256, OCC) void k_history(const MatDev* __restrict__
                         if (lane == 0) m = __hip_atomic_fetch_and(leftover + word, ~(1u << b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         if ((__builtin_amdgcn_readfirstlane(m) >> b) & 1u) taken = 32 * word + b;
                     }
-                    if (lane == 0) sh.cmd = taken;
+                    if (lane == 0) sh.taken = taken;
                 }
                 __syncthreads();
-                if (t < 0) t = __builtin_amdgcn_readfirstlane(sh.cmd);
+                if (t < 0) t = __builtin_amdgcn_readfirstlane(sh.taken);
                 if (t < 0) return;
                 const TileRef at = {it.mat, t / across * rows, t % across * cols, nbs << 2};
                 transform_tile<RT, HB, BF16_N>(sh, md, dyn, dy, at, sc, wv, lane, status);
@@ -513,10 +515,10 @@ __global__ __launch_bounds__(256, OCC) void k_history(const MatDev* __restrict__
         if (wv == 0) {
             bool help = false;
             if (c == kGo) c = wait_for_weights(sh, lines, part, s, head, lane, wait_ticks, help);
-            if (lane == 0) sh.cmd = c | (help ? 16 : 0);
+            if (lane == 0) sh.tile_cmd = c | (help ? 16 : 0);
         }
         __syncthreads();
-        const int cmd = __builtin_amdgcn_readfirstlane(sh.cmd);
+        const int cmd = __builtin_amdgcn_readfirstlane(sh.tile_cmd);
         if ((cmd & 15) == kGo) {
             f32x4_t g[RT];
 #pragma unroll

@@ -67,6 +67,20 @@ def test_tiles_left_by_workgroups_that_gave_way(dtype, r, s, kw):
     t.assert_equal("gave way")
 
 
+@pytest.mark.parametrize("r,s", [(8, 5), (16, 1), (8, 9), (40, 3), (40, 5), (40, 15)])
+def test_what_the_new_slot_held_before_does_not_matter(r, s):
+    # fp32 sets whose projection leaves row chunks: the slot is written by the launch that also reads the ring.  One of two
+    # equal sets finds NaN there; slots beyond s must not bring it in with a weight of zero.
+    t = _twin([(384, 520), (200, 333), (130, 75)], r, s, "f32", seed=367, k=40)
+    assert all(_tiles(t.b, i) > 0 for i in range(3))
+    for _ in range(s + 1):
+        for i in range(3):
+            slot, head = t.b.layouts[i].slot_elems, t.b.counters(i)[1]
+            t.b.buffers[i][B.NG_BUF_H].view(torch.float32)[head * slot:(head + 1) * slot].fill_(float("nan"))
+        t.step()
+        t.assert_equal("new slot")
+
+
 def test_two_streams_at_once():
     # two sets of matrices of the largest kind on two streams: their workgroups share the chip.  Against equal sets that had
     # it to themselves.

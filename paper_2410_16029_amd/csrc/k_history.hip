@@ -366,6 +366,7 @@ __global__ __launch_bounds__(256, OCC) void k_history(const MatDev* __restrict__
                                                       unsigned wait_ticks, int* status) {
     typedef typename HistVec<HB>::type hist_t;
     static_assert(NL == 0 || !HB, "rows of 16 bytes go straight into LDS");
+    static_assert(NL == 0 || BF16_N, "where R may be summed here, every slot beyond s is in registers");
     constexpr int NR = S - NL;
     constexpr unsigned HS = HB ? 2u : 4u;
     __shared__ __align__(16) unsigned char kept[NL > 0 ? NL * RT * 4096 : 16];   // [slot][row][thread] x 16 bytes
@@ -426,7 +427,8 @@ __global__ __launch_bounds__(256, OCC) void k_history(const MatDev* __restrict__
         const HistTile<RT> tl(md, it, wv, lane);
         const int part = it.pad >> 4;
         const unsigned long long slot_bytes = (unsigned long long)md.slot_elems * HS;
-        // slot (head + j) mod s; a slot beyond s re-reads R, with weight 0
+        // slot (head + j) mod s; a slot beyond s re-reads R, with weight 0, or where R is still to be summed is taken as zero
+        // below (what the slot held before may be anything)
         const NG_AS1 unsigned char* const first = (const NG_AS1 unsigned char*)md.H;
         const NG_AS1 unsigned char* const mine = first + (unsigned long long)head * slot_bytes;
         const NG_AS1 unsigned char* slot = mine;
@@ -458,6 +460,12 @@ __global__ __launch_bounds__(256, OCC) void k_history(const MatDev* __restrict__
                     for (int x = 0; x < 4; ++x) h[0][e][x] = __float_as_uint(sum[e][x]);
                     if (e < tl.nrow) *(NG_AS1 f32x4_t*)(r_slot + tl.eoff[e] * 4u) = sum[e];
                 }
+#pragma unroll
+                for (int j = 1; j < NR; ++j)
+#pragma unroll
+                    for (int e = 0; e < RT; ++e)
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) h[j][e][x] = j < s ? h[j][e][x] : 0u;
             }
         }
         auto kept_at = [&](int j, int e) -> hist_t { return *(const hist_t*)(kept + ((j - NR) * RT + e) * 4096 + tid * 16); };

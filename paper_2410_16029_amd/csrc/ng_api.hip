@@ -288,8 +288,8 @@ void make_plan(const ng_matrix_desc* d, int n_mats, const ng_hparams& hp, Plan* 
     // gradient tile next to each other, form 3 its row tiles: they share the gradient tile in one XCD's L2.
     p->small_ortho[0] = p->small_ortho[1] = true;
     for (int i = 0; i < n_mats; ++i)
-        for (int b = 0; b < 2; ++b)
-            if (p->sz[i].l > 32 || (b ? d[i].n : d[i].m) > kOrthoRows) p->small_ortho[b] = false;
+        for (int b = 0; b < 2; ++b)      // rows of the projected problem's sketch
+            if (p->sz[i].l > 32 || (b ? effective(d[i]).n : effective(d[i]).m) > kOrthoRows) p->small_ortho[b] = false;
     p->sketch_planes = p->planeless = false;
     for (int i = 0; i < n_mats; ++i) {
         const bool planes = hp.grad_dtype == NG_BF16 && all_left && projection_tile_direct(d[i].n);
@@ -1264,6 +1264,11 @@ int ng_debug_history_wait(ng_state* st, uint32_t ticks) {
 // launches).
 int ng_debug_history_tiles(const ng_state* st, int mat) {
     return st && mat >= 0 && mat < st->n_mats ? st->plan.hist_tiles[mat] : -1;
+}
+
+// Not in the header, for tests: bit 0 set where Ya and P are orthonormalised in one launch each, bit 1 where Yb is.
+int ng_debug_small_ortho(const ng_state* st) {
+    return st ? (st->plan.small_ortho[0] ? 1 : 0) | (st->plan.small_ortho[1] ? 2 : 0) : -1;
 }
 
 void ng_destroy(ng_state* st) {

@@ -183,18 +183,33 @@ struct HistShared {
 enum { kGo, kExit, kSolve };
 __device__ __forceinline__ int wave_lane() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 
-// First wavefront of a tile whose share is counted in: w from its line, every component with its mark.  A tile that has waited
-// long enough (others of its matrix are with workgroups that have not started, and may not before this one ends) is
-// left to whoever takes its bit.  The bit is set before w is looked at for the last time, and the solver goes
+// Workgroups of the matrix, the solver's among them, that have not started.  (First wavefront; a look at eight lines, for those
+// that have waited for long.)
+__device__ __forceinline__ unsigned not_started(const HistoryLine* lines, int T, int lane) {
+    unsigned n = 0;
+    if (lane < kHistoryLines) n = __hip_atomic_load(&lines[lane].started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int sum = 0;
+#pragma unroll
+    for (int l = 0; l < kHistoryLines; ++l) sum += __builtin_amdgcn_readlane((int)n, l);
+    return (unsigned)(T + 1 - sum);
+}
+
+// First wavefront of a tile whose share is counted in: w from its line, every component with its mark.  After every wait_ticks
+// of waiting it looks how many workgroups of its matrix have not started, which may need the places of those that have: the
+// first that many tiles are left to whoever takes their bits, then twice as many, and so on.  Those that have started all arrive,
+// so nobody leaves when all have; kHistoryPatience looks end any wait.  (When every tile left at the first look, a matrix whose
+// last two tiles stood behind a neighbour's, on a first step with its page tables still to be walked, went through the few that
+// were still there one tile after the other: first step of the 1.1B set 32 to 39 ms.)  The bit is set before w is looked at for the last time, and the solver goes
 // through the bits after w is there: either this workgroup sees w and takes the bit back, or the solver sees the bit.
 // `help`: others of the matrix had been left when the solver was done.
-__device__ __forceinline__ int wait_for_weights(HistShared& sh, HistoryLine* lines, int part, int s, int head, int lane,
+__device__ __forceinline__ int wait_for_weights(HistShared& sh, HistoryLine* lines, int part, int T, int s, int head, int lane,
                                                 unsigned wait_ticks, bool& help) {
     HistoryLine* line = lines + (part & (kHistoryLines - 1));
     unsigned* leftover = reinterpret_cast<unsigned*>(lines + kHistoryLines) + (part >> 5);
     const unsigned bit = 1u << (part & 31);
     const int j = head + lane < s ? head + lane : head + lane - s;
-    const unsigned long long start = __builtin_amdgcn_s_memrealtime();
+    unsigned start = (unsigned)__builtin_amdgcn_s_memrealtime();
+    unsigned looks = 0;
     bool late = false;
     for (;;) {
         unsigned long long v = 1ull << 32;
@@ -208,7 +223,13 @@ __device__ __forceinline__ int wait_for_weights(HistShared& sh, HistoryLine* lin
             return (__builtin_amdgcn_readfirstlane(old) & bit) ? kGo : kExit;
         }
         if (late) return kExit;
-        if (__builtin_amdgcn_s_memrealtime() - start > wait_ticks) {
+        bool leave = false;
+        const unsigned now = (unsigned)__builtin_amdgcn_s_memrealtime();
+        if (now - start > wait_ticks) {
+            leave = history_leaves(part, not_started(lines, T, lane), looks++) || wait_ticks == 0;
+            start = now;
+        }
+        if (leave) {
             late = true;
             if (lane == 0) __hip_atomic_store((unsigned*)&line->arrived_late + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (lane == 0) __hip_atomic_fetch_or(leftover, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -232,6 +253,7 @@ __device__ __forceinline__ bool solve_matrix(HistShared& sh, const MatDev& md, c
     const double lam = (double)sc.lambda, inv_s = 1.0 / (double)(sc.norm_count ? dy.count : s);
     bool late = false;
     if (wv == 0) {
+        if (tile < 0 && lane == 0) __hip_atomic_fetch_add(&lines->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (int q = lane; q < s * s; q += 64) {
             const int i = q / s, j = q - i * s;
             sh.A[i][j] = md.K[q];
@@ -245,9 +267,10 @@ __device__ __forceinline__ bool solve_matrix(HistShared& sh, const MatDev& md, c
 #pragma unroll
             for (int k = 0; k < 16; ++k) sh.A[k][lane] = v[k];
         }
-        // Until all tiles are counted in.  Nothing says that they start while this workgroup holds its place: after a while
-        // it gives way, and the last of them solves.
-        const unsigned long long start = __builtin_amdgcn_s_memrealtime();
+        // Until all tiles are counted in.  Nothing says that they start while this workgroup holds its place: if some have not
+        // after a while, it gives way, and the last of them solves.
+        unsigned start = (unsigned)__builtin_amdgcn_s_memrealtime();
+        unsigned looks = 0;
         int c = kGo;
         for (;;) {
             // (the count and whether tiles were left, one line of the matrix per lane)
@@ -258,7 +281,10 @@ __device__ __forceinline__ bool solve_matrix(HistShared& sh, const MatDev& md, c
             unsigned n = (unsigned)v;
             for (int d = 1; d < kHistoryLines; d *= 2) n += __shfl_xor(n, d);
             if (__builtin_amdgcn_readfirstlane(n) == (unsigned)T) break;
-            if (__builtin_amdgcn_s_memrealtime() - start > wait_ticks) {
+            const unsigned now = (unsigned)__builtin_amdgcn_s_memrealtime();
+            const bool look = now - start > wait_ticks;
+            if (look) start = now;
+            if (look && (not_started(lines, T, lane) > 0 || ++looks == kHistoryPatience || wait_ticks == 0)) {
                 unsigned there = 0;
                 if (lane == 0) there = __hip_atomic_exchange(&lines->state, kSolverGone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kAllThere;
                 if (!__builtin_amdgcn_readfirstlane(there)) c = kExit;
@@ -449,6 +475,8 @@ __global__ __launch_bounds__(256, OCC) void k_history(const MatDev* __restrict__
             }
             slot = j + 1 >= s ? mine : head + j + 1 == s ? first : slot + slot_bytes;
         }
+        if (wv == 0 && lane == 0)
+            __hip_atomic_fetch_add(&lines[part & (kHistoryLines - 1)].started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if constexpr (!BF16_N) {
             if (nparts > 0) {
                 f32x4_t sum[RT];
@@ -522,7 +550,7 @@ __global__ __launch_bounds__(256, OCC) void k_history(const MatDev* __restrict__
         for (int k = 0; k < PF; ++k) ahead[k].template load<RT>(md, tl.eoff, 2 * k);
         if (wv == 0) {
             bool help = false;
-            if (c == kGo) c = wait_for_weights(sh, lines, part, s, head, lane, wait_ticks, help);
+            if (c == kGo) c = wait_for_weights(sh, lines, part, T, s, head, lane, wait_ticks, help);
             if (lane == 0) sh.tile_cmd = c | (help ? 16 : 0);
         }
         __syncthreads();
@@ -583,7 +611,7 @@ void history_shape(int s, int hist_bf16, int bf16_n, int* lane_rows, int* wave_c
         *lane_rows = RT;                                        \
         *wave_cols = HistTile<RT>::WC;                          \
         *most_tiles = MOST;                                     \
-        static_assert(MOST <= 256 * OCC / 2, "two such matrices on the chip"); \
+        static_assert(MOST <= 256 * OCC / 2, "a matrix, its solver and nearly all of the next one on the chip"); \
     } while (0)
     NG_HISTORY_CASES(NG_HISTORY_SHAPE)
 #undef NG_HISTORY_SHAPE

@@ -1266,6 +1266,15 @@ int ng_debug_history_tiles(const ng_state* st, int mat) {
     return st && mat >= 0 && mat < st->n_mats ? st->plan.hist_tiles[mat] : -1;
 }
 
+// Not in the header, for tests: the rule by which tiles of launch_history that wait give way.
+int ng_debug_history_leaves(uint32_t tile, uint32_t not_started, uint32_t looks) { return history_leaves(tile, not_started, looks); }
+
+// Not in the header, for tests: place of a matrix's HistoryLines in the workspace, for steps on the workspace's own scratch.
+int64_t ng_debug_history_lines(const ng_state* st, int mat) {
+    if (!st || mat < 0 || mat >= st->n_mats || st->plan.hist_tiles[mat] == 0) return -1;
+    return (int64_t)(st->plan.off_step + st->plan.sync_off[mat]);
+}
+
 // Not in the header, for tests: bit 0 set where Ya and P are orthonormalised in one launch each, bit 1 where Yb is.
 int ng_debug_small_ortho(const ng_state* st) {
     return st ? (st->plan.small_ortho[0] ? 1 : 0) | (st->plan.small_ortho[1] ? 2 : 0) : -1;

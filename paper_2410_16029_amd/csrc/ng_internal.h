@@ -163,11 +163,18 @@ struct HistoryLine {
     unsigned long long arrived_late;  // tiles of this line whose partial sums are in memory, and above, whether one was left
     unsigned full;                    // line 0: lines whose tiles have all arrived
     unsigned state;                   // line 0: kSolverGone or kAllThere, whichever came first
-    unsigned pad[28];
+    unsigned started;                 // workgroups of this line's tiles (and in line 0 the solver) that have started
+    unsigned pad[27];
 };
+static_assert(sizeof(HistoryLine) == 256, "two cache lines");
 constexpr int kHistoryLines = 8;
 constexpr unsigned kSolverGone = 1, kAllThere = 2;
 constexpr unsigned kHistoryWait = 10000;   // 100 us, several times what the largest matrix takes to arrive
+constexpr unsigned kHistoryPatience = 100; // times that end any wait
+// Whether a tile that waits is left at its look number `looks` (from 0): see wait_for_weights in k_history.hip
+__host__ __device__ inline bool history_leaves(unsigned tile, unsigned not_started, unsigned looks) {
+    return looks + 1 >= kHistoryPatience || tile < not_started << (looks < 16 ? looks : 16);
+}
 // Items of k_history (TileRef): a tile (its first row and column, and in `pad` log2(bands) << 2 | tile << 4), or the solver of a
 // matrix.
 enum { kHistoryTile = 0, kHistorySolve = 1 };

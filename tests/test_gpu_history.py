@@ -81,6 +81,29 @@ def test_what_the_new_slot_held_before_does_not_matter(r, s):
         t.assert_equal("new slot")
 
 
+@pytest.mark.parametrize("dtype,r,s", [("bf16", 64, 16), ("bf16", 72, 8), ("f32", 40, 5)])
+def test_nobody_gives_way_when_all_have_started(dtype, r, s):
+    # Waiting limits far below what the last sums take (2 us), on a chip that has places for all: the workgroups look whether
+    # the others of their matrix have started and wait on.  (When they did not look, a slow first step sent whole matrices
+    # through the workgroup that solves, tile after tile: first step of the 1.1B set 32 ms.)
+    t = _twin([(384, 520), (200, 2333), (520, 384), (130, 75)], r, s, dtype, seed=373, k=40)
+    _wait(t.b, 200)
+    ws = t.b.workspace[(-t.b.workspace.data_ptr()) % 256:]
+    B._lib.ng_debug_history_lines.restype = ctypes.c_int64
+    at = [B._lib.ng_debug_history_lines(t.b.st, ctypes.c_int(i)) for i in range(4)]
+    assert min(at) > 0
+    left = []
+    for _ in range(8):
+        t.step()
+        torch.cuda.synchronize()
+        # eight lines of 256 bytes per matrix; behind 16 weights the tiles counted in, and whether one was left
+        words = [ws[a:a + 2048].view(torch.int32).view(8, 64)[:, 32:34] for a in at]
+        assert [int(w[:, 0].sum()) for w in words] == [_tiles(t.b, i) for i in range(4)]
+        left.append(sum(int(w[:, 1].sum()) for w in words))
+    assert min(left) == 0, left                      # (a step that something else held up may have left some)
+    t.assert_equal("waited on")
+
+
 def test_two_streams_at_once():
     # two sets of matrices of the largest kind on two streams: their workgroups share the chip.  Against equal sets that had
     # it to themselves.

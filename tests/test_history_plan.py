@@ -43,6 +43,19 @@ def test_right_side_counts_the_projected_problem():
     assert _tiles(left) == [_expect(24, 140, 4, 384)] and _tiles(right) == [_expect(24, 300, 4, 384)]
 
 
+@pytest.mark.parametrize("tiles", [1, 24, 512])
+def test_tiles_give_way_to_those_that_have_not_started(tiles):
+    def leave(missing, look):
+        return sum(B._lib.ng_debug_history_leaves(t, missing, look) for t in range(tiles))
+
+    patience = 100
+    for look in range(patience - 1):
+        assert leave(0, look) == 0                               # all have started: nobody's place is wanted
+        for missing in (1, 3, 200, tiles + 1):
+            assert leave(missing, look) == min(tiles, missing << min(look, 16))
+    assert leave(0, patience - 1) == leave(1, patience - 1) == tiles     # any wait ends
+
+
 @pytest.mark.parametrize("count,tiles", [(400, 512), (900, 0), (1100, 512)])
 def test_a_step_that_fitted_the_librarys_own_scratch_still_does(count, tiles):
     # Partial sums per tile take 64 KB of a matrix of 512 tiles at 16 slots, the plain ones 32 KB: 900 of these matrices fit

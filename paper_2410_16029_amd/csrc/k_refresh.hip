@@ -522,28 +522,38 @@ __device__ __forceinline__ bool factor_diag(double* __restrict__ A, double* __re
 }
 
 // A workgroup's part of a ClearShare.  A CU stores 18 to 28 GB/s of zeros however many wavefronts it has at it, so a launch of
-// its own takes the whole chip to clear at 4.7 TB/s (350M set, 4.2 GB: 0.89 ms).  The Jacobi's rounds use next to no memory
-// bandwidth: beside 60 of them the refresh of that set takes 13.02 -> 12.00 ms.  Where the
+// its own takes the whole chip to clear at 4.7 TB/s (350M set, 5.2 GB: 1.1 ms).  The Jacobi's rounds use next to no memory
+// bandwidth: beside 60 of them the refresh of that set takes 12.83 -> 11.9 ms.  Where the
 // visits leave CUs to spare, a round is the latency of one visit and the clearing is better beside the factors, which have one
 // workgroup per matrix (60M set 1663 -> 1658 us beside the rounds, 1672 -> 1642 beside seven factors; the
 // 350M set 12.55 ms beside the factors, whose 88 idle CUs and 195 us are not enough for it).
+// Every workgroup has as many bytes as any other, a run of them across the matrices.  (With eight pieces per matrix one matrix had
+// eight workgroups: refresh of a 1024 x 128256 at rank 128, 1.06 GB of history, 10.90 ms, against 9.60 with a launch of its own and
+// 9.48 now; 40 of 1024 x 16384 at rank 64 4.27, 4.21, 4.00.)
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void clear_share(const MatDev* __restrict__ mats, int n_mats, const ClearShare& cs, int block) {
-    constexpr int kPieces = 8;                   // of a matrix's share, one workgroup's work at a time
     const u32x4_t zero = {0u, 0u, 0u, 0u};
-    for (int i = block; i < kPieces * n_mats; i += cs.blocks) {
-        const MatDev& md = mats[i / kPieces];
-        const unsigned long long n16 =
-            (((unsigned long long)md.slot_elems * (unsigned)cs.h_elem_bytes * (unsigned)(cs.s > 0 ? cs.s : 1) + 255ull) & ~255ull) / 16;
-        const unsigned piece = (unsigned)cs.part * kPieces + (unsigned)(i % kPieces), pieces = (unsigned)cs.parts * kPieces;
-        const unsigned long long last = n16 * (piece + 1) / pieces;
-        u32x4_t* __restrict__ h = reinterpret_cast<u32x4_t*>(md.H);
-        for (unsigned long long q = n16 * piece / pieces + threadIdx.x; q < last; q += blockDim.x) __builtin_nontemporal_store(zero, h + q);
-        if (piece == 0) {
-            u32x4_t* __restrict__ k = reinterpret_cast<u32x4_t*>(md.K);
-            for (unsigned long long q = threadIdx.x; q < cs.k_bytes / 16; q += blockDim.x) k[q] = zero;
+    unsigned long long at, end;
+    clear_range(cs, block, &at, &end);
+    if (at < end) {
+        // the last matrix that starts at or before the first unit
+        const int lane = threadIdx.x & 63;
+        int i = -1;
+        for (int b = 0; b < n_mats; b += 64) i += __popcll(__ballot(b + lane < n_mats && mats[b + lane < n_mats ? b + lane : 0].clear_off <= at));
+        for (; at < end; ++i) {
+            const MatDev& md = mats[i];
+            const unsigned long long behind = i + 1 < n_mats ? mats[i + 1].clear_off : cs.units, last = behind < end ? behind : end;
+            u32x4_t* __restrict__ h = reinterpret_cast<u32x4_t*>(md.H);
+            for (unsigned long long q = at - md.clear_off + threadIdx.x; q < last - md.clear_off; q += blockDim.x)
+                __builtin_nontemporal_store(zero, h + q);
+            at = last;
         }
     }
+    if (cs.part == 0)
+        for (int i = block; i < n_mats; i += cs.blocks) {
+            u32x4_t* __restrict__ k = reinterpret_cast<u32x4_t*>(mats[i].K);
+            for (unsigned long long q = threadIdx.x; q < cs.k_bytes / 16; q += blockDim.x) k[q] = zero;
+        }
 }
 
 //
@@ -1103,10 +1113,24 @@ static hipError_t run_factor(const MatDev* mats, const SymPlanes* sym, int n_mat
     return run_factor_blocks<FACTOR, 7, 6>(mats, sym, n_mats, nb, shift_rel, clear, status, stream);
 }
 
-int clear_share_blocks(int n_mats, int max_order, int max_pairs) {
-    if (max_order <= 32) return 512;             // (of one wavefront)
+// Workgroups that clear `bytes` beside a launch: as many as there are places, or fewer, so that each has about as much as it
+// stores while the launch lasts; spread wider, the stores hold up what the launch is there for.  Refresh (us) at 64 KB / 128 KB /
+// 256 KB / 512 KB / 1 MB / 2 MB / 4 MB each:
+//   orders up to 32: six 2048-wide blocks at rank 24 1706 / 1705 / 1723 / 1739 / 1844 / 2055 / 2430, one 1024 x 32000 1447 / 1445 / 1444 / 1456 /
+//     1488 / 1580 / 1783
+//   other factors: 60M set 1597 / 1596 / 1594 / 1590 / 1589 / 1590 / 1674, eight 1024 x 16384 at rank 128 2682 / 2681 / 2682 / 2680 / 2646 / 2620 / 2677,
+//     one 768 x 50257 4270 / 4286 / 4284 / 4257 / 4255 / 4256 / 4335
+//   rounds, at 256 KB / 512 KB / 768 KB / 1 MB / 2 MB: 350M set 11642 / 11593 / 11550 / 11576 / 12336, 130M set 6940 / 6921 / 6917 / 6916 / 7361
+constexpr unsigned long long kClearSmall = 128 << 10, kClearFactor = 1 << 20, kClearRound = 768 << 10;
+static int clear_blocks(unsigned long long bytes, unsigned long long each, int places) {
+    const unsigned long long wanted = (bytes + each - 1) / each;
+    return wanted < (unsigned)places ? (int)wanted : places;
+}
+
+int clear_share_blocks(int n_mats, int max_order, int max_pairs, unsigned long long bytes) {
+    if (max_order <= 32) return clear_blocks(bytes, kClearSmall, 512);
     if (max_order > kFactorMax || (long long)n_mats * max_pairs > 512 || n_mats > 192) return 0;
-    return 256 - n_mats;
+    return clear_blocks(bytes, kClearFactor, 256 - n_mats);
 }
 
 hipError_t launch_inverse_factor(GemmOp op, const MatDev* mats, const SymPlanes* sym, int n_mats, int max_order,
@@ -1970,8 +1994,9 @@ hipError_t launch_jacobi(const MatDev* mats, int n_mats, int max_pairs, int swee
         // The clearing, if there is some to do, goes beside the rounds of the first four sweeps, which nearly every matrix
         // needs, in the places that the visits leave on the chip.
         const int places = few ? 3 * 256 : 6 * 256, idle = (places - visits % places) % places;
-        clear.blocks = clear.parts == 0 || idle < 64 ? 0 : idle < 256 ? idle : 256;
+        const bool wanted = clear.parts > 0 && idle >= 64;
         clear.parts = (done < 4 ? done : 4) * (2 * max_pairs - 1);
+        clear.blocks = wanted ? clear_blocks(clear.units * 16 / (unsigned)clear.parts, kClearRound, idle < 256 ? idle : 256) : 0;
         *cleared = clear.blocks > 0;
         for (int sw = 0; sw < done; ++sw)
             for (int round = 0; round < 2 * max_pairs - 1; ++round) {

@@ -436,6 +436,7 @@ struct ng_state {
     char* ws;
     MatDev* d_mats;
     MatDyn* d_dyn;
+    unsigned long long clear_units;   // see ClearShare
     int* d_status;
     TileRef *d_proj, *d_upd, *d_dots, *d_patches, *d_skinny, *d_hist, *d_sketch[3];
     unsigned history_wait;   // see launch_history
@@ -818,6 +819,7 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
 
         st->mats.resize(n_mats);
         std::vector<TileRef> dots, dots_last;
+        st->clear_units = 0;
         size_t off = pl.off_scratch;
         st->max_m = st->max_n = st->max_r = st->max_l = st->max_lp = st->max_rows = st->max_ldn = 0;
         st->max_jpairs = 0;
@@ -837,6 +839,8 @@ int ng_init_state(const ng_matrix_desc* descs, const ng_matrix_buffers* bufs, in
             md.l = z.l; md.ldk = z.ldk; md.ldr = z.ldr; md.roct = z.roct;
             md.ld_w = descs[i].ld_w; md.ld_g = descs[i].ld_g;
             md.slot_elems = (long long)md.r * state_cols(z.ldn, z.pw);
+            md.clear_off = st->clear_units;
+            st->clear_units += z.bytes[NG_BUF_H] / 16;
             md.pw = z.pw;
             md.P = (float*)bufs[i].buf[NG_BUF_P];
             md.M = (float*)bufs[i].buf[NG_BUF_M];
@@ -1023,13 +1027,13 @@ int ng_refresh_projector(ng_state* st, const void* const* grads, ng_stream strea
     // the two passes of the last basis are one launch) or the Jacobi's rounds.
     ClearShare clear;
     memset(&clear, 0, sizeof(clear));
-    clear.s = st->hp.s;
-    clear.h_elem_bytes = hist_is_bf16(st->hp) ? 2 : 4;
+    clear.units = st->clear_units;
     clear.k_bytes = st->plan.sz[0].bytes[NG_BUF_K];
     bool cleared = false;
-    if (!carry) clear.blocks = clear_share_blocks(st->n_mats, st->max_l, st->max_jpairs);
+    const int factors = 2 * q + (st->plan.small_ortho[0] ? 2 : 3);
+    if (!carry) clear.blocks = clear_share_blocks(st->n_mats, st->max_l, st->max_jpairs, clear.units * 16 / (unsigned)factors);
     if (clear.blocks > 0) {
-        clear.parts = 2 * q + (st->plan.small_ortho[0] ? 2 : 3);
+        clear.parts = factors;
         cleared = true;
     }
     if ((rc = gradient_product(st, OP_G_B2A, q == 0, stream, sc)) != NG_OK) return rc;
@@ -1273,6 +1277,20 @@ int ng_debug_history_leaves(uint32_t tile, uint32_t not_started, uint32_t looks)
 int64_t ng_debug_history_lines(const ng_state* st, int mat) {
     if (!st || mat < 0 || mat >= st->n_mats || st->plan.hist_tiles[mat] == 0) return -1;
     return (int64_t)(st->plan.off_step + st->plan.sync_off[mat]);
+}
+
+// Not in the header, for tests: what one workgroup of a refresh clears, in 16-byte units of all history rings in a row.
+void ng_debug_clear_range(uint64_t units, int part, int parts, int blocks, int block, uint64_t* lo, uint64_t* hi) {
+    ClearShare cs;
+    memset(&cs, 0, sizeof(cs));
+    cs.part = part;
+    cs.parts = parts;
+    cs.blocks = blocks;
+    cs.units = units;
+    unsigned long long a, b;
+    clear_range(cs, block, &a, &b);
+    *lo = a;
+    *hi = b;
 }
 
 // Not in the header, for tests: bit 0 set where Ya and P are orthonormalised in one launch each, bit 1 where Yb is.

@@ -85,6 +85,7 @@ struct MatDev {
     // k_history: place of the matrix's HistoryLines in the step's scratch, and its tiles (0: see k_gram_row)
     long long hist_sync_off;
     int hist_tiles;
+    unsigned long long clear_off;   // 16-byte units of the history rings before this matrix's, in the table's order (see ClearShare)
 };
 
 // Per-step values: uploaded into the step's scratch block by a tiny kernel that receives them by value.
@@ -389,12 +390,18 @@ __host__ __device__ inline int ritz_place(const double* v, int n, int i, int fir
 }
 
 // Part `part` of `parts` of clearing the history ring of every matrix (and, in the first, the Gram blocks), done by extra
-// workgroups of a launch that leaves units and memory idle; parts == 0: none.
+// workgroups of a launch that leaves units and memory idle; parts == 0: none.  units: 16-byte units of all rings.
 struct ClearShare {
     int part, parts, blocks;
-    int s, h_elem_bytes;
-    unsigned long long k_bytes;
+    unsigned long long units, k_bytes;
 };
+// The units [lo, hi) that workgroup `block` of a part clears: all rings in a row, cut evenly, whatever the matrices' sizes, at
+// whole cache lines (refresh of the 350M set 11.99 ms, cut anywhere 12.19).
+__host__ __device__ inline void clear_range(const ClearShare& cs, int block, unsigned long long* lo, unsigned long long* hi) {
+    const unsigned long long a = cs.units * (unsigned)cs.part / (unsigned)cs.parts, n = cs.units * (unsigned)(cs.part + 1) / (unsigned)cs.parts - a;
+    *lo = (a + n * (unsigned)block / (unsigned)cs.blocks) & ~15ull;
+    *hi = (a + n * (unsigned)(block + 1) / (unsigned)cs.blocks) & ~15ull;
+}
 
 // refresh helpers (k_refresh.hip)
 // fills Yb (n x l), or, where a matrix has sketch planes, the first of them with the same values rounded to bf16
@@ -414,8 +421,8 @@ enum { kOrthoA, kOrthoB, kOrthoP };
 constexpr int kOrthoRows = 1024;
 hipError_t launch_orthonormalise_small(int which, int passes, double shift_rel, int planes, const MatDev* mats, int n_mats,
                                        ClearShare clear, int* status, hipStream_t stream);
-// extra workgroups of those launches that clearing is to have; 0 where it is better elsewhere
-int clear_share_blocks(int n_mats, int max_order, int max_pairs);
+// extra workgroups of those launches that clearing is to have, bytes in each launch; 0 where it is better elsewhere
+int clear_share_blocks(int n_mats, int max_order, int max_pairs, unsigned long long bytes);
 // the rows that the Jacobi starts from: L^T of T = B B^T = L L^T (planes of OP_B_BT)
 hipError_t launch_jacobi_prepare(const MatDev* mats, const SymPlanes* sym, int n_mats, int max_l, int max_lp, int* status,
                                  hipStream_t stream);

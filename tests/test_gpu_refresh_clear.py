@@ -17,6 +17,10 @@ pytestmark = pytest.mark.gpu
     ([(140, 150)] * 129 + [(141, 133)], 120, 2, {"dtype": "bf16", "hist_dtype": "bf16"}),   # beside the rounds, 520 visits
     ([(330, 350), (400, 417)], 300, 5, {"power_iters": 0}),                    # beside the rounds, order above 256
     ([(140, 150)] * 3, 120, 2, {"sweeps": 1, "power_iters": 0}),
+    ([(64, 9001)], 20, 4, {}),                                                 # one matrix, over all workgroups
+    ([(40, 61)] * 70 + [(64, 9001)] + [(40, 61)] * 70, 20, 3, {"dtype": "bf16"}),   # a wide one among more than 64
+    ([(140, 150)] * 65 + [(150, 4097)] + [(141, 133)], 120, 2, {"dtype": "bf16", "hist_dtype": "bf16"}),
+    ([(140, 150)] * 64 + [(150, 4097)] + [(140, 150)] * 64, 120, 2, {}),       # beside the rounds
     ([(130, 140)] * 383, 128, 1, {}),                                          # no room: 1536 visits
 ])
 def test_refresh_leaves_no_history(shapes, r, s, kw):

@@ -2187,13 +2187,16 @@ __global__ __launch_bounds__(32 * kSignRows) void k_sign_fix(const MatDev* __res
     }
 }
 
-// The copies beside the signs save a pass over P, but a workgroup goes down all rows of its columns, 256 at a time, where a launch of
-// their own has a workgroup per 32.  Refreshes with them apart and in here (us, each with the faster k_ritz_sort on the second
-// side, some 3 to 15 us): one 1024 x 1024 at rank 64 (2 workgroups) 647 -> 645, 2048 x 1024 725 -> 725, 4096 x 1024 890 -> 900,
-// 16000 x 512 1786 -> 1856; 8 of 8192 x 512 at rank 128 (32) 1959 -> 1973, 32 of them (128) 2862 -> 2834; the 60M set (224, up to 1376
-// rows) 1608 -> 1595, the 350M set (1344, 2736) 11.72 -> 11.64 ms.
+// The copies beside the signs save a launch and a pass over P, but a workgroup goes down all rows of its columns, 256 at a time,
+// where a launch of their own has a workgroup per 32.  Refreshes with the copies apart and beside, all else equal (us; runs of one
+// side differ by 1 or 2 in a thousand):
+//   few workgroups: 256 x 512 at rank 32 (1) 263.8 -> 261.2, 512 x 512 304.2 -> 303.3, 768 x 512 342.0 -> 342.2, 1024 x 512 378.9 -> 381.0,
+//     2048 x 1024 at rank 64 (2) 720.4 -> 725.8, 16000 x 512 1778 -> 1853
+//   32 of 1024 x 512 at rank 64 (64) 699.8 -> 700.5, 32 of 2048 x 512 (64) 840.2 -> 838.6, 72 of up to 3072 rows at rank 8 (72) 855.1 -> 861.7
+//   32 of 2048 x 512 at rank 128 (128) 1602 -> 1598, 4096 x 512 2062 -> 2048, 8192 x 512 2990 -> 2957, 16 of 16000 x 512 at rank 256 (128)
+//     7682 -> 7597, 60M set (224) 1615 -> 1610, 350M set (1344) 12.21 -> 12.16 ms
 bool sign_fix_copies(int n_mats, int max_m, int max_r) {
-    return max_m <= 1024 || (long long)((max_r + 31) / 32) * n_mats >= max_m / 64;
+    return max_m <= 512 || (long long)((max_r + 31) / 32) * n_mats >= 128;
 }
 
 hipError_t launch_sign_fix(const MatDev* mats, int n_mats, int max_r, bool copies, hipStream_t stream) {

@@ -12,10 +12,14 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("shapes,r,kw", [
     ([(40, 61), (33, 50), (257, 96)], [20, 32, 33], {}),                   # beside the signs: edges of columns, rows and 256-row runs
+    ([(512, 70), (255, 90), (256, 64)], [9, 64, 40], {}),                  # at most 512 rows
+    ([(513, 70)], [40], {}),                                               # one more, in few workgroups: apart
     ([(1024, 70), (255, 90), (256, 64)], [9, 64, 40], {}),
-    ([(1025, 80)], [40], {}),                                              # two workgroups of more than 1024 rows: apart
+    ([(1025, 80)], [40], {}),
     ([(1100, 60), (31, 1200)], [16, 31], {"sides": [B.NG_SIDE_LEFT, B.NG_SIDE_RIGHT]}),    # (right side: 1200 rows)
-    ([(1100, 60)] * 20, 17, {}),                                           # beside the signs, 20 workgroups
+    ([(1100, 60)] * 20, 17, {}),
+    ([(1100, 60)] * 127, 17, {}),                                          # apart, and with one workgroup more beside the signs
+    ([(1100, 60)] * 128, 17, {}),
     ([(300, 200)], [70], {"proj_dtype": "bf16"}),
 ])
 def test_bf16_copies_are_the_rounded_projector(shapes, r, kw):

@@ -566,7 +566,7 @@ template <bool FACTOR, int WAVES, int SLOTS>
 __global__ __launch_bounds__(64 * (WAVES + 1)) void k_inverse_factor(const MatDev* __restrict__ mats,
                                                            const SymPlanes* __restrict__ sym, double shift_rel, int max_nb,
                                                            int n_mats, ClearShare share, int* status) {
-    if ((int)blockIdx.x >= n_mats) {
+    if (!FACTOR && (int)blockIdx.x >= n_mats) {      // (nothing is cleared beside FACTOR: its launches come after the last share)
         clear_share(mats, n_mats, share, (int)blockIdx.x - n_mats);
         return;
     }
@@ -795,7 +795,7 @@ template <bool FACTOR>
 __global__ __launch_bounds__(64) void k_inverse_factor_small(const MatDev* __restrict__ mats,
                                                              const SymPlanes* __restrict__ sym,
                                                              double shift_rel, int n_mats, ClearShare share, int* status) {
-    if ((int)blockIdx.x >= n_mats) {
+    if (!FACTOR && (int)blockIdx.x >= n_mats) {      // (nothing is cleared beside FACTOR: its launches come after the last share)
         clear_share(mats, n_mats, share, (int)blockIdx.x - n_mats);
         return;
     }

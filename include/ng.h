@@ -209,7 +209,10 @@ int ng_commit_projector(ng_state* st, int clear_history, ng_stream stream);
  *   M, V <- Adam moments of g~ ;  N = update direction
  *   W <- W - lr * (scale * P N + weight_decay * W)
  * then t += 1, head = (head+1) mod s, count = min(count+1, s) on the host.
- * grads[i] read-only, weights[i] (m x n, ld_w, grad_dtype) updated in place. */
+ * grads[i] read-only, weights[i] (m x n, ld_w, grad_dtype) updated in place.
+ * The launches are cut for a GPU of 256 CUs to themselves.  On a partition of one, or beside work
+ * that holds its places, results are the same; matrices of several hundred tiles (ranks of 256 and
+ * more at widths from 2048 on) can then spend 0.1 ms and more waiting for places. */
 int ng_step(ng_state* st, const void* const* grads, void* const* weights, float lr,
             ng_stream stream);
 
@@ -224,8 +227,8 @@ int ng_step(ng_state* st, const void* const* grads, void* const* weights, float 
  * calls ordered on one stream, also from different handles, are fine (each call rewrites all it
  * reads; nothing in the array has to start at zero).  A layer set whose step scratch exceeds the
  * array returns NG_ERR_WORKSPACE (the per-matrix share is 2 KiB * s for the reduction -- up to
- * 4 KiB * s and 2.25 KiB where both passes over the history are one launch, which is only done where it fits -- plus, for
- * fp32 sets of rank <= 16, ceil(m/128) * rank class * ldn * 4 bytes; the row chunks that the projection of
+ * 4 KiB * s and 2.25 KiB where both passes over the history are one launch, which is only done,
+ * here and in ng_step, where it fits -- plus, for fp32 sets of rank <= 16, ceil(m/128) * rank class * ldn * 4 bytes; the row chunks that the projection of
  * small fp32 sets of larger rank is cut into are taken only where they fit); nothing is launched then.
  * Calls no hipMalloc / hipFree.  The first call on a GPU looks the array's address up
  * (hipGetSymbolAddress, once per device and process): make that call outside a graph capture.

@@ -13,10 +13,16 @@
 //   - tiles count themselves in and look for w on eight lines per matrix (on one, history phase of the 350M set
 //     1543 us, on eight 1099);
 //   - the slots that fit LDS go there, which makes room for a fourth workgroup per CU.
-// Without any waiting (results wrong) the 350M set's history phase takes 920 us, 195 at 130M, 54 at 60M; as it is 990, 190, 50;
-// in separate launches 1460, 310, 83.  Tried: the last tiles of a matrix too large for the chip kept and the others read
+// Kernel times (us, medians of 40 launches; without any waiting, results wrong / as it is / gram row, solve and transform in
+// separate launches): 60M set 52 / 54 / 84, 130M 196 / 213 / 311, 350M 922 / 1010 / 1471, the 2048-wide matrices of the 1.1B
+// set, of 512 tiles each, 1866 / 2485 / 2790.  Their bytes once at the 6.95 TB/s of a plain read: 39, 175, 768, 1485.
+// Tried: the last tiles of a matrix too large for the chip kept and the others read
 // twice in the same launch (1.1B set 6.0 ms against 5.8 in separate launches); fewer loads in flight per workgroup
 // (the same).
+//
+// No progress depends on workgroups being on the chip together (wait_for_weights).  The split counts on a whole chip, 256 CUs,
+// all the same: where others hold part of it, or the device is a partition, matrices of many tiles have workgroups that
+// have not started after 100 us, and lose that time and a second read of the tiles that give way.
 #include "state_math.h"
 
 namespace ng {
@@ -590,6 +596,13 @@ __global__ __launch_bounds__(256, OCC) void k_history(const MatDev* __restrict__
 // tiles) 20 times slower for want of places; at 8 float slots 344 -> 297 (384 tiles), 334 -> 303 (512); bf16 slots,
 // 16 of them 225 -> 193 (256), 244 -> 226 (384), 234 -> 233 (512); 8 of them 244 -> 224 (384), 238 -> 248 (512); 4 float slots
 // 237 -> 226 (384), 235 -> 248 (512).  fp32 sets at 4 slots 90 -> 88 (64), 139 -> 142 (256).
+// Every instance at its limit, sets of one and of six matrices of rank 512, then of rank 128 and four times the width:
+//   bf16 slots   4: 57 -> 53, 91 -> 84, 44 -> 41, 103 -> 98      8: 67 -> 62, 165 -> 148, 60 -> 55, 196 -> 182
+//               16: 78 -> 69, 223 -> 206, 69 -> 62, 246 -> 240
+//   float slots  4: 70 -> 63, 164 -> 146, 60 -> 55, 198 -> 183   8: 87 -> 68, 210 -> 186, 76 -> 59, 245 -> 223
+//               16: 92 -> 70, 206 -> 182, 77 -> 56, 229 -> 206
+//   fp32 sets    4: 52 -> 47, 104 -> 97, 45 -> 41, 116 -> 112    8: 64 -> 54, 173 -> 161, 61 -> 51, 204 -> 194
+//               16: 75 -> 58, 205 -> 199, 72 -> 55, 232 -> 232
 #define NG_HISTORY_CASES(X)                                     \
     if (hist_bf16) {                                            \
         if (s <= 4) X(4, 4, 0, 1, true, true, 4, 192);          \

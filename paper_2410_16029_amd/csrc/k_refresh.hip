@@ -522,8 +522,8 @@ __device__ __forceinline__ bool factor_diag(double* __restrict__ A, double* __re
 }
 
 // A workgroup's part of a ClearShare.  A CU stores 18 to 28 GB/s of zeros however many wavefronts it has at it, so a launch of
-// its own takes the whole chip to clear at 4.7 TB/s (350M set, 5.2 GB: 1.1 ms).  The Jacobi's rounds use next to no memory
-// bandwidth: beside 60 of them the refresh of that set takes 12.83 -> 11.9 ms.  Where the
+// its own takes the whole chip to clear at 4.7 to 5.9 TB/s (350M set, 5.2 GB with the padding of its panels: 0.89 ms).  The
+// Jacobi's rounds use next to no memory bandwidth: beside 60 of them the refresh of that set takes 12.83 -> 11.95 ms.  Where the
 // visits leave CUs to spare, a round is the latency of one visit and the clearing is better beside the factors, which have one
 // workgroup per matrix (60M set 1663 -> 1658 us beside the rounds, 1672 -> 1642 beside seven factors; the
 // 350M set 12.55 ms beside the factors, whose 88 idle CUs and 195 us are not enough for it).
